@@ -5,13 +5,18 @@
 //
 // Layer 0 (2 inputs) runs on the VALU in FP32 so the normalised ln E input is
 // not rounded to bf16 (its 8-bit mantissa would move a grid row by ~4 % in
-// E); layers 1.. run on the tiled BF16 MFMA GEMM with fused bias + SiLU (or
-// Softplus on the output) epilogues.  The backward chains the same GEMMs: dW
-// as dZ^T H with K split over workgroups (fixed-order sum), dH = dZ W with the
-// SiLU derivative fused into the epilogue, db and the layer-0 weights by
+// E).  Networks whose hidden widths are multiples of 128 up to 512 (the
+// paper's is) take the kernels of anet_fused.hip, which keep a row tile's
+// activations in LDS: at wider layers a tile's activations would not fit, and
+// other widths are not whole fragments per wave.  Those run layer by layer
+// here: the tiled BF16 MFMA GEMM with fused bias + SiLU (or Softplus on the
+// output) epilogues, and a backward that chains the same GEMMs: dW as dZ^T H
+// with K split over workgroups (fixed-order sum), dH = dZ W with the SiLU
+// derivative fused into the epilogue, db and the layer-0 weights by
 // fixed-order column reductions.
 #include <math.h>
 
+#include "anet_fused.hpp"
 #include "collide.hpp"
 #include "gemm.hpp"
 
@@ -47,6 +52,14 @@ static int check_anet(const dsmc_anet* net, AnetDims* a)
         if (l < a->L - 1 && a->d[l + 1] > a->dmax) a->dmax = a->d[l + 1];
     }
     return DSMC_OK;
+}
+
+static AnetShape shape_of(const AnetDims& a)
+{
+    AnetShape s{};
+    s.L = a.L;
+    for (int l = 0; l <= a.L; ++l) s.d[l] = a.d[l];
+    return s;
 }
 
 // Workspace of forward + backward on R rows.
@@ -356,6 +369,8 @@ extern "C" size_t dsmc_anet_ws(const dsmc_anet* net, int64_t rows)
 {
     AnetDims a;
     if (check_anet(net, &a) || rows < 0) return 0;
+    const AnetShape f = shape_of(a);
+    if (anet_fused_shape(f)) return anet_fused_layout(nullptr, f, rows).bytes + 256;
     return anet_layout(nullptr, a, rows).bytes + 256;
 }
 
@@ -370,6 +385,10 @@ extern "C" int dsmc_anet_forward(const dsmc_anet* net, int64_t rows, const float
     if (!x || !y || !ws) return arg_error("dsmc_anet_forward: null pointer");
     if (ws_bytes < dsmc_anet_ws(net, rows))
         return arg_error("dsmc_anet_forward: workspace %zu < %zu", ws_bytes, dsmc_anet_ws(net, rows));
+    const AnetShape f = shape_of(a);
+    if (anet_fused_shape(f))
+        return anet_fused_forward(net, f, rows, x, y, anet_fused_layout(ws, f, rows), true,
+                                  AnetGrid{0, 0}, false, as_stream(stream));
     const AnetWs w = anet_layout(ws, a, rows);
     return anet_forward_impl(net, a, rows, x, y, w, true, 0, nullptr, as_stream(stream));
 }
@@ -389,6 +408,9 @@ extern "C" int dsmc_anet_backward(const dsmc_anet* net, int64_t rows, const floa
         return arg_error("dsmc_anet_backward: workspace %zu < %zu", ws_bytes,
                          dsmc_anet_ws(net, rows));
     hipStream_t s = as_stream(stream);
+    const AnetShape f = shape_of(a);
+    if (anet_fused_shape(f))
+        return anet_fused_backward(net, f, rows, dy, dW, db, anet_fused_layout(ws, f, rows), s);
     const AnetWs w = anet_layout(ws, a, rows);
     int cur = 0;
     const int L = a.L;
@@ -481,6 +503,8 @@ extern "C" size_t dsmc_chi_table_ws(const dsmc_anet* net, const dsmc_chi_table* 
 {
     AnetDims a;
     if (check_anet(net, &a) || check_table(tab)) return 0;
+    const AnetShape f = shape_of(a);
+    if (anet_fused_shape(f)) return anet_fused_layout(nullptr, f, 1).bytes + 256;
     return anet_layout(nullptr, a, table_rows(tab)).bytes + 256;
 }
 
@@ -498,6 +522,11 @@ extern "C" int dsmc_chi_table_build(const dsmc_anet* net, const dsmc_chi_table* 
                          dsmc_chi_table_ws(net, tab));
     hipStream_t s = as_stream(stream);
     const int64_t total = (int64_t)tab->n_e * tab->n_b;
+    const AnetShape f = shape_of(a);
+    if (anet_fused_shape(f))
+        return anet_fused_forward(net, f, total, nullptr, tab->theta,
+                                  anet_fused_layout(ws, f, 1), false,
+                                  AnetGrid{tab->n_e, tab->n_b}, true, s);
     const int64_t RC = table_rows(tab);
     const AnetWs w = anet_layout(ws, a, RC);
     const TableGrid tg{tab->n_e, tab->n_b, tab->lne_lo, tab->lne_hi};

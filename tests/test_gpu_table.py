@@ -83,6 +83,33 @@ def test_anet_backward_matches_fp64(orc, dev, api):
         assert eW < 3e-2 and eb < 3e-2
 
 
+@pytest.mark.parametrize("dims", [(2, 128, 1), (2, 384, 128, 256, 1),
+                                  (2, 512, 512, 512, 256, 128, 1)])
+@pytest.mark.parametrize("rows", [1, 33, 8192, 8193, 32833])
+def test_anet_row_tiles_match_fp64(orc, dev, api, dims, rows):
+    """Forward and backward at the edges of the row tiles (32, 64 and 128 rows
+    per workgroup) and of the widths a layer's units are dealt to the waves
+    by.  Bounds as above: bf16 activations and deltas, 2^-8 per element."""
+    say("anet row tiles", dims, rows)
+    net, Wr, br = _net(api, dev, 5, dims)
+    rng = np.random.default_rng(rows)
+    x = np.stack([rng.uniform(-1, 1, rows), rng.uniform(0, 1, rows)], axis=1).astype(np.float32)
+    dy = rng.normal(0, 1.0 / rows, rows).astype(np.float32)
+    y, ws = api.anet_forward(net, torch.as_tensor(x, device=dev))
+    ref = orc.angle_net_forward(Wr, br, x.astype(np.float64))
+    err = np.abs(y.double().cpu().numpy() - ref)
+    assert np.sqrt(np.mean(err ** 2)) < 1e-2 * np.sqrt(np.mean(ref ** 2))
+    dW = [torch.full_like(w, float("nan")) for w in net.master_W]
+    db = [torch.full_like(b, float("nan")) for b in net.b]
+    api.anet_backward(net, torch.as_tensor(dy, device=dev), dW, db, ws)
+    rW, rb, _ = orc.angle_net_backward(Wr, br, x.astype(np.float64), dy.astype(np.float64))
+    for l in range(len(dims) - 1):
+        eW = np.linalg.norm(dW[l].double().cpu().numpy() - rW[l]) / np.linalg.norm(rW[l])
+        eb = np.linalg.norm(db[l].double().cpu().numpy() - rb[l]) / np.linalg.norm(rb[l])
+        say(f"  layer {l}: dW rel {eW:.2e}, db rel {eb:.2e}")
+        assert eW < 3e-2 and eb < 3e-2
+
+
 def test_huber_loss_matches_oracle(orc, dev, api):
     say("huber loss")
     rng = np.random.default_rng(2)
