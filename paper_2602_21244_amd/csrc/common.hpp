@@ -29,7 +29,7 @@ int device_cus();
 
 inline hipStream_t as_stream(dsmc_stream_t s) { return reinterpret_cast<hipStream_t>(s); }
 
-inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
+constexpr size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // --------------------------------------------------------------------------
 // Counter-based RNG: Philox4x32-10 (Salmon et al., SC'11), counter

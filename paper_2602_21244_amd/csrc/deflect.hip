@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "chi_quad.hpp"
+#include "chi_tab.hpp"
 #include "collide.hpp"
 
 namespace dsmc {
@@ -34,7 +35,8 @@ namespace dsmc {
 //     evaluated there; D'' at r_min by a central difference on two lanes.
 //  4. The sinh-mapped integral, its nodes spread over the lanes, summed by a
 //     fixed butterfly.
-__device__ double chi_refine_wave(const Pot& P, const QuadCfg& q, const GLRule& gl, double b,
+template <class PV>
+__device__ double chi_refine_wave(const PV& P, const QuadCfg& q, const GLRule& gl, double b,
                                   double E)
 {
     const int lane = threadIdx.x & 63;
@@ -42,7 +44,7 @@ __device__ double chi_refine_wave(const Pot& P, const QuadCfg& q, const GLRule& 
     s.b2 = b * b;
     s.E = E;
     double rtop, rho;
-    ref_grid(P, b, rtop, rho);
+    ref_grid(plain(P), b, rtop, rho);
     const double r = ref_sample_r(rtop, rho, lane);
     const double D = D_of<double>(P, s.b2, E, r);
     const double Dup = __shfl(D, lane > 0 ? lane - 1 : 0, 64);
@@ -172,27 +174,38 @@ k_refine(Job job, int64_t n, Pot P, QuadCfg q, GLRule gl, dsmc_status* st)
 template <typename T> __device__ __forceinline__ T pending_mark() { return T(INFINITY); }
 template <typename T> __device__ __forceinline__ bool is_pending(T x) { return x == T(INFINITY); }
 
-// Host-side potential set-up is costly for JAGER (grid search); cache the
-// last one.
+// Host-side potential set-up is costly for JAGER (grid search, and the check
+// that the table resolves it); cache the last one.
 static bool same_pot(const dsmc_potential& a, const dsmc_potential& b)
 {
     return memcmp(&a, &b, sizeof(a)) == 0;
 }
 
-static int get_pot(const dsmc_potential* pot, Pot* out)
+static const CtRule& ct_rule()
 {
-    static thread_local bool have = false;
+    static const CtRule r = [] {
+        CtRule x;
+        make_ct_rule(&x);
+        return x;
+    }();
+    return r;
+}
+
+// *tab: the kernels with the potential in a table apply.
+static int get_pot(const dsmc_potential* pot, Pot* out, bool* tab)
+{
+    static thread_local bool have = false, cached_tab = false;
     static thread_local Pot cached;
-    if (have && pot && same_pot(cached.p, *pot)) {
-        *out = cached;
-        return DSMC_OK;
-    }
-    int rc = make_pot(pot, out);
-    if (rc == DSMC_OK) {
+    if (!(have && pot && same_pot(cached.p, *pot))) {
+        const int rc = make_pot(pot, out);
+        if (rc) return rc;
         cached = *out;
+        cached_tab = ct_resolves(*out, ct_rule());
         have = true;
     }
-    return rc;
+    *out = cached;
+    *tab = cached_tab;
+    return DSMC_OK;
 }
 
 constexpr double KB = 1.380649e-23;
@@ -206,7 +219,334 @@ __device__ __forceinline__ void count_root_fail(dsmc_status* st)
 }
 
 // ------------------------------------------------------------------------
-// Kernels.  Each lane-pass kernel evaluates its items with the lane rule and
+// JAGER potentials in a table (chi_tab.hpp).  One workgroup of 16 waves per
+// CU builds the coefficients in LDS, one interval per thread (six direct
+// evaluations of V against the hundred of every pair), then each wave takes
+// 64 items at a time with the lane rule.  Flagged items go to a list in LDS
+// and the workgroup's waves share them, one item per wave at a time (they come
+// in runs: a wave that refined its own took up to 20 of its 64).  Chunks are
+// dealt to workgroups first, so a small batch spreads over the CUs.
+//
+// What bounds it: VALU issue, two thirds of the cycles (7 000 instructions per
+// 64 pairs in FP64, half of them FP64 arithmetic), then the table reads (48
+// bytes per lane and node in FP64, 16 in FP32, at random rows).  2^20 pairs in FP64: 0.39 ms (2.2 ms with V
+// evaluated directly and a second pass for the flagged pairs, bound by the
+// FP64 VALU); Phase A of 3.5 million pairs in FP32: 0.70 ms (3.3 ms).
+// ------------------------------------------------------------------------
+constexpr int TAB_THREADS = 1024;
+
+// Arguments of a table kernel: the node constants, which every lane reads as
+// uniform values, and half of the (symmetric) rule, which is unfolded in LDS
+// for the nodes that lanes take on their own.
+template <typename T> struct TabNode;
+template <> struct TabNode<double> { using type = CtNode; };
+template <> struct TabNode<float> { using type = CtNodeF; };
+template <typename T> struct TabArgs {
+    Pot P;
+    QuadCfg q;
+    CtRule rule;
+    int n;
+    double t[GL_MAX / 2], w[GL_MAX / 2];
+    typename TabNode<T>::type nd[GL_MAX];
+};
+
+template <typename T>
+static void tab_args(const Pot& P, const QuadCfg& q, const GLRule& gl, TabArgs<T>* a)
+{
+    a->P = P;
+    a->q = q;
+    a->rule = ct_rule();
+    a->n = gl.n;
+    for (int k = 0; k < (gl.n + 1) / 2; ++k) {
+        a->t[k] = gl.t[k];
+        a->w[k] = gl.w[k];
+    }
+    make_ct_nodes(gl, a->nd);
+}
+
+// LDS: FP64 coefficients, the rule, the list of items left for the workgroup
+// (from the front those to refine, from the back those whose range crosses
+// the branches' meeting point, with 1 / r_min), FP32 coefficients.
+struct TabList {
+    double b[TAB_THREADS], E[TAB_THREADS], w[TAB_THREADS];
+    int64_t i[TAB_THREADS];
+    int n, kinks;
+};
+constexpr size_t TAB_GL = sizeof(double) * CT_N * CT_C;
+constexpr size_t TAB_LIST = TAB_GL + align_up(sizeof(GLRule));
+constexpr size_t TAB_F32 = TAB_LIST + align_up(sizeof(TabList));
+template <typename T> constexpr size_t tab_lds()
+{
+    return TAB_F32 + (sizeof(T) == 4 ? sizeof(float) * CT_N * CT_CF : 0);
+}
+
+// Value of lane `src` (the same for the whole wave).
+__device__ __forceinline__ double lane_value(double x, int src)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, src);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// chi of one pair by the whole wave with V from the table: the steps of
+// chi_refine_wave in w = 1/r, where the nodes need no division, D'' comes
+// from the polynomial, and sinh and cosh of a node share one exponential.
+__device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& gl, double b,
+                                                 double E)
+{
+    const int lane = threadIdx.x & 63;
+    if (E == 0.0) return b < 1e300 ? Consts<double>::pi : NAN;   // a pair at rest: the limit
+    const double b2 = b * b, iE = 1.0 / E;
+    const double rtop = b > t.P.r_zero ? b : t.P.r_zero;
+    const double wtop = 1.0 / rtop;
+    const double w = wtop * exp(lane * (log(rtop / (0.98 * t.P.r_floor)) * (1.0 / (REF_SAMPLES - 1))));
+    const double D = 1.0 - b2 * (w * w) - ct_value<double>(t, w) * iE;
+    const double Dup = __shfl(D, lane > 0 ? lane - 1 : 0, 64);
+    const double Ddn = __shfl(D, lane < 63 ? lane + 1 : 63, 64);
+    const uint64_t neg = __ballot(D <= 0.0);
+    if (!neg) return NAN;
+    const int kneg = __ffsll((unsigned long long)neg) - 1;
+    double wa = lane_value(w, kneg > 0 ? kneg - 1 : 0), wb = lane_value(w, kneg);
+    const uint64_t mins = __ballot(lane >= 1 && lane < kneg && D < Dup && D < Ddn);
+    bool has_min = false;
+    double wm = 0.0, dm = 0.0, d2m = 0.0;
+    if (mins) {
+        const int k = __ffsll((unsigned long long)mins) - 1;
+        double a = lane_value(w, k - 1), c = lane_value(w, k + 1), fa = 0.0, fc = 0.0;
+        const double outer = a;
+        for (int rd = 0; rd < REF_ROUNDS; ++rd) {
+            const double x = ref_x(a, c, lane);
+            double dV;
+            ct_V<true>(t, x, dV);
+            const double f = -2.0 * b2 * x - dV * iE;
+            const uint64_t pos = __ballot(f >= 0.0);
+            const int L = ref_pick(pos ? __ffsll((unsigned long long)pos) - 1 : 64);
+            a = lane_value(x, L - 1);
+            c = lane_value(x, L);
+            fa = lane_value(f, L - 1);
+            fc = lane_value(f, L);
+        }
+        wm = (fc > fa) ? a - fa * (c - a) / (fc - fa) : 0.5 * (a + c);
+        wm = fmin(fmax(wm, a), c);
+        d2m = (fc - fa) / (c - a);
+        dm = 1.0 - b2 * (wm * wm) - ct_value<double>(t, wm) * iE;
+        if (dm <= 0.0) {   // the dip reaches zero: the largest root lies outside it
+            wa = outer;
+            wb = wm;
+        } else {
+            has_min = true;
+        }
+    }
+    // root of D in [wa, wb] (D(wa) > 0 >= D(wb); equal ends if D(wtop) <= 0)
+    double fl = 1.0, fh = -1.0;
+    for (int rd = 0; rd < REF_ROUNDS && wb > wa; ++rd) {
+        const double x = ref_x(wa, wb, lane);
+        const double f = 1.0 - b2 * (x * x) - ct_value<double>(t, x) * iE;
+        const uint64_t np = __ballot(!(f > 0.0));
+        const int L = ref_pick(np ? __ffsll((unsigned long long)np) - 1 : 64);
+        wa = lane_value(x, L - 1);
+        wb = lane_value(x, L);
+        fl = lane_value(f, L - 1);
+        fh = lane_value(f, L);
+    }
+    double w0 = (wb > wa && fl > fh) ? wa + fl * (wb - wa) / (fl - fh) : wb;
+    w0 = fmin(fmax(w0, wa), wb);
+    double dV, d2V;
+    const double Vmin = ct_V2(t, w0, dV, d2V), beta = b * w0;
+    // sinh map of t around the interior peak, else around t = 0, where
+    // F / t^2 ~ Q0 + Q2 t^2
+    double c = 0.0, h;
+    if (has_min && dm > 0.0 && wm < w0) {
+        c = sqrt(1.0 - wm / w0);
+        const double k = 2.0 * d2m * (w0 * c) * (w0 * c);
+        h = k > 0.0 ? sqrt(dm / k) : 1.0;
+    } else {
+        const double q0 = w0 * (2.0 * b2 * w0 + dV * iE);
+        const double q2 = 0.5 * w0 * w0 * (-2.0 * b2 - d2V * iE);
+        h = (q0 > 0.0 && q2 > 0.0) ? sqrt(q0 / q2) : 1.0;
+    }
+    if (!(h > 1e-12)) h = 1e-12;
+    if (h > 1.0) h = 1.0;
+    const double xl = c / h, xh = (1.0 - c) / h;
+    const double s_lo = c > 0.0 ? -log(xl + sqrt(xl * xl + 1.0)) : 0.0;
+    const double s_hi = log(xh + sqrt(xh * xh + 1.0));
+    const int per = REF_PANELS * gl.n, M = c > 0.0 ? 2 * per : per;
+    double I = 0.0, smax = 0.0;
+    int nonpos = 0;
+    for (int m = lane; m < M; m += 64) {
+        const int mm = m < per ? m : m - per;
+        const int pnl = mm / gl.n, j = mm - pnl * gl.n;
+        const double lo = m < per ? 0.0 : s_lo, hi = m < per ? s_hi : 0.0;
+        const double len = (hi - lo) * (1.0 / REF_PANELS);
+        const double e = exp(lo + len * (pnl + gl.t[j])), ei = 1.0 / e;
+        const double tt = c + 0.5 * h * (e - ei);
+        I += gl.w[j] * len * (0.5 * h * (e + ei)) *
+             ct_node<double>(t, w0, beta * beta, Vmin, iE, tt, smax, nonpos);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) I += __shfl_xor(I, o, 64);
+    return Consts<double>::pi - 2.0 * beta * I;
+}
+
+template <typename T>
+__device__ __forceinline__ TabPot tab_build(const TabArgs<T>& a, uint8_t* smem)
+{
+    double* c64 = reinterpret_cast<double*>(smem);
+    float* c32 = reinterpret_cast<float*>(smem + TAB_F32);
+    const CtScale s = ct_scale(a.P);
+    for (int i = threadIdx.x; i < CT_N; i += TAB_THREADS) {
+        double c[CT_C];
+        ct_build(a.P, s, a.rule, i, c);
+#pragma unroll
+        for (int k = 0; k < CT_C; ++k) c64[i * CT_C + k] = c[k];
+        if (sizeof(T) == 4) {
+            float o[CT_CF];
+            ct_build_f32(c, o);
+#pragma unroll
+            for (int k = 0; k < CT_CF; ++k) c32[i * CT_CF + k] = o[k];
+        }
+    }
+    return TabPot{a.P, s, c64, c32};
+}
+
+template <typename T>
+__device__ __forceinline__ const GLRule& tab_gl(const TabArgs<T>& a, uint8_t* smem)
+{
+    GLRule* g = reinterpret_cast<GLRule*>(smem + TAB_GL);
+    const int n = a.n, k = threadIdx.x;
+    if (k == 0) g->n = n;
+    if (k < n) {
+        const int h = k < n - 1 - k ? k : n - 1 - k;
+        g->t[k] = k <= n - 1 - k ? a.t[h] : 1.0 - a.t[h];
+        g->w[k] = a.w[h];
+    }
+    return *g;
+}
+
+// Job: count(n), the items; inputs(i, b, E) with b in Angstrom and E / k_B in
+// K (called by the item's lane, once); store(i, chi) and fail(i).
+template <typename T, class Job>
+__global__ void __launch_bounds__(TAB_THREADS)
+k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    n = job.count(n);
+    const int64_t chunks = (n + 63) >> 6;
+    if ((int64_t)blockIdx.x >= chunks) return;
+    TabList& list = *reinterpret_cast<TabList*>(smem + TAB_LIST);
+    const TabPot t = tab_build<T>(a, smem);
+    const GLRule& gl = tab_gl<T>(a, smem);
+    if (threadIdx.x == 0) list.n = list.kinks = 0;
+    __syncthreads();
+    constexpr int WAVES = TAB_THREADS / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lt = (1ull << lane) - 1;
+    // rounds of one chunk per wave of the grid: in a round, wave w of block b
+    // takes chunk w gridDim + b, moved on by a few blocks in each round so a
+    // wave does not meet the same part of a periodic input again
+    const int64_t per_round = (int64_t)gridDim.x * WAVES;
+    for (int64_t rd = 0; rd * per_round < chunks; ++rd) {
+        const int64_t blk = (blockIdx.x + 37 * rd) % gridDim.x;
+        const int64_t ch = rd * per_round + (int64_t)wave * gridDim.x + blk;
+        const int64_t i = ch * 64 + lane;
+        const bool active = i < n;
+        double b = 0.0, E = 1.0;
+        CtLane<T> c{T(0), false, 0.0};
+        if (active) {
+            job.inputs(i, b, E);
+            c = chi_tab_lane(t, a.q, gl, a.nd, b, E);
+        }
+        const bool pending = active && c.flag && a.q.refine;
+        const bool kink = active && !pending && c.kink_w > 0.0;
+        if (active && !pending && !kink) {
+            if (c.chi != c.chi) {
+                count_root_fail(st);
+                job.fail(i);
+            } else {
+                job.store(i, c.chi);
+            }
+        }
+        const uint64_t pend = __ballot(pending), kinks = __ballot(kink);
+        if (pend | kinks) {
+            int at = 0, ak = 0;
+            if (lane == 0) {
+                if (pend) at = atomicAdd(&list.n, (int)__popcll(pend));
+                if (kinks) ak = atomicAdd(&list.kinks, (int)__popcll(kinks));
+            }
+            at = __builtin_amdgcn_readfirstlane(at) + (int)__popcll(pend & lt);
+            ak = TAB_THREADS - 1 - (__builtin_amdgcn_readfirstlane(ak) + (int)__popcll(kinks & lt));
+            if (pending | kink) {
+                const int k = pending ? at : ak;
+                list.b[k] = b;
+                list.E[k] = E;
+                list.w[k] = c.kink_w;
+                list.i[k] = i;
+            }
+        }
+        __syncthreads();
+        const int pairs = list.n, nk = list.kinks;
+        for (int k = wave; k < pairs; k += WAVES) {
+            const double cr = ct_refine_wave(t, gl, list.b[k], list.E[k]);
+            if (lane == 0) {
+                if (cr != cr) {
+                    count_root_fail(st);
+                    job.fail(list.i[k]);
+                } else {
+                    job.store(list.i[k], cr);
+                }
+            }
+        }
+        // eight lanes per kinked pair
+        for (int k = threadIdx.x >> 3; k < nk; k += TAB_THREADS / 8) {
+            const int e = TAB_THREADS - 1 - k;
+            const double w = list.w[e], beta = list.b[e] * w, iE = 1.0 / list.E[e];
+            const double Vmin = ct_value<double>(t, w), tsw = sqrt(1.0 - t.s.w_sw / w);
+            double I = 0.0;
+            for (int m = threadIdx.x & 7; m < 2 * gl.n; m += 8)
+                I += ct_kink_node(t, gl, w, beta, Vmin, iE, tsw, m);
+            I += __shfl_xor(I, 1, 64);
+            I += __shfl_xor(I, 2, 64);
+            I += __shfl_xor(I, 4, 64);
+            const double cr = Consts<double>::pi - 2.0 * beta * I;
+            if ((threadIdx.x & 7) == 0) {
+                if (cr != cr) {
+                    count_root_fail(st);
+                    job.fail(list.i[e]);
+                } else {
+                    job.store(list.i[e], cr);
+                }
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) list.n = list.kinks = 0;
+        // (the next append comes after each wave's lane rule; a barrier keeps
+        // a fast wave's from meeting the old counts)
+        __syncthreads();
+    }
+}
+
+template <typename T, class Job>
+static int launch_tab(const Job& job, int64_t n, const Pot& P, const QuadCfg& q, const GLRule& gl,
+                      dsmc_status* st, hipStream_t s, const char* what)
+{
+    TabArgs<T> a;
+    tab_args(P, q, gl, &a);
+    static_assert(sizeof(TabArgs<T>) + sizeof(Job) + 16 <= 4096, "kernel arguments");
+    const size_t lds = tab_lds<T>();
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_chi_tab<T, Job>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_check(e, what);
+    const int64_t chunks = (n + 63) / 64, cus = device_cus();
+    k_chi_tab<T, Job><<<(unsigned)(chunks < cus ? chunks : cus), TAB_THREADS, lds, s>>>(job, n, a,
+                                                                                       st);
+    DSMC_LAUNCH_CHECK(what);
+    return DSMC_OK;
+}
+
+// ------------------------------------------------------------------------
+// Direct kernels (other potentials, and JAGER parameters that the table does
+// not resolve).  Each lane-pass kernel evaluates its items with the lane rule and
 // leaves the flagged ones pending; k_refine with the matching job finishes
 // them.
 // ------------------------------------------------------------------------
@@ -386,6 +726,18 @@ __device__ __forceinline__ void harvest_b_E(const double* vr, const double* z, d
     E = half_m_over_k * (v0 * v0 + v1 * v1 + v2 * v2);
 }
 
+__device__ __forceinline__ void harvest_inputs(const double* vr, const double* xi,
+                                               const double* z, double inv_sv, int64_t r,
+                                               float* x_out, float* g_out)
+{
+    const double v0 = vr[3 * r], v1 = vr[3 * r + 1], v2 = vr[3 * r + 2];
+    float* xo = x_out + 8 * r;
+    xo[0] = (float)(v0 * inv_sv); xo[1] = (float)(v1 * inv_sv); xo[2] = (float)(v2 * inv_sv);
+    xo[3] = (float)xi[3 * r]; xo[4] = (float)xi[3 * r + 1]; xo[5] = (float)xi[3 * r + 2];
+    xo[6] = (float)z[2 * r]; xo[7] = (float)z[2 * r + 1];
+    g_out[r] = (float)sqrt(v0 * v0 + v1 * v1 + v2 * v2);
+}
+
 __global__ void __launch_bounds__(256)
 k_harvest(int64_t B, const double* __restrict__ vr, const double* __restrict__ xi,
           const double* __restrict__ z, double inv_sv, double b_max_A, double half_m_over_k,
@@ -394,14 +746,9 @@ k_harvest(int64_t B, const double* __restrict__ vr, const double* __restrict__ x
 {
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < B;
          r += (int64_t)gridDim.x * blockDim.x) {
-        const double v0 = vr[3 * r], v1 = vr[3 * r + 1], v2 = vr[3 * r + 2];
         double bb, E;
         harvest_b_E(vr, z, b_max_A, half_m_over_k, r, bb, E);
-        float* xo = x_out + 8 * r;
-        xo[0] = (float)(v0 * inv_sv); xo[1] = (float)(v1 * inv_sv); xo[2] = (float)(v2 * inv_sv);
-        xo[3] = (float)xi[3 * r]; xo[4] = (float)xi[3 * r + 1]; xo[5] = (float)xi[3 * r + 2];
-        xo[6] = (float)z[2 * r]; xo[7] = (float)z[2 * r + 1];
-        g_out[r] = (float)sqrt(v0 * v0 + v1 * v1 + v2 * v2);
+        harvest_inputs(vr, xi, z, inv_sv, r, x_out, g_out);
         bool flag;
         const double c = chi_lane<double>(P, q, gl, bb, E, flag);
         if (flag && q.refine) {
@@ -427,6 +774,77 @@ struct HarvestJob {
         harvest_b_E(vr, z, b_max_A, half_m_over_k, r, bb, E);
     }
     __device__ void store(int64_t r, double c) const { harvest_target(vr, xi, r, c, tgt, chi_out); }
+};
+
+// Jobs of the table kernel.
+template <typename T>
+struct DeflectTab {
+    const T* b;
+    const T* g;
+    T* chi;
+    double half_m_over_k;
+    int fold;
+    __device__ int64_t count(int64_t n) const { return n; }
+    __device__ void inputs(int64_t p, double& bb, double& E) const
+    {
+        const double gg = double(g[p]);
+        bb = double(b[p]) * 1e10;
+        E = half_m_over_k * gg * gg;
+    }
+    template <typename U> __device__ void store(int64_t p, U c) const
+    {
+        chi[p] = T(fold ? acos(cos(c)) : c);
+    }
+    __device__ void fail(int64_t p) const { chi[p] = T(NAN); }
+};
+
+template <typename T>
+struct PhaseAJagerTab {
+    PairsView pr;
+    dsmc_rng rng;
+    V3<const T> v;
+    double half_m_over_k, b_max_A;
+    PairBuf<T> out;
+    int32_t n_cells;
+    __device__ int64_t count(int64_t n) const
+    {
+        const int64_t np = pr.total(n_cells);
+        return np < n ? np : n;
+    }
+    __device__ void inputs(int64_t p, double& bb, double& E) const
+    {
+        T xi[3];
+        pair_b_E<T>(pr, rng, v, half_m_over_k, b_max_A, p, xi, bb, E);
+        out.c[p] = xi[0];
+        out.d[p] = xi[1];
+        out.e[p] = xi[2];
+    }
+    template <typename U> __device__ void store(int64_t p, U c) const
+    {
+        out.a[p] = T(cos(c));
+        out.b[p] = T(sin(c));
+    }
+    // no deflection for a failed evaluation
+    __device__ void fail(int64_t p) const { store(p, T(0)); }
+};
+
+struct HarvestTab {
+    const double* vr;
+    const double* xi;
+    const double* z;
+    double inv_sv, b_max_A, half_m_over_k;
+    float* x_out;
+    float* g_out;
+    float* tgt;
+    double* chi_out;
+    __device__ int64_t count(int64_t n) const { return n; }
+    __device__ void inputs(int64_t r, double& bb, double& E) const
+    {
+        harvest_b_E(vr, z, b_max_A, half_m_over_k, r, bb, E);
+        harvest_inputs(vr, xi, z, inv_sv, r, x_out, g_out);
+    }
+    __device__ void store(int64_t r, double c) const { harvest_target(vr, xi, r, c, tgt, chi_out); }
+    __device__ void fail(int64_t r) const { store(r, NAN); }
 };
 
 template <class Job>
@@ -455,7 +873,8 @@ extern "C" int dsmc_deflect_jager(int64_t n, int32_t dtype, const void* b, const
     if (n > 0 && (!b || !g || !chi)) return arg_error("dsmc_deflect_jager: null pointer");
     if (!(m_red > 0)) return arg_error("dsmc_deflect_jager: m_red must be > 0");
     Pot P;
-    int rc = get_pot(pot, &P);
+    bool tab;
+    int rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
     GLRule gl;
@@ -464,17 +883,25 @@ extern "C" int dsmc_deflect_jager(int64_t n, int32_t dtype, const void* b, const
     if (n == 0) return DSMC_OK;
     const double hmk = 0.5 * m_red / KB;
     hipStream_t s = as_stream(stream);
+    if (dtype != DSMC_F64 && dtype != DSMC_F32)
+        return arg_error("dsmc_deflect_jager: dtype %d", dtype);
+    if (tab && dtype == DSMC_F64)
+        return launch_tab<double>(DeflectTab<double>{(const double*)b, (const double*)g,
+                                                     (double*)chi, hmk, fold},
+                                  n, P, q, gl, st, s, "deflect_jager");
+    if (tab)
+        return launch_tab<float>(DeflectTab<float>{(const float*)b, (const float*)g, (float*)chi,
+                                                   hmk, fold},
+                                 n, P, q, gl, st, s, "deflect_jager");
     int blocks = (int)((n + 255) / 256);
     const int pb = persistent_blocks(256);
     if (blocks > pb) blocks = pb;
     if (dtype == DSMC_F64) {
         k_deflect_f64<<<blocks, 256, 0, s>>>(n, (const double*)b, (const double*)g,
                                                  (double*)chi, hmk, P, q, gl, fold, st);
-    } else if (dtype == DSMC_F32) {
+    } else {
         k_deflect_f32<<<blocks, 256, 0, s>>>(n, (const float*)b, (const float*)g, (float*)chi,
                                                 hmk, P, q, gl, fold, st);
-    } else {
-        return arg_error("dsmc_deflect_jager: dtype %d", dtype);
     }
     DSMC_LAUNCH_CHECK("deflect_jager");
     if (dtype == DSMC_F64)
@@ -497,7 +924,8 @@ extern "C" int dsmc_collide_jager(int32_t n_cells, int32_t dtype, dsmc_vec3 v, d
     if (schedule < DSMC_SCHED_AUTO || schedule > DSMC_SCHED_WAVE)
         return arg_error("dsmc_collide_jager: schedule %d", schedule);
     Pot P;
-    rc = get_pot(pot, &P);
+    bool tab;
+    rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
     GLRule gl;
@@ -507,6 +935,21 @@ extern "C" int dsmc_collide_jager(int32_t n_cells, int32_t dtype, dsmc_vec3 v, d
     const PairsView pr = PairsView::of(pairs);
     const int pb = persistent_blocks(256);
     const double hmk = 0.5 * m_red / KB;
+    if (tab) {
+        if (dtype == DSMC_F64)
+            rc = launch_tab<double>(
+                PhaseAJagerTab<double>{pr, rng, v3<const double>(v), hmk, b_max * 1e10,
+                                       PairBuf<double>::of(ws, pairs.cap), n_cells},
+                pairs.cap, P, q, gl, st, s, "collide_jager:phaseA");
+        else
+            rc = launch_tab<float>(
+                PhaseAJagerTab<float>{pr, rng, v3<const float>(v), hmk, b_max * 1e10,
+                                      PairBuf<float>::of(ws, pairs.cap), n_cells},
+                pairs.cap, P, q, gl, st, s, "collide_jager:phaseA");
+        if (rc) return rc;
+        if (schedule == DSMC_SCHED_DEFER) return DSMC_OK;
+        return phase_b(RULE_CHI, dtype, n_cells, nullptr, v, pairs, ws, pairs.cap, schedule, s);
+    }
     if (dtype == DSMC_F64) {
         k_phaseA_jager_f64<<<pb, 256, 0, s>>>(n_cells, pr, rng, v3<const double>(v), hmk,
                                                  b_max * 1e10, P, q, gl,
@@ -542,13 +985,18 @@ extern "C" int dsmc_harvest_rows(int64_t B, const double* vr, const double* xi, 
     if (!(sigma_v > 0) || !(b_max > 0) || !(m_red > 0))
         return arg_error("dsmc_harvest_rows: sigma_v, b_max, m_red must be > 0");
     Pot P;
-    int rc = get_pot(pot, &P);
+    bool tab;
+    int rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
     GLRule gl;
     rc = make_cfg(quad, &q, &gl);
     if (rc) return rc;
     if (B == 0) return DSMC_OK;
+    if (tab)
+        return launch_tab<double>(HarvestTab{vr, xi, z, 1.0 / sigma_v, b_max * 1e10,
+                                             0.5 * m_red / KB, x_out, g_out, target_out, chi_out},
+                                  B, P, q, gl, st, as_stream(stream), "harvest_rows");
     int blocks = (int)((B + 255) / 256);
     const int pb = persistent_blocks(256);
     if (blocks > pb) blocks = pb;
@@ -667,15 +1115,58 @@ k_q2_terms(int64_t n_items, int n_b, const double* __restrict__ E_kelvin, double
     }
 }
 
-// Q2[i] = 2 pi sum_j terms[i][j] (fixed order), in m^2.
+// The same terms by the table kernel, for rules of up to Q2_TAB_GL nodes a
+// panel: half of a longer one would not fit the 4 KB of kernel arguments
+// beside the table kernel's own.
+constexpr int Q2_TAB_GL = 32;
+struct Q2Tab {
+    const double* E_kelvin;
+    double* terms;
+    int n_b, bn;
+    double h;                     // panel width
+    double t[Q2_TAB_GL / 2], w[Q2_TAB_GL / 2];   // half of the (symmetric) rule of a panel
+    __device__ void inputs(int64_t it, double& b, double& E) const
+    {
+        const int64_t i = it / n_b;
+        const int j = (int)(it - i * n_b), pnl = j / bn, node = j - pnl * bn;
+        const int o = bn - 1 - node, m = node < o ? node : o;
+        b = h * (pnl + (node <= o ? t[m] : 1.0 - t[m]));
+        E = E_kelvin[i];
+    }
+    __device__ int64_t count(int64_t n) const { return n; }
+    __device__ void store(int64_t it, double c) const
+    {
+        const int64_t i = it / n_b;
+        const int j = (int)(it - i * n_b), pnl = j / bn, node = j - pnl * bn;
+        const int o = bn - 1 - node, m = node < o ? node : o;
+        const double b = h * (pnl + (node <= o ? t[m] : 1.0 - t[m])), cc = cos(c);
+        terms[it] = h * w[m] * (1.0 - cc * cc) * b;
+    }
+    // a failed evaluation counts as no deflection
+    __device__ void fail(int64_t it) const { store(it, 0.0); }
+};
+
+// Q2[i] = 2 pi sum_j terms[i][j] in m^2, one wave per energy: lane l adds
+// terms l, l + 64, .. and the lanes are added by the fixed butterfly.  (One
+// thread per energy read the rows uncoalesced: 255 us for 1 024 energies of
+// 2 048 terms against 5 us.)
 __global__ void __launch_bounds__(256)
 k_q2_sum(int64_t n_E, int n_b, const double* __restrict__ terms, double* __restrict__ Q)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_E;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+    const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t i = wave; i < n_E; i += n_waves) {
         double s = 0.0;
-        for (int j = 0; j < n_b; ++j) s += terms[i * n_b + j];
-        Q[i] = 2.0 * 3.14159265358979323846 * s * 1e-20;
+        int j = lane;
+        for (; j + 192 < n_b; j += 256) {
+            const double a0 = terms[i * n_b + j], a1 = terms[i * n_b + j + 64];
+            const double a2 = terms[i * n_b + j + 128], a3 = terms[i * n_b + j + 192];
+            s += a0; s += a1; s += a2; s += a3;
+        }
+        for (; j < n_b; j += 64) s += terms[i * n_b + j];
+        s = wave_sum(s);
+        if (lane == 0) Q[i] = 2.0 * 3.14159265358979323846 * s * 1e-20;
     }
 }
 
@@ -705,7 +1196,8 @@ static int q2_impl(int64_t n_E, const double* E, double b_cut, int n_panels, int
                    dsmc_status* st, hipStream_t s)
 {
     Pot P;
-    int rc = get_pot(pot, &P);
+    bool tab;
+    int rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
     GLRule gl, bgl;
@@ -717,12 +1209,23 @@ static int q2_impl(int64_t n_E, const double* E, double b_cut, int n_panels, int
     const int64_t items = n_E * (int64_t)n_b;
     double* terms = static_cast<double*>(ws);
     const int pb = persistent_blocks(256);
-    int64_t blocks = (items + 255) / 256;
-    if (blocks > pb) blocks = pb;
-    k_q2_terms<<<(int)(blocks < 1 ? 1 : blocks), 256, 0, s>>>(items, n_b, E, b_cut * 1e10,
-                                                              n_panels, bgl, P, q, gl, terms, st);
-    DSMC_LAUNCH_CHECK("q2:terms");
-    k_q2_sum<<<(int)((n_E + 255) / 256), 256, 0, s>>>(n_E, n_b, terms, Q);
+    if (tab && bgl.n <= Q2_TAB_GL) {
+        Q2Tab job{E, terms, n_b, bgl.n, b_cut * 1e10 / n_panels, {}, {}};
+        for (int k = 0; k < (bgl.n + 1) / 2; ++k) {
+            job.t[k] = bgl.t[k];
+            job.w[k] = bgl.w[k];
+        }
+        rc = launch_tab<double>(job, items, P, q, gl, st, s, "q2:terms");
+        if (rc) return rc;
+    } else {
+        int64_t blocks = (items + 255) / 256;
+        if (blocks > pb) blocks = pb;
+        k_q2_terms<<<(int)(blocks < 1 ? 1 : blocks), 256, 0, s>>>(
+            items, n_b, E, b_cut * 1e10, n_panels, bgl, P, q, gl, terms, st);
+        DSMC_LAUNCH_CHECK("q2:terms");
+    }
+    const int64_t sb = (n_E + 3) / 4;
+    k_q2_sum<<<(int)(sb < pb ? sb : pb), 256, 0, s>>>(n_E, n_b, terms, Q);
     DSMC_LAUNCH_CHECK("q2:sum");
     return DSMC_OK;
 }

@@ -67,3 +67,17 @@ def test_jager_cross_section_and_viscosity_match_oracle(orc, dev, api):
     say("  mu (Pa s)", mu.cpu().numpy(), "oracle", mo)
     np.testing.assert_allclose(om.cpu().numpy(), oo, rtol=1e-6)
     np.testing.assert_allclose(mu.cpu().numpy(), mo, rtol=1e-6)
+
+
+def test_cross_section_routes_agree(dev, api):
+    """Rules of up to 32 nodes a panel take the potential's table, longer ones
+    the direct kernel: the same integral by 64 panels of 32 nodes and by 32 of
+    64 (2 048 nodes each) agrees to the b rule's own convergence, which 48 of
+    32 against 64 of 32 bounds."""
+    E = torch.tensor([150.0, 300.0, 1000.0, 20000.0], dtype=torch.float64, device=dev)
+    pot = api.potential_jager(W.JAGER_PLACEHOLDER)
+    a = api.transport_q2(E, 2.5e-9, pot, n_panels=64, n_gl=32).cpu().numpy()
+    b = api.transport_q2(E, 2.5e-9, pot, n_panels=32, n_gl=64).cpu().numpy()
+    c = api.transport_q2(E, 2.5e-9, pot, n_panels=48, n_gl=32).cpu().numpy()
+    say("  Q2 routes: rel", np.abs(b / a - 1).max(), "48 panels:", np.abs(c / a - 1).max())
+    assert np.all(np.abs(b / a - 1) <= 1e-9 + 4 * np.abs(c / a - 1))

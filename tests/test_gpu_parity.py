@@ -5,6 +5,7 @@ bit-exact; FP64 velocities agree to 1e-12 and FP32 to 1e-5, relative to the
 population's velocity scale; the BF16 surrogate agrees with FP64 inference of
 the same weights to a direction (chi) RMS <= 1e-2 rad.
 """
+import dataclasses
 import math
 import sys
 
@@ -444,6 +445,36 @@ def test_deflect_jager_against_oracle(orc, dev, api, dtype):
     s = api.read_status(st)
     assert s.root_fail == 0 and np.all(np.isfinite(got))
     check_chi(got, ref, "f64" if dtype == torch.float64 else "f32", "batch 8192")
+
+
+@pytest.mark.parametrize("change,g_hi", [({}, 2e5), ({"a1": -3.2}, 2000.0),
+                                         ({"a1": -11.7, "A": 4e20}, 500.0)])
+@pytest.mark.parametrize("n", [1, 64, 2049])
+def test_deflect_potential_table_edges(orc, dev, api, n, change, g_hi):
+    """Pairs on both sides of the branches' meeting point and beyond the end of
+    the potential's table (g up to 2e5 m/s), slow and distant ones, at sizes
+    around a wave and a workgroup; parameters that the table resolves, and a
+    wall so steep that it does not (it takes the direct kernels); the two changed
+    sets have a step of V at the meeting point and stay at speeds clear of it.
+    Bounds as above."""
+    say("deflect jager, table edges", n, change)
+    rng = np.random.default_rng(n)
+    g = np.exp(rng.uniform(np.log(150.0), np.log(g_hi), n))
+    b = rng.uniform(0.0, 2.5e-9, n) * rng.random(n)
+    b[0] = 0.0
+    p = dataclasses.replace(W.JAGER_PLACEHOLDER, **change)
+    ref, bad = orc.chi_batch(orc.potential_jager(p), b, g, W.AR_MASS / 2, n_threads=8)
+    ok = bad == 0
+    for dtype, kind in ((torch.float64, "f64"), (torch.float32, "f32")):
+        if kind == "f32":
+            bb, gg = b.astype(np.float32), g.astype(np.float32)
+            ref, bad = orc.chi_batch(orc.potential_jager(p), bb.astype(np.float64),
+                                     gg.astype(np.float64), W.AR_MASS / 2, n_threads=8)
+        else:
+            bb, gg = b, g
+        got = api.deflect_jager(torch.as_tensor(bb, device=dev), torch.as_tensor(gg, device=dev),
+                                W.AR_MASS / 2, api.potential_jager(p)).double().cpu().numpy()
+        check_chi(got[ok], ref[ok], kind, f"{n} {kind}")
 
 
 def test_deflect_refinement_off_is_worse(orc, dev, api):
