@@ -131,19 +131,9 @@ __device__ __forceinline__ int block_excl_scan(int x, int* total)
     return base + inc - x;
 }
 
-__device__ __forceinline__ int64_t scan_n(int64_t n, const int64_t* n_dev, int64_t n_max)
-{
-    if (n_dev) {
-        int64_t v = *n_dev;
-        return v < 0 ? 0 : (v > n_max ? n_max : v);
-    }
-    return n;
-}
-
 __global__ void __launch_bounds__(SCAN_THREADS)
-k_scan_reduce(const int32_t* in, int64_t n, const int64_t* n_dev, int32_t* tile_sums)
+k_scan_reduce(const int32_t* in, int64_t n, int32_t* tile_sums)
 {
-    n = scan_n(n, n_dev, n);
     const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
     int s = 0;
     if (base < n) {
@@ -174,15 +164,10 @@ k_scan_tiles(int32_t* tile_sums, int64_t n_tiles)
 }
 
 __global__ void __launch_bounds__(SCAN_THREADS)
-k_scan_down(const int32_t* in, int32_t* out, int64_t n, const int64_t* n_dev, int64_t n_max,
-            const int32_t* tile_off, int64_t n_tiles, int64_t* total64)
+k_scan_down(const int32_t* in, int32_t* out, int64_t n, const int32_t* tile_off, int64_t n_tiles)
 {
-    n = scan_n(n, n_dev, n_max);
     const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        out[n] = tile_off[n_tiles];
-        if (total64) *total64 = tile_off[n_tiles];
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = tile_off[n_tiles];
     if (base >= n) return;
     // blocked arrangement: thread t owns items [t*ITEMS, (t+1)*ITEMS)
     int v[SCAN_ITEMS];
@@ -207,34 +192,18 @@ size_t scan_ws_bytes(int64_t n)
     return align_up(sizeof(int32_t) * (size_t)(tiles + 1));
 }
 
-static int scan_impl(const int32_t* in, int32_t* out, int64_t n, const int64_t* n_dev,
-                     int64_t n_max, int64_t* total64, void* ws, hipStream_t s)
+int exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, void* ws, hipStream_t s)
 {
-    const int64_t n_cap = n_dev ? n_max : n;
-    const int64_t tiles = (n_cap + SCAN_TILE - 1) / SCAN_TILE;
+    const int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
     int32_t* tile = static_cast<int32_t*>(ws);
     const int grid = (int)(tiles > 0 ? tiles : 1);
-    // reduce: tiles beyond the device count contribute 0
-    k_scan_reduce<<<grid, SCAN_THREADS, 0, s>>>(in, n_cap, n_dev, tile);
+    k_scan_reduce<<<grid, SCAN_THREADS, 0, s>>>(in, n, tile);
     DSMC_LAUNCH_CHECK("scan_reduce");
     k_scan_tiles<<<1, SCAN_THREADS, 0, s>>>(tile, grid);
     DSMC_LAUNCH_CHECK("scan_tiles");
-    k_scan_down<<<grid, SCAN_THREADS, 0, s>>>(in, out, n_cap, n_dev, n_max, tile, grid,
-                                              total64);
+    k_scan_down<<<grid, SCAN_THREADS, 0, s>>>(in, out, n, tile, grid);
     DSMC_LAUNCH_CHECK("scan_down");
     return DSMC_OK;
-}
-
-int exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, int64_t* total64, void* ws,
-                       hipStream_t s)
-{
-    return scan_impl(in, out, n, nullptr, n, total64, ws, s);
-}
-
-int exclusive_scan_i32_dev(const int32_t* in, int32_t* out, const int64_t* n_dev, int64_t n_max,
-                           void* ws, hipStream_t s)
-{
-    return scan_impl(in, out, n_max, n_dev, n_max, nullptr, ws, s);
 }
 
 }  // namespace dsmc

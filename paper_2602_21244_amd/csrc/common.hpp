@@ -252,13 +252,9 @@ template <typename T> inline V3<T> v3(dsmc_vec3 v)
 }
 
 // Device-wide exclusive scan of int32 counts into int32 offsets (n+1 outputs:
-// out[n] = total); also stores the total as int64 to *total64 when given.
+// out[n] = total).
 size_t scan_ws_bytes(int64_t n);
-int exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, int64_t* total64, void* ws,
-                       hipStream_t s);
-// Same with a device-side element count (n_dev) bounded by n_max.
-int exclusive_scan_i32_dev(const int32_t* in, int32_t* out, const int64_t* n_dev, int64_t n_max,
-                           void* ws, hipStream_t s);
+int exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, void* ws, hipStream_t s);
 
 // Fill kernels (graph-safe replacements of memset).
 int fill_i32(int32_t* p, int32_t value, int64_t n, hipStream_t s);

@@ -1,13 +1,16 @@
 // No-Time-Counter pair selection (section "Cell partition and collision-pair
 // selection").  Candidates are generated for all cells at once, one lane per
 // candidate, so the work is balanced however uneven the cell populations are:
-//   count M_k per cell -> scan (candidate offsets) -> the cell of each
-//   1024-candidate chunk's first candidate -> decide pass: each wave takes a
-//   chunk, walks its cells forward, draws and decides the candidates and
-//   stages the accepted pairs compactly in the chunk's own slots, with each
-//   cell's offset inside the chunk -> scan of the chunk counts -> copy pass:
-//   the staged pairs of every chunk to their dense, cell-major place -> per
-//   cell offsets and counts.
+//   count M_k per cell, with each tile of cells' sum -> candidate offsets
+//   (a workgroup adds the sums of the tiles before its own), the cell of each
+//   64-candidate round's first candidate and the overflow decision -> decide
+//   pass: each wave takes a chunk of candidates, walks its cells forward,
+//   draws and decides the candidates and stages the accepted pairs compactly
+//   in the chunk's own slots, with each cell's offset inside the chunk -> one
+//   workgroup's scan of the chunk counts -> copy pass: the staged pairs of
+//   every chunk to their dense, cell-major place -> per cell offsets and
+//   counts.
+// Six launches; with general scans the stage took twelve, at some 4 us each.
 // The decision arithmetic (g, the candidate count) uses explicitly rounded
 // FP64 operations so it is the same on every launch shape.
 #include <math.h>
@@ -60,35 +63,131 @@ __device__ __forceinline__ int32_t cand_count(int32_t N, double lam, XsLaw law, 
     return (int32_t)floor(x);
 }
 
-__global__ void __launch_bounds__(256)
-k_cand_count(const int32_t* __restrict__ cell_start, int32_t n_cells,
-             const double* __restrict__ lambda, const double* __restrict__ mom, XsLaw law,
-             dsmc_rng rng, int32_t* __restrict__ cnt)
+// Candidates (NTC) or trials (SBT: N - 1) of every cell, and their sum over
+// each tile of `tile` cells (one workgroup per tile).
+enum { SEL_NTC = 0, SEL_SBT = 1 };
+
+constexpr int CNT_THREADS = 256;
+constexpr int CNT_TILES = 4096;   // most tiles: the offsets pass adds this many sums
+
+__device__ __forceinline__ int64_t block_sum_i64(int64_t x)
 {
-    for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n_cells;
-         k += gridDim.x * blockDim.x) {
-        const int32_t N = cell_start[k + 1] - cell_start[k];
-        cnt[k] = cand_count(N, lambda[k], law, mom[6 * (size_t)k + 4], rng, k);
-    }
+    __shared__ int64_t ws_[CNT_THREADS / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) ws_[threadIdx.x >> 6] = x;
+    __syncthreads();
+    int64_t t = 0;
+#pragma unroll
+    for (int w = 0; w < CNT_THREADS / 64; ++w) t += ws_[w];
+    return t;
 }
 
-constexpr int CAND_ROUNDS = 16;
-constexpr int CAND_CHUNK = 64 * CAND_ROUNDS;
+template <int SEL>
+__global__ void __launch_bounds__(CNT_THREADS)
+k_cand_count(const int32_t* __restrict__ cell_start, int32_t n_cells, int32_t tile,
+             const double* __restrict__ lambda, const double* __restrict__ mom, XsLaw law,
+             dsmc_rng rng, int32_t* __restrict__ cnt, int64_t* __restrict__ tile_sum)
+{
+    const int64_t k0 = (int64_t)blockIdx.x * tile;
+    const int64_t k1 = k0 + tile < n_cells ? k0 + tile : n_cells;
+    int64_t sum = 0;
+    for (int64_t k = k0 + threadIdx.x; k < k1; k += CNT_THREADS) {
+        const int32_t N = cell_start[k + 1] - cell_start[k];
+        int32_t c;
+        if (SEL == SEL_NTC)
+            c = cand_count(N, lambda[k], law, mom[6 * (size_t)k + 4], rng, (int32_t)k);
+        else
+            c = N >= 2 ? N - 1 : 0;
+        cnt[k] = c;
+        sum += c;
+    }
+    sum = block_sum_i64(sum);
+    if (threadIdx.x == 0) tile_sum[blockIdx.x] = sum;
+}
+
 constexpr int CAND_GROUP = 4;
 constexpr int CAND_WIN = 4;      // scalar cell window of a group (see k_cand_decide)
 
-// Overflow decision: total candidates vs capacity; number of chunks.
-__global__ void k_cand_check(const int64_t* total, int64_t cap, int32_t* ok, int64_t* n_use,
-                             int64_t* n_chunks, dsmc_status* st)
+// Rounds of 64 candidates per chunk (one chunk per wave at a time): few, so a
+// small selection spreads over the chip's waves, until there are candidates
+// enough to give every wave a long chunk; then 16, whose staged runs are
+// longer and whose counts are fewer (53 million candidates: decide 0.46 ms
+// against 0.63 ms with 4, copy 0.07 against 0.14 ms; 17 000 candidates:
+// decide 13 us with 4 against 32 us with 16).
+constexpr int CHUNK_MIN = 64 * CAND_GROUP;
+constexpr int64_t CHUNK_LONG_FROM = (int64_t)1 << 23;
+__device__ __forceinline__ int cand_rounds(int64_t total)
 {
-    const int64_t t = *total;
-    const bool fits = t <= cap;
-    *ok = fits ? 1 : 0;
-    *n_use = fits ? t : 0;
-    *n_chunks = fits ? (t + CAND_CHUNK - 1) / CAND_CHUNK : 0;
-    if (st) {
-        st->n_cand = t;
-        if (!fits) atomicOr(&st->flags, (uint32_t)DSMC_ST_PAIR_OVERFLOW);
+    return total < CHUNK_LONG_FROM ? CAND_GROUP : 4 * CAND_GROUP;
+}
+
+// What the passes after the count share.
+struct SelTotals {
+    int64_t n_use;      // candidates processed (0 on overflow)
+    int64_t n_chunks;
+    int32_t ok;
+    int32_t chunk;      // candidates per chunk
+};
+
+// Offsets of a tile's cells: the sums of the tiles before it, then a running
+// scan over its cells; the cell owning the first candidate of each
+// 64-candidate round (written by that cell's thread); the overflow decision.
+__global__ void __launch_bounds__(CNT_THREADS)
+k_cand_offsets(int32_t n_cells, int32_t tile, const int32_t* __restrict__ cnt,
+               const int64_t* __restrict__ tile_sum, int64_t cap, int32_t* __restrict__ cand_off,
+               int32_t* __restrict__ round_cell, SelTotals* __restrict__ tot, dsmc_status* st)
+{
+    int64_t before = 0, all = 0;
+    for (int t = threadIdx.x; t < (int)gridDim.x; t += CNT_THREADS) {
+        const int64_t x = tile_sum[t];
+        all += x;
+        before += t < (int)blockIdx.x ? x : 0;
+    }
+    before = block_sum_i64(before);
+    all = block_sum_i64(all);
+    const bool fits = all <= cap;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        tot->n_use = fits ? all : 0;
+        const int chunk = 64 * cand_rounds(all);
+        tot->n_chunks = fits ? (all + chunk - 1) / chunk : 0;
+        tot->ok = fits ? 1 : 0;
+        tot->chunk = chunk;
+        if (st) {
+            st->n_cand = all;
+            if (!fits) atomicOr(&st->flags, (uint32_t)DSMC_ST_PAIR_OVERFLOW);
+        }
+    }
+    if (!fits) return;
+    __shared__ int32_t wsum[CNT_THREADS / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t k0 = (int64_t)blockIdx.x * tile;
+    const int64_t k1 = k0 + tile < n_cells ? k0 + tile : n_cells;
+    int32_t run = (int32_t)before;
+    for (int64_t b = k0; b < k1; b += CNT_THREADS) {
+        const int64_t k = b + threadIdx.x;
+        const int32_t x = k < k1 ? cnt[k] : 0;
+        int32_t inc = x;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        __syncthreads();
+        if (lane == 63) wsum[w] = inc;
+        __syncthreads();
+        int32_t pre = run;
+#pragma unroll
+        for (int q = 0; q < CNT_THREADS / 64; ++q) {
+            if (q < w) pre += wsum[q];
+            run += wsum[q];
+        }
+        if (k < k1) {
+            const int64_t a = pre + inc - x, e = a + x;
+            cand_off[k] = (int32_t)a;
+            for (int64_t r = (a + 63) / 64; r * 64 < e; ++r) round_cell[r] = (int32_t)k;
+        }
     }
 }
 
@@ -175,60 +274,31 @@ __device__ __forceinline__ bool sbt_accept(const CandDraw& d, int32_t m, const V
     return d.U < P;
 }
 
-// Trials per cell of the SBT scheme: N - 1.
-__global__ void __launch_bounds__(256)
-k_trial_count(const int32_t* __restrict__ cell_start, int32_t n_cells, int32_t* __restrict__ cnt)
-{
-    for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n_cells;
-         k += gridDim.x * blockDim.x) {
-        const int32_t N = cell_start[k + 1] - cell_start[k];
-        cnt[k] = N >= 2 ? N - 1 : 0;
-    }
-}
-
-enum { SEL_NTC = 0, SEL_SBT = 1 };
-
-// Cell owning the first candidate of each 64-candidate round (one thread per
-// cell writes the rounds that start inside its candidate range).
-__global__ void __launch_bounds__(256)
-k_round_cells(int32_t n_cells, const int32_t* __restrict__ cand_off,
-              const int64_t* __restrict__ n_use, int32_t* __restrict__ round_cell)
-{
-    const int64_t total = *n_use;
-    for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n_cells;
-         k += gridDim.x * blockDim.x) {
-        const int64_t a = cand_off[k];
-        const int64_t nxt = k + 1 < n_cells ? (int64_t)cand_off[k + 1] : total;
-        const int64_t b = nxt < total ? nxt : total;
-        for (int64_t r = (a + 63) / 64; r * 64 < b; ++r) round_cell[r] = k;
-    }
-}
-
 // Decide every candidate of a chunk; accepted pairs go to the chunk's slots
-// [ch * 1024, ...) of the staging arrays in candidate order; loc[k] = number
+// [ch * chunk, ...) of the staging arrays in candidate order; loc[k] = number
 // of accepted pairs of the chunk before cell k's first candidate (for every
 // cell whose candidates start inside the chunk; empty cells take the value of
 // the next candidate).
 template <typename T, int SEL>
 __global__ void __launch_bounds__(256)
 k_cand_decide(const int32_t* __restrict__ cell_start, int32_t n_cells,
-              const int32_t* __restrict__ cand_off, const int64_t* __restrict__ n_use,
+              const int32_t* __restrict__ cand_off, const SelTotals* __restrict__ tot,
               const int32_t* __restrict__ round_cell, const double* __restrict__ mom,
               const double* __restrict__ lambda, double C, double e, dsmc_rng rng,
-              V3<const T> v, int32_t* __restrict__ chunk_cnt, int32_t* __restrict__ si,
-              int32_t* __restrict__ sj, int32_t* __restrict__ sc, int32_t* __restrict__ loc,
-              dsmc_status* st)
+              V3<const T> v, int32_t* __restrict__ chunk_cnt, int32_t* __restrict__ chunk_clamped,
+              int32_t* __restrict__ si, int32_t* __restrict__ sj, int32_t* __restrict__ sc,
+              int32_t* __restrict__ loc)
 {
-    int clamped_n = 0;
-    const int64_t total = *n_use;
-    const int64_t nch = (total + CAND_CHUNK - 1) / CAND_CHUNK;
+    const int64_t total = tot->n_use;
+    const int64_t nch = tot->n_chunks;
+    const int chunk = tot->chunk, rounds = chunk / 64;
     const int lane = threadIdx.x & 63;
     const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t ch = wave; ch < nch; ch += nwaves) {
-        const int64_t cbase = ch * CAND_CHUNK;
-        int32_t acc = 0;
+        const int64_t cbase = ch * chunk;
+        int32_t acc = 0, clamped_n = 0;
         // CAND_GROUP rounds at a time.  Cells are looked up in two ways:
         //  - when the group's candidates lie in the CAND_WIN cells from the
         //    cell of its first candidate (cells of many candidates), those
@@ -240,7 +310,7 @@ k_cand_decide(const int32_t* __restrict__ cell_start, int32_t n_cells,
         //    the window's candidate offsets with lane shuffles, and a round
         //    that crosses more than 63 cell starts (runs of cells without
         //    candidates) walks on from the window's last cell.
-        for (int r0 = 0; r0 < CAND_ROUNDS; r0 += CAND_GROUP) {
+        for (int r0 = 0; r0 < rounds; r0 += CAND_GROUP) {
             const int64_t gfirst = cbase + r0 * 64;
             if (gfirst >= total) break;
             int32_t kk[CAND_GROUP], s0u[CAND_GROUP], nu[CAND_GROUP], au[CAND_GROUP];
@@ -346,7 +416,7 @@ k_cand_decide(const int32_t* __restrict__ cell_start, int32_t n_cells,
                 } else {
                     bool cl = false;
                     take[u] = val[u] && sbt_accept<T>(dr[u], mm[u], v, gu[u], C, e, cl);
-                    clamped_n += (val[u] && cl) ? 1 : 0;
+                    clamped_n += (int32_t)__popcll(__ballot(val[u] && cl));
                 }
             }
 #pragma unroll
@@ -365,31 +435,116 @@ k_cand_decide(const int32_t* __restrict__ cell_start, int32_t n_cells,
                 acc += (int32_t)__popcll(ab);
             }
         }
-        if (lane == 0) chunk_cnt[ch] = acc;
+        if (lane == 0) {
+            chunk_cnt[ch] = acc;
+            if (SEL == SEL_SBT) chunk_clamped[ch] = clamped_n;
+        }
     }
+}
+
+// Exclusive scan of the chunk counts by one workgroup, 16 384 counts a step
+// (chunk_off[n_chunks] = all pairs), and the sum of the trials whose
+// probability was clamped.  52 000 counts take 15 us.  (Sums added
+// atomically by the decide pass instead, one address per 64 chunks, cost it
+// more than this launch; its waves' atomic counts of clamped trials on the one
+// status word took 40 of its 55 us for a million trials.)
+constexpr int SCAN1_THREADS = 1024;
+constexpr int SCAN1_ROWS = 4;                     // rows of 4 096 counts per step
+constexpr int SCAN1_ROW = 4 * SCAN1_THREADS;
+
+template <int SEL>
+__global__ void __launch_bounds__(SCAN1_THREADS)
+k_chunk_scan(const SelTotals* __restrict__ tot, const int32_t* __restrict__ cnt,
+             const int32_t* __restrict__ clamped, int32_t* __restrict__ off, dsmc_status* st)
+{
+    __shared__ int32_t wsum[2][SCAN1_ROWS][SCAN1_THREADS / 64];
+    __shared__ int32_t csum[SCAN1_THREADS / 64];
+    const int64_t n = tot->n_chunks;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int32_t run = 0, nclamp = 0;
+    int par = 0;
+    for (int64_t b = 0; b < n; b += SCAN1_ROWS * SCAN1_ROW, par ^= 1) {
+        int4 v[SCAN1_ROWS];
+        int32_t s[SCAN1_ROWS], inc[SCAN1_ROWS];
+#pragma unroll
+        for (int q = 0; q < SCAN1_ROWS; ++q) {
+            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
+            v[q] = int4{0, 0, 0, 0};
+            if (i + 4 <= n) {
+                v[q] = *reinterpret_cast<const int4*>(cnt + i);
+            } else {
+                if (i < n) v[q].x = cnt[i];
+                if (i + 1 < n) v[q].y = cnt[i + 1];
+                if (i + 2 < n) v[q].z = cnt[i + 2];
+            }
+        }
+        if (SEL == SEL_SBT)
+            for (int64_t i = b + threadIdx.x; i < n && i < b + SCAN1_ROWS * SCAN1_ROW;
+                 i += SCAN1_THREADS)
+                nclamp += clamped[i];
+#pragma unroll
+        for (int q = 0; q < SCAN1_ROWS; ++q) {
+            s[q] = inc[q] = v[q].x + v[q].y + v[q].z + v[q].w;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int32_t y = __shfl_up(inc[q], o, 64);
+                if (lane >= o) inc[q] += y;
+            }
+            if (lane == 63) wsum[par][q][w] = inc[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < SCAN1_ROWS; ++q) {
+            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
+            int32_t pre = run + inc[q] - s[q];
+#pragma unroll
+            for (int u = 0; u < SCAN1_THREADS / 64; ++u) {
+                const int32_t y = wsum[par][q][u];
+                if (u < w) pre += y;
+                run += y;
+            }
+            const int4 o = {pre, pre + v[q].x, pre + v[q].x + v[q].y,
+                            pre + v[q].x + v[q].y + v[q].z};
+            if (i + 4 <= n) {
+                *reinterpret_cast<int4*>(off + i) = o;
+            } else {
+                if (i < n) off[i] = o.x;
+                if (i + 1 < n) off[i + 1] = o.y;
+                if (i + 2 < n) off[i + 2] = o.z;
+            }
+        }
+    }
+    if (threadIdx.x == 0) off[n] = run;
     if (SEL == SEL_SBT && st) {
-        const int w = wave_sum_i(clamped_n);
-        if (lane == 0 && w > 0) {
-            atomicAdd(&st->prob_clamped, w);
-            atomicOr(&st->flags, (uint32_t)DSMC_ST_PROB_CLAMP);
+        nclamp = wave_sum_i(nclamp);
+        if (lane == 0) csum[w] = nclamp;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int32_t c = 0;
+            for (int u = 0; u < SCAN1_THREADS / 64; ++u) c += csum[u];
+            if (c > 0) {
+                atomicAdd(&st->prob_clamped, c);
+                atomicOr(&st->flags, (uint32_t)DSMC_ST_PROB_CLAMP);
+            }
         }
     }
 }
 
 // Staged pairs of each chunk to their dense place (one wave per chunk).
 __global__ void __launch_bounds__(256)
-k_stage_copy(const int64_t* __restrict__ n_chunks, const int32_t* __restrict__ chunk_cnt,
+k_stage_copy(const SelTotals* __restrict__ tot, const int32_t* __restrict__ chunk_cnt,
              const int32_t* __restrict__ chunk_off, const int32_t* __restrict__ si,
              const int32_t* __restrict__ sj, const int32_t* __restrict__ sc,
              int32_t* __restrict__ pi, int32_t* __restrict__ pj, int32_t* __restrict__ pc)
 {
-    const int64_t nch = *n_chunks;
+    const int64_t nch = tot->n_chunks;
+    const int chunk = tot->chunk;
     const int lane = threadIdx.x & 63;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t ch = wave; ch < nch; ch += nwaves) {
         const int32_t n = chunk_cnt[ch], o = chunk_off[ch];
-        const int64_t src = ch * CAND_CHUNK;
+        const int64_t src = ch * chunk;
         for (int32_t q = lane; q < n; q += 64) {
             pi[o + q] = si[src + q];
             pj[o + q] = sj[src + q];
@@ -402,14 +557,14 @@ k_stage_copy(const int64_t* __restrict__ n_chunks, const int32_t* __restrict__ c
 // after the last candidate (none left) get the total as offset.
 __global__ void __launch_bounds__(256)
 k_pair_counts(int32_t n_cells, const int32_t* __restrict__ cand_off,
-              const int32_t* __restrict__ ok, const int64_t* __restrict__ n_use,
-              const int64_t* __restrict__ n_chunks, const int32_t* __restrict__ chunk_off,
+              const SelTotals* __restrict__ tot, const int32_t* __restrict__ chunk_off,
               const int32_t* __restrict__ loc, int32_t* __restrict__ off,
               int32_t* __restrict__ cnt, dsmc_status* st)
 {
-    const bool fits = *ok != 0;
-    const int64_t total = *n_use;
-    const int32_t npairs = fits ? chunk_off[*n_chunks] : 0;
+    const bool fits = tot->ok != 0;
+    const int64_t total = tot->n_use;
+    const int32_t npairs = fits ? chunk_off[tot->n_chunks] : 0;
+    const int chunk = tot->chunk;
     for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n_cells;
          k += gridDim.x * blockDim.x) {
         if (!fits) {
@@ -418,11 +573,11 @@ k_pair_counts(int32_t n_cells, const int32_t* __restrict__ cand_off,
             continue;
         }
         const int64_t ca = cand_off[k];
-        const int32_t a = ca >= total ? npairs : chunk_off[ca / CAND_CHUNK] + loc[k];
+        const int32_t a = ca >= total ? npairs : chunk_off[ca / chunk] + loc[k];
         int32_t b = npairs;
         if (k + 1 < n_cells) {
             const int64_t cb = cand_off[k + 1];
-            b = cb >= total ? npairs : chunk_off[cb / CAND_CHUNK] + loc[k + 1];
+            b = cb >= total ? npairs : chunk_off[cb / chunk] + loc[k + 1];
         }
         off[k] = a;
         cnt[k] = b - a;
@@ -432,47 +587,43 @@ k_pair_counts(int32_t n_cells, const int32_t* __restrict__ cand_off,
 
 struct SelectWs {
     int32_t* cand_cnt;    // [n_cells]
-    int32_t* cand_off;    // [n_cells + 1]
+    int32_t* cand_off;    // [n_cells]
     int32_t* loc;         // [n_cells]
-    int64_t* total;       // candidates
-    int64_t* n_use;       // candidates processed (0 on overflow)
-    int64_t* n_chunks;
-    int32_t* ok;
-    int32_t* round_cell;  // [max chunks * 16]
+    int64_t* tile_sum;    // [CNT_TILES]
+    SelTotals* tot;
+    int32_t* round_cell;  // [max chunks * CAND_GROUP]
     int32_t* chunk_cnt;   // [max chunks]
+    int32_t* chunk_clamped; // [max chunks]
     int32_t* chunk_off;   // [max chunks + 1]
-    int32_t* si;          // staging [max chunks * 1024]
+    int32_t* si;          // staging [max chunks * CHUNK_MIN]
     int32_t* sj;
     int32_t* sc;
-    void* scan;
     size_t bytes;
 };
 
-static int64_t max_chunks(int64_t cap) { return (cap + CAND_CHUNK - 1) / CAND_CHUNK + 1; }
+static int64_t max_chunks(int64_t cap) { return (cap + CHUNK_MIN - 1) / CHUNK_MIN + 1; }
 
 static SelectWs select_ws_layout(void* base, int32_t n_cells, int64_t cap)
 {
     SelectWs w{};
-    uint8_t* p = static_cast<uint8_t*>(base);
+    // (the queried size has 256 spare bytes for the alignment of the base)
+    uint8_t* p = reinterpret_cast<uint8_t*>(align_up(reinterpret_cast<uintptr_t>(base)));
     size_t o = 0;
     auto take = [&](size_t b) { uint8_t* r = p ? p + o : nullptr; o += align_up(b); return r; };
     const int64_t mc = max_chunks(cap);
-    w.cand_cnt = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * ((size_t)n_cells + 1)));
-    w.cand_off = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * ((size_t)n_cells + 2)));
-    w.loc = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * ((size_t)n_cells + 1)));
-    w.total = reinterpret_cast<int64_t*>(take(sizeof(int64_t)));
-    w.n_use = reinterpret_cast<int64_t*>(take(sizeof(int64_t)));
-    w.n_chunks = reinterpret_cast<int64_t*>(take(sizeof(int64_t)));
-    w.ok = reinterpret_cast<int32_t*>(take(sizeof(int32_t)));
-    w.round_cell = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)mc * CAND_ROUNDS));
+    w.cand_cnt = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n_cells));
+    w.cand_off = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n_cells));
+    w.loc = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n_cells));
+    w.tile_sum = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * CNT_TILES));
+    w.tot = reinterpret_cast<SelTotals*>(take(sizeof(SelTotals)));
+    w.round_cell = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)mc * CAND_GROUP));
     w.chunk_cnt = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)mc));
+    w.chunk_clamped = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)mc));
     w.chunk_off = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * ((size_t)mc + 1)));
-    const size_t stage = sizeof(int32_t) * (size_t)mc * CAND_CHUNK;
+    const size_t stage = sizeof(int32_t) * (size_t)mc * CHUNK_MIN;
     w.si = reinterpret_cast<int32_t*>(take(stage));
     w.sj = reinterpret_cast<int32_t*>(take(stage));
     w.sc = reinterpret_cast<int32_t*>(take(stage));
-    const size_t sb = scan_ws_bytes((int64_t)(mc > n_cells ? mc : n_cells) + 1);
-    w.scan = take(sb);
     w.bytes = o;
     return w;
 }
@@ -486,30 +637,31 @@ static int select_impl(int32_t n_cells, const int32_t* cell_start, dsmc_vec3 v, 
     const int pb = persistent_blocks(256);
     int cb = (n_cells + 255) / 256;
     cb = cb < 1 ? 1 : (cb > pb ? pb : cb);
-    if (SEL == SEL_NTC)
-        k_cand_count<<<cb, 256, 0, s>>>(cell_start, n_cells, lambda, mom, law, rng, w.cand_cnt);
-    else
-        k_trial_count<<<cb, 256, 0, s>>>(cell_start, n_cells, w.cand_cnt);
+    // tiles of one workgroup-width of cells, larger only beyond CNT_TILES of them
+    const int64_t widths = ((int64_t)n_cells + CNT_THREADS - 1) / CNT_THREADS;
+    const int32_t tile = (int32_t)((widths + CNT_TILES - 1) / CNT_TILES * CNT_THREADS);
+    const int tiles = (int)(((int64_t)n_cells + tile - 1) / tile);
+    k_cand_count<SEL><<<tiles, CNT_THREADS, 0, s>>>(cell_start, n_cells, tile, lambda, mom, law,
+                                                    rng, w.cand_cnt, w.tile_sum);
     DSMC_LAUNCH_CHECK("select:count");
-    int rc = exclusive_scan_i32(w.cand_cnt, w.cand_off, n_cells, w.total, w.scan, s);
-    if (rc) return rc;
-    k_cand_check<<<1, 1, 0, s>>>(w.total, pairs.cap, w.ok, w.n_use, w.n_chunks, st);
-    DSMC_LAUNCH_CHECK("select:check");
-    k_round_cells<<<cb, 256, 0, s>>>(n_cells, w.cand_off, w.n_use, w.round_cell);
-    DSMC_LAUNCH_CHECK("select:round_cells");
-    k_cand_decide<T, SEL><<<pb, 256, 0, s>>>(cell_start, n_cells, w.cand_off, w.n_use,
-                                             w.round_cell, mom, lambda, law.C, law.e, rng,
-                                             v3<const T>(v), w.chunk_cnt, w.si, w.sj, w.sc,
-                                             w.loc, st);
+    k_cand_offsets<<<tiles, CNT_THREADS, 0, s>>>(n_cells, tile, w.cand_cnt, w.tile_sum, pairs.cap,
+                                                 w.cand_off, w.round_cell, w.tot, st);
+    DSMC_LAUNCH_CHECK("select:offsets");
+    // no more workgroups than chunks fit the capacity
+    const int64_t ch_max = max_chunks(pairs.cap);
+    const int db = (int)((ch_max + 3) / 4 < pb ? (ch_max + 3) / 4 : pb);
+    k_cand_decide<T, SEL><<<db, 256, 0, s>>>(cell_start, n_cells, w.cand_off, w.tot, w.round_cell,
+                                             mom, lambda, law.C, law.e, rng, v3<const T>(v),
+                                             w.chunk_cnt, w.chunk_clamped, w.si, w.sj, w.sc, w.loc);
     DSMC_LAUNCH_CHECK("select:decide");
-    rc = exclusive_scan_i32_dev(w.chunk_cnt, w.chunk_off, w.n_chunks, max_chunks(pairs.cap),
-                                w.scan, s);
-    if (rc) return rc;
-    k_stage_copy<<<pb, 256, 0, s>>>(w.n_chunks, w.chunk_cnt, w.chunk_off, w.si, w.sj, w.sc,
-                                    pairs.i, pairs.j, pairs.cell);
+    k_chunk_scan<SEL><<<1, SCAN1_THREADS, 0, s>>>(w.tot, w.chunk_cnt, w.chunk_clamped, w.chunk_off,
+                                                  st);
+    DSMC_LAUNCH_CHECK("select:scan");
+    k_stage_copy<<<db, 256, 0, s>>>(w.tot, w.chunk_cnt, w.chunk_off, w.si, w.sj, w.sc, pairs.i,
+                                    pairs.j, pairs.cell);
     DSMC_LAUNCH_CHECK("select:copy");
-    k_pair_counts<<<cb, 256, 0, s>>>(n_cells, w.cand_off, w.ok, w.n_use, w.n_chunks, w.chunk_off,
-                                     w.loc, pairs.off, pairs.cnt, st);
+    k_pair_counts<<<cb, 256, 0, s>>>(n_cells, w.cand_off, w.tot, w.chunk_off, w.loc, pairs.off,
+                                     pairs.cnt, st);
     DSMC_LAUNCH_CHECK("select:counts");
     return DSMC_OK;
 }

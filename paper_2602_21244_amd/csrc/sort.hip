@@ -517,7 +517,7 @@ static int sort_impl(int32_t n, int32_t n_cells, const int32_t* cell_of, dsmc_ve
         vin_idx = vout_idx;
     }
     // cell_start: exclusive scan, in place, of the counts the last pass added
-    int rc = exclusive_scan_i32(cell_start, cell_start, n_cells, nullptr, scan_ws, s);
+    int rc = exclusive_scan_i32(cell_start, cell_start, n_cells, scan_ws, s);
     if (rc) return rc;
     return DSMC_OK;
 }

@@ -214,6 +214,33 @@ def test_select_sbt_bitexact(orc, dev, api, case):
         assert sel["n_clamped"] > 0
 
 
+@pytest.mark.parametrize("n_cells,mean,lam_scale", [(1, 2, 1.0), (1, 3000, 1.0), (257, 300, 1.0),
+                                                    (40000, 25, 8.0), (40000, 25, 12.0)])
+def test_select_sizes_bitexact(orc, dev, api, n_cells, mean, lam_scale):
+    """Selections around the sizes where the passes change: one cell, a tile of
+    cells and one more, more chunk counts than one step of their scan takes
+    (4 million candidates), and enough candidates (8.4 million) for the long
+    chunks.  Pair lists bit-exact."""
+    say("select sizes", n_cells, mean, lam_scale)
+    pop = W.vhs_argon_1d(seed=n_cells, n=n_cells * mean, n_cells=n_cells)
+    cs, perm, vs, st = _gpu_sort(api, dev, pop, torch.float32)
+    lam = pop.lam * lam_scale
+    v64 = vs.cpu().numpy().astype(np.float64)
+    mom = torch.zeros(6 * n_cells, dtype=torch.float64, device=dev)
+    api.moment_match(cs, vs, mom, api.L.MM_CAPTURE)
+    sel = orc.select_ntc(cs.cpu().numpy(), v64, pop.xs, lam, mom.cpu().numpy().reshape(-1, 6), 5, 1)
+    pairs = api.PairList(n_cells, int(sel["n_cand"]), dev)
+    api.select_pairs_ntc(cs, vs, pop.xs, torch.as_tensor(lam, device=dev), mom, 5, 1, pairs, st=st)
+    s = api.read_status(st)
+    n = int(sel["pair_cnt"].sum())
+    say(f"  {sel['n_cand']} candidates, {n} pairs")
+    assert s.n_cand == sel["n_cand"] and s.n_pairs == n
+    assert np.array_equal(pairs.cnt.cpu().numpy(), sel["pair_cnt"])
+    assert np.array_equal(pairs.off.cpu().numpy(), sel["pair_off"])
+    for name in ("i", "j", "cell"):
+        assert np.array_equal(getattr(pairs, name)[:n].cpu().numpy(), sel["pair_" + name]), name
+
+
 def test_sbt_step_and_overflow(orc, dev, api):
     say("sbt step")
     pop = W.ragged_population(15, 250, 120, empty_frac=0.1)
