@@ -8,9 +8,9 @@
 // and without atomics on the particle data:
 //   up    : per 4096-particle tile, a 512-bucket digit histogram (LDS
 //           atomics), stored tile-major so every store is a row segment
-//   scan  : offsets of the (tile, digit) table in digit-major order by three
-//           small kernels over chunks of tiles (column sums, a scan of those
-//           per digit, expansion of the chunk rows)
+//   scan  : offsets of the (tile, digit) table in digit-major order over
+//           chunks of tiles (column sums, a scan of those per digit, expansion
+//           of the chunk rows); few tiles need no table, see sort_impl
 //   down  : 512 threads per tile; each wave ranks its 512 particles in index
 //           order (digit groups split off by ballots, per-wave digit
 //           counters in LDS), the tile is reordered by digit through one LDS
@@ -20,6 +20,14 @@
 // cell counts (its tiles are sorted by the whole key, so a few integer
 // atomics per tile); an in-place exclusive scan of the counts gives
 // cell_start.
+// That gather reads whole lines for one particle each when the input is in no
+// particular order.  With two passes the first one then carries (v, index)
+// records of 16 or 32 bytes along, in runs of a digit, and the last reads them
+// from its own tile: both passes take 99 us instead of 184 us for 3 million
+// shuffled FP32 particles, 60 instead of 76 us for a million in FP64.  Input
+// close to cell order, whose gather is nearly coalesced, would only move 24
+// bytes more per particle (30 million, movers a few cells away: 0.40 ms with
+// the gather).  The first histogram pass samples which of the two it is.
 // Ids outside [0, n_cells) are mapped to the key n_cells, so they sort after
 // every kept particle.
 #include <mutex>
@@ -51,12 +59,23 @@ __device__ __forceinline__ int32_t sort_key(const int32_t* cell_of, int64_t p, i
 // the cell-sorted-with-movers order typical after streaming costs a few
 // atomics per thread.  The first pass reads cell_of, maps bad ids and counts
 // them in the status word.
+// It also clears the cell counts, and tile b of the at most FAR_TILES sampled
+// ones (evenly spread) writes how many of its neighbouring ids lie more than
+// FAR_CELLS apart, and of how many.
+constexpr int FAR_TILES = 64;
+constexpr int FAR_CELLS = 64;
+
 template <bool FIRST>
 __global__ void __launch_bounds__(SORT_THREADS)
 k_radix_up(const int32_t* __restrict__ keys_in, int32_t n, int32_t n_cells, int shift,
-           int32_t mask, int32_t* __restrict__ ghist, dsmc_status* st)
+           int32_t mask, int32_t* __restrict__ ghist, int32_t* __restrict__ counts,
+           int2* __restrict__ far, dsmc_status* st)
 {
     __shared__ int32_t h[RADIX];
+    if (FIRST)
+        for (int64_t k = blockIdx.x * (int64_t)SORT_THREADS + threadIdx.x; k <= n_cells;
+             k += (int64_t)gridDim.x * SORT_THREADS)
+            counts[k] = 0;
     for (int i = threadIdx.x; i <= mask; i += SORT_THREADS) h[i] = 0;
     __syncthreads();
     const int64_t p0 = (int64_t)blockIdx.x * SORT_TILE + (int64_t)threadIdx.x * SORT_ITEMS;
@@ -72,6 +91,32 @@ k_radix_up(const int32_t* __restrict__ keys_in, int32_t n, int32_t n_cells, int 
     } else {
 #pragma unroll
         for (int q = 0; q < SORT_ITEMS; ++q) key[q] = (p0 + q < n) ? keys_in[p0 + q] : -1;
+    }
+    if (FIRST && far) {
+        const int64_t nt = gridDim.x, S = nt < FAR_TILES ? nt : FAR_TILES;
+        const int64_t smp = blockIdx.x * S / nt;
+        if ((smp * nt + S - 1) / S == blockIdx.x) {
+            __shared__ int2 fs[SORT_THREADS / 64];
+            int nf = 0, np = 0;
+#pragma unroll
+            for (int q = 1; q < SORT_ITEMS; ++q)
+                if (p0 + q < n) {
+                    const int64_t d = (int64_t)key[q] - key[q - 1];
+                    nf += (d > FAR_CELLS || d < -FAR_CELLS) ? 1 : 0;
+                    ++np;
+                }
+            nf = wave_sum_i(nf);
+            np = wave_sum_i(np);
+            if ((threadIdx.x & 63) == 0) fs[threadIdx.x >> 6] = int2{nf, np};
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                for (int w = 1; w < SORT_THREADS / 64; ++w) {
+                    nf += fs[w].x;
+                    np += fs[w].y;
+                }
+                far[smp] = int2{nf, np};
+            }
+        }
     }
     int bad = 0;
     int32_t run_d = -1, run_n = 0;
@@ -213,6 +258,52 @@ k_hist_expand(const int32_t* __restrict__ h, const int32_t* __restrict__ cpre,
     }
 }
 
+// The expansion without the chunk scan, for few chunks: each workgroup adds
+// the chunk sums itself.
+constexpr int HSELF = 32;
+__global__ void __launch_bounds__(256)
+k_hist_expand_self(const int32_t* __restrict__ h, const int32_t* __restrict__ csum, int32_t nch,
+                   int32_t nblk, int32_t R, int32_t* __restrict__ goff)
+{
+    __shared__ int32_t t_s[RADIX];
+    __shared__ int32_t e_s[RADIX];
+    int32_t pre[RADIX / 256];
+#pragma unroll
+    for (int e = 0; e < RADIX / 256; ++e) {
+        const int d = threadIdx.x + 256 * e;
+        int32_t all = 0, p = 0;
+        if (d < R) {
+#pragma unroll 8
+            for (int c = 0; c < nch; ++c) {
+                const int32_t x = csum[(int64_t)c * R + d];
+                p += c < (int)blockIdx.x ? x : 0;
+                all += x;
+            }
+        }
+        t_s[d] = all;
+        pre[e] = p;
+    }
+    __syncthreads();
+    block_scan_radix(t_s, e_s);
+    __syncthreads();
+    const int64_t b0 = (int64_t)blockIdx.x * HCHUNK;
+    const int nb = (int)((nblk - b0) < HCHUNK ? (nblk - b0) : HCHUNK);
+#pragma unroll
+    for (int e = 0; e < RADIX / 256; ++e) {
+        const int d = threadIdx.x + 256 * e;
+        if (d >= R) continue;
+        int32_t v[HCHUNK];
+#pragma unroll
+        for (int r = 0; r < HCHUNK; ++r) v[r] = r < nb ? h[(b0 + r) * R + d] : 0;
+        int32_t run = e_s[d] + pre[e];
+#pragma unroll
+        for (int r = 0; r < HCHUNK; ++r) {
+            if (r < nb) goff[(b0 + r) * R + d] = run;
+            run += v[r];
+        }
+    }
+}
+
 constexpr int PEEL = 4;   // digit groups split off one at a time before the bit match
 
 // Rank of this lane's item among the wave's valid items with the same digit
@@ -271,15 +362,37 @@ __device__ __forceinline__ void count_runs(int32_t k, bool ok, int s, int32_t tn
     }
 }
 
+// A particle carried through the first pass.
+template <typename T> struct SortRec;
+template <> struct __align__(16) SortRec<float> {
+    float x, y, z;
+    int32_t idx;
+};
+template <> struct __align__(32) SortRec<double> {
+    double x, y, z;
+    int64_t idx;
+};
+
+// Whether the sampled tiles of the first histogram pass call for records:
+// more than half of the neighbouring ids far apart.
+__device__ __forceinline__ bool carry_records(int2 f)
+{
+    return 2 * wave_sum_i(f.x) > wave_sum_i(f.y);
+}
+
+// Most tiles for which the down pass adds the histogram rows itself.
+constexpr int DIRECT_TILES = 64;
+
 // LAST: the final pass also gathers the velocities into sorted order
-// (vals are then the original indices, i.e. perm).
+// (vals are then the original indices, i.e. perm).  direct: goff is the
+// histogram of all tiles instead of their offsets.
 template <bool FIRST, bool LAST, typename T>
 __global__ void __launch_bounds__(DN_THREADS, 8)
 k_radix_down(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ vals_in, int32_t n,
              int32_t n_cells, int shift, int32_t mask, int dbits,
-             const int32_t* __restrict__ goff, int32_t* __restrict__ keys_out,
+             const int32_t* __restrict__ goff, int direct, int32_t* __restrict__ keys_out,
              int32_t* __restrict__ vals_out, V3<const T> vin, V3<T> vout,
-             int32_t* __restrict__ counts)
+             int32_t* __restrict__ counts, const int2* __restrict__ far, SortRec<T>* rec)
 {
     __shared__ int32_t cnt[DN_WAVES][RADIX];   // per wave and digit
     __shared__ int32_t gb[RADIX];                       // global slot of tile slot 0, per digit
@@ -287,15 +400,41 @@ k_radix_down(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ va
     __shared__ int32_t stage[SORT_TILE];               // keys, then values, in tile order
 
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int2 fr{0, 0};
+    if (FIRST != LAST && far && lane < gridDim.x) fr = far[lane];
     for (int i = threadIdx.x; i < DN_WAVES * RADIX; i += DN_THREADS)
         (&cnt[0][0])[i] = 0;
     // this tile's global digit offsets (digits 2t, 2t+1), loaded early
     int32_t g[DN_DPT];
+    static_assert(DN_DPT == 1, "one digit per thread");
+    if (direct) {
+        // offsets of this tile: totals of the smaller digits, and of this
+        // digit in the tiles before
+        int32_t all = 0, pre = 0;
+        const int d = threadIdx.x;
+        if (d <= mask) {
+#pragma unroll 8
+            for (int b = 0; b < (int)gridDim.x; ++b) {
+                const int32_t x = goff[(int64_t)b * (mask + 1) + d];
+                pre += b < (int)blockIdx.x ? x : 0;
+                all += x;
+            }
+        }
+        int32_t inc = all;
 #pragma unroll
-    for (int e = 0; e < DN_DPT; ++e) {
-        const int d = DN_DPT * threadIdx.x + e;
-        g[e] = d <= mask ? goff[(int64_t)blockIdx.x * (mask + 1) + d] : 0;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        if (lane == 63) wsum[w] = inc;
+        __syncthreads();
+        g[0] = pre + inc - all;
+        for (int q = 0; q < w; ++q) g[0] += wsum[q];
+    } else {
+        const int d = threadIdx.x;
+        g[0] = d <= mask ? goff[(int64_t)blockIdx.x * (mask + 1) + d] : 0;
     }
+    const bool carry = FIRST != LAST && far && carry_records(fr);
     __syncthreads();
 
     const int64_t tbase = (int64_t)blockIdx.x * SORT_TILE;
@@ -317,7 +456,7 @@ k_radix_down(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ va
                 val[it] = (int32_t)(tbase + q);
             } else {
                 key[it] = kt[q];
-                val[it] = vt[q];
+                val[it] = carry ? q : vt[q];
             }
         }
     }
@@ -407,10 +546,48 @@ k_radix_down(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ va
         vv[it] = 0;
         if (oo[it] >= 0) {
             vv[it] = stage[s];
-            vals_out[oo[it]] = vv[it];
+            if (!carry) vals_out[oo[it]] = vv[it];
         }
     }
-    if (LAST) {
+    // records in groups that fit the registers, the loads of a group first
+    constexpr int GRP = sizeof(T) == 8 ? 2 : 4;
+    if (!LAST && carry) {
+        // from this tile's own stretch of the input
+#pragma unroll
+        for (int it0 = 0; it0 < DN_ITEMS; it0 += GRP) {
+            T gx[GRP], gy[GRP], gz[GRP];
+#pragma unroll
+            for (int q = 0; q < GRP; ++q) {
+                if (oo[it0 + q] < 0) continue;
+                const int32_t p = vv[it0 + q];
+                gx[q] = vin.x[p];
+                gy[q] = vin.y[p];
+                gz[q] = vin.z[p];
+            }
+#pragma unroll
+            for (int q = 0; q < GRP; ++q)
+                if (oo[it0 + q] >= 0)
+                    rec[oo[it0 + q]] = SortRec<T>{gx[q], gy[q], gz[q], vv[it0 + q]};
+        }
+    }
+    if (LAST && carry) {
+#pragma unroll
+        for (int it0 = 0; it0 < DN_ITEMS; it0 += GRP) {
+            SortRec<T> r[GRP];
+#pragma unroll
+            for (int q = 0; q < GRP; ++q)
+                if (oo[it0 + q] >= 0) r[q] = rec[tbase + vv[it0 + q]];
+#pragma unroll
+            for (int q = 0; q < GRP; ++q) {
+                const int32_t o = oo[it0 + q];
+                if (o < 0) continue;
+                vals_out[o] = (int32_t)r[q].idx;
+                vout.x[o] = r[q].x;
+                vout.y[o] = r[q].y;
+                vout.z[o] = r[q].z;
+            }
+        }
+    } else if (LAST) {
         // all gathers first, then all stores, so the loads overlap
         T gx[DN_ITEMS], gy[DN_ITEMS], gz[DN_ITEMS];
 #pragma unroll
@@ -439,9 +616,37 @@ static int sort_passes(int32_t n_cells, int* bits_total)
 
 static int64_t sort_tiles(int32_t n) { return ((int64_t)n + SORT_TILE - 1) / SORT_TILE; }
 
+// Records are carried through two passes only: one pass gathers inside its
+// tile anyway, three would need a second buffer.  RECORDS_MAX bounds the
+// workspace they take to 4 GiB.
+constexpr int32_t RECORDS_MAX = 1 << 27;
+
+static bool may_carry(int32_t n, int32_t n_cells)
+{
+    int bits;
+    return n > 0 && n <= RECORDS_MAX && sort_passes(n_cells, &bits) == 2;
+}
+
+static size_t sort_base_ws(int32_t n, int32_t n_cells)
+{
+    const int64_t nblk = sort_tiles(n);
+    const int64_t nch = (nblk + HCHUNK - 1) / HCHUNK;
+    return 3 * align_up(sizeof(int32_t) * (size_t)n) +
+           2 * align_up(sizeof(int32_t) * (size_t)(RADIX * nblk)) +
+           2 * align_up(sizeof(int32_t) * (size_t)(RADIX * nch)) +
+           align_up(sizeof(int32_t) * (size_t)RADIX) + scan_ws_bytes(n_cells) + 256;
+}
+
+// Offsets of a pass's digits: up to DIRECT_TILES tiles the down pass adds the
+// histogram rows itself (two launches a pass instead of five; both passes of
+// 62 tiles: 49 us against 64 us, of which the down kernels 38 and 28; at 245
+// tiles each workgroup would read 0.5 MB); up to HSELF chunks of tiles the
+// expansion adds the chunk sums (6 us with 8 chunks, against 4 and 8 us for a
+// scan and the expansion); more take the chunk scan.  recs: whether the
+// workspace has room for the records.
 template <typename T>
 static int sort_impl(int32_t n, int32_t n_cells, const int32_t* cell_of, dsmc_vec3 vin,
-                     dsmc_vec3 vout, int32_t* cell_start, int32_t* perm, void* ws,
+                     dsmc_vec3 vout, int32_t* cell_start, int32_t* perm, void* ws, bool recs,
                      dsmc_status* st, hipStream_t s)
 {
     if (n == 0) return fill_i32(cell_start, 0, (int64_t)n_cells + 1, s);
@@ -465,13 +670,19 @@ static int sort_impl(int32_t n, int32_t n_cells, const int32_t* cell_of, dsmc_ve
     int32_t* dtot = reinterpret_cast<int32_t*>(w);
     w += align_up(sizeof(int32_t) * (size_t)RADIX);
     void* scan_ws = w;
-    {
-        const int rc = fill_i32(cell_start, 0, (int64_t)n_cells + 1, s);
-        if (rc) return rc;
-    }
-
+    w += scan_ws_bytes(n_cells);
     int nbits = 0;
     const int passes = sort_passes(n_cells, &nbits);
+    int2* far = nullptr;
+    SortRec<T>* rec = nullptr;
+    if (recs && may_carry(n, n_cells)) {
+        w += (256 - reinterpret_cast<uintptr_t>(w) % 256) % 256;   // ws may have any base
+        far = reinterpret_cast<int2*>(w);
+        w += align_up(sizeof(int2) * FAR_TILES);
+        rec = reinterpret_cast<SortRec<T>*>(w);
+    }
+    const int direct = nblk <= DIRECT_TILES ? 1 : 0;
+
     const int32_t* kin = cell_of;
     const int32_t* vin_idx = nullptr;
     for (int pass = 0; pass < passes; ++pass) {
@@ -483,35 +694,44 @@ static int sort_impl(int32_t n, int32_t n_cells, const int32_t* cell_of, dsmc_ve
         int32_t* vout_idx = to_final ? perm : vals_a;
         if (pass == 0)
             k_radix_up<true><<<(int)nblk, SORT_THREADS, 0, s>>>(kin, n, n_cells, shift, mask, ghist,
-                                                                st);
+                                                                cell_start, far, st);
         else
             k_radix_up<false><<<(int)nblk, SORT_THREADS, 0, s>>>(kin, n, n_cells, shift, mask, ghist,
-                                                                 st);
+                                                                 cell_start, far, st);
         DSMC_LAUNCH_CHECK("sort:up");
         const int32_t R = mask + 1;
-        k_hist_chunk_sum<<<(int)nch, 256, 0, s>>>(ghist, (int32_t)nblk, R, csum);
-        k_hist_chunk_scan<<<(R + HDIG - 1) / HDIG, 256, 0, s>>>(csum, (int32_t)nch, R, cpre, dtot);
-        k_hist_expand<<<(int)nch, 256, 0, s>>>(ghist, cpre, dtot, (int32_t)nblk, R, goff);
-        DSMC_LAUNCH_CHECK("sort:scan");
+        if (!direct) {
+            k_hist_chunk_sum<<<(int)nch, 256, 0, s>>>(ghist, (int32_t)nblk, R, csum);
+            if (nch <= HSELF) {
+                k_hist_expand_self<<<(int)nch, 256, 0, s>>>(ghist, csum, (int32_t)nch,
+                                                            (int32_t)nblk, R, goff);
+            } else {
+                k_hist_chunk_scan<<<(R + HDIG - 1) / HDIG, 256, 0, s>>>(csum, (int32_t)nch, R,
+                                                                        cpre, dtot);
+                k_hist_expand<<<(int)nch, 256, 0, s>>>(ghist, cpre, dtot, (int32_t)nblk, R, goff);
+            }
+            DSMC_LAUNCH_CHECK("sort:scan");
+        }
+        const int32_t* offs = direct ? ghist : goff;
         const bool last = pass == passes - 1;
         const V3<const T> vi = v3<const T>(vin);
         const V3<T> vo = v3<T>(vout);
         if (pass == 0 && last)
             k_radix_down<true, true, T><<<(int)nblk, DN_THREADS, 0, s>>>(
-                kin, vin_idx, n, n_cells, shift, mask, dbits, goff, kout, vout_idx,
-                vi, vo, cell_start);
+                kin, vin_idx, n, n_cells, shift, mask, dbits, offs, direct, kout, vout_idx,
+                vi, vo, cell_start, far, rec);
         else if (pass == 0)
             k_radix_down<true, false, T><<<(int)nblk, DN_THREADS, 0, s>>>(
-                kin, vin_idx, n, n_cells, shift, mask, dbits, goff, kout, vout_idx,
-                vi, vo, cell_start);
+                kin, vin_idx, n, n_cells, shift, mask, dbits, offs, direct, kout, vout_idx,
+                vi, vo, cell_start, far, rec);
         else if (last)
             k_radix_down<false, true, T><<<(int)nblk, DN_THREADS, 0, s>>>(
-                kin, vin_idx, n, n_cells, shift, mask, dbits, goff, kout, vout_idx,
-                vi, vo, cell_start);
+                kin, vin_idx, n, n_cells, shift, mask, dbits, offs, direct, kout, vout_idx,
+                vi, vo, cell_start, far, rec);
         else
             k_radix_down<false, false, T><<<(int)nblk, DN_THREADS, 0, s>>>(
-                kin, vin_idx, n, n_cells, shift, mask, dbits, goff, kout, vout_idx,
-                vi, vo, cell_start);
+                kin, vin_idx, n, n_cells, shift, mask, dbits, offs, direct, kout, vout_idx,
+                vi, vo, cell_start, far, rec);
         DSMC_LAUNCH_CHECK("sort:down");
         kin = kout;
         vin_idx = vout_idx;
@@ -590,27 +810,25 @@ extern "C" int dsmc_sort_cells_noalloc(int32_t n, int32_t n_cells, const int32_t
         return arg_error("dsmc_sort_cells_noalloc: null pointer");
     if (dtype != DSMC_F64 && dtype != DSMC_F32)
         return arg_error("dsmc_sort_cells_noalloc: dtype %d", dtype);
-    if (dsmc_sort_cells_ws(n, n_cells) > NOALLOC_SCRATCH_BYTES)
+    if (sort_base_ws(n, n_cells) > NOALLOC_SCRATCH_BYTES)
         return arg_error("dsmc_sort_cells_noalloc: scratch %zu < %zu", NOALLOC_SCRATCH_BYTES,
-                         dsmc_sort_cells_ws(n, n_cells));
+                         sort_base_ws(n, n_cells));
     void* ws = nullptr;
     int rc = scratch_ptr(&ws);
     if (rc) return rc;
     hipStream_t s = as_stream(stream);
     if (dtype == DSMC_F64)
-        return sort_impl<double>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, st, s);
-    return sort_impl<float>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, st, s);
+        return sort_impl<double>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, false, st, s);
+    return sort_impl<float>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, false, st, s);
 }
 
 extern "C" size_t dsmc_sort_cells_ws(int32_t n, int32_t n_cells)
 {
     if (n < 0 || n_cells < 0) return 0;
-    const int64_t nblk = sort_tiles(n);
-    const int64_t nch = (nblk + HCHUNK - 1) / HCHUNK;
-    return 3 * align_up(sizeof(int32_t) * (size_t)n) +
-           2 * align_up(sizeof(int32_t) * (size_t)(RADIX * nblk)) +
-           2 * align_up(sizeof(int32_t) * (size_t)(RADIX * nch)) +
-           align_up(sizeof(int32_t) * (size_t)RADIX) + scan_ws_bytes(n_cells) + 256;
+    size_t b = sort_base_ws(n, n_cells);
+    if (may_carry(n, n_cells))
+        b += align_up(sizeof(int2) * FAR_TILES) + align_up(sizeof(SortRec<double>) * (size_t)n);
+    return b;
 }
 
 extern "C" int dsmc_sort_cells(int32_t n, int32_t n_cells, const int32_t* cell_of, int32_t dtype,
@@ -630,8 +848,8 @@ extern "C" int dsmc_sort_cells(int32_t n, int32_t n_cells, const int32_t* cell_o
                          dsmc_sort_cells_ws(n, n_cells));
     hipStream_t s = as_stream(stream);
     if (dtype == DSMC_F64)
-        return sort_impl<double>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, st, s);
+        return sort_impl<double>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, true, st, s);
     if (dtype == DSMC_F32)
-        return sort_impl<float>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, st, s);
+        return sort_impl<float>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, true, st, s);
     return arg_error("dsmc_sort_cells: dtype %d", dtype);
 }

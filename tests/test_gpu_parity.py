@@ -54,6 +54,58 @@ def _thermal(T=300.0):
 # ---------------------------------------------------------------------------
 # sort
 # ---------------------------------------------------------------------------
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("n,n_cells,order", [
+    # one tile and a last particle alone in its tile, near-sorted and not;
+    # 64 / 65 tiles and 1 024 / 1 025 are the limits of the offset forms,
+    # 511 / 512 and 262 143 / 262 144 cells those of the passes, 32 768 / 32 769
+    # those of the one-workgroup scan
+    (1, 512, "shuffled"), (4096, 700, "shuffled"), (4097, 700, "near"),
+    (262_144, 511, "shuffled"), (262_145, 512, "shuffled"), (262_144, 32_768, "near"),
+    (262_145, 32_769, "shuffled"), (300_001, 262_143, "shuffled"),
+    (300_001, 262_144, "shuffled"), (4_194_304, 9_000, "half"),
+    (4_194_305, 20_000, "shuffled"), (4_194_305, 20_000, "near")])
+def test_sort_sizes_bitexact(dev, api, n, n_cells, order, f32):
+    say("sort sizes", n, n_cells, order, f32)
+    rng = np.random.default_rng(n + n_cells)
+    cell = np.sort(rng.integers(0, n_cells, n)).astype(np.int32)
+    if order == "shuffled":
+        rng.shuffle(cell)
+    elif order == "half":
+        rng.shuffle(cell[:n // 2 + 4096])
+    else:
+        mv = rng.integers(0, n, n // 20)
+        cell[mv] = np.clip(cell[mv] + rng.integers(-70, 71, mv.size), 0, n_cells - 1)
+    cell[::4001] = -1
+    cell[n // 2] = n_cells
+    v = torch.randn(3, n, generator=torch.Generator().manual_seed(n),
+                    dtype=torch.float32 if f32 else torch.float64)
+    key = np.where((cell < 0) | (cell >= n_cells), n_cells, cell)
+    perm = np.argsort(key, kind="stable")
+    cs = np.concatenate([[0], np.cumsum(np.bincount(key, minlength=n_cells + 1))[:n_cells]])
+    st = api.new_status(dev)
+    # a workspace of any base
+    wsb = api.lib().dsmc_sort_cells_ws(n, n_cells)
+    buf = torch.full((wsb + 4,), 255, dtype=torch.uint8, device=dev)
+    vd, cd = v.to(dev), torch.from_numpy(cell).to(dev)
+    vo = torch.empty_like(vd)
+    csd = torch.empty(n_cells + 1, dtype=torch.int32, device=dev)
+    pd = torch.empty(n, dtype=torch.int32, device=dev)
+    api.check(api.lib().dsmc_sort_cells(n, n_cells, api._ptr(cd), api._dtype(vd), api._vec3(vd),
+                                        api._vec3(vo), api._ptr(csd), api._ptr(pd),
+                                        buf.data_ptr() + 4, wsb, api._ptr(st), api._stream(None)),
+              "dsmc_sort_cells")
+    outs = [(csd, pd, vo)]
+    if n <= 1 << 20:
+        b = [torch.empty_like(t) for t in outs[0]]
+        api.sort_cells_noalloc(cd, n_cells, vd, b[0], b[1], b[2])
+        outs.append(tuple(b))
+    for c, p, o in outs:
+        assert np.array_equal(c.cpu().numpy(), cs)
+        assert np.array_equal(p.cpu().numpy(), perm)
+        assert torch.equal(o.cpu(), v[:, torch.from_numpy(perm)])
+
+
 @pytest.mark.parametrize("case", ["c1", "ragged", "bigcells", "empty_tail", "bad_ids", "f32",
                                   "three_pass", "one_cell", "shuffled", "tiny", "all_bad",
                                   "sorted_runs"])
