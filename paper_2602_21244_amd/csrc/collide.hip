@@ -88,8 +88,10 @@ __device__ __forceinline__ void apply_pair(V3<T> v, int32_t a, int32_t b, const 
 
 template <typename T, int RULE>
 __global__ void __launch_bounds__(256)
-k_phaseB_lane(int32_t n_cells, PairsView pr, V3<T> v, PairBuf<T> d, int32_t max_pairs)
+k_phaseB_lane(int32_t n_cells, PairsView pr, V3<T> v, PairBuf<T> d, int32_t max_pairs,
+              int32_t* list)
 {
+    if (list && blockIdx.x == 0 && threadIdx.x < 2) list[threadIdx.x] = 0;   // see CellList
     for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n_cells;
          k += gridDim.x * blockDim.x) {
         const int32_t c = pr.cnt[k];
@@ -859,8 +861,19 @@ int phase_b(int rule, int dtype, int32_t n_cells, const int32_t* cell_start, dsm
     int lb = (n_cells + 255) / 256;
     lb = lb < 1 ? 1 : (lb > pb ? pb : lb);
     // cells with at most `thr` pairs: LANE; larger: WAVE when they fit its
-    // LDS tables (AUTO, WAVE), else BLOCK
+    // LDS tables (AUTO, WAVE), else BLOCK.  A lane takes about 1.8 us per pair
+    // of its cell, one after the other; a wave 9 to 12 us for up to 16 of
+    // them, and they queue up from some 4 000 cells on.  LANE against WAVE,
+    // FP64: 200 cells of 4 / 16 / 48 pairs 8 / 29 / 85 us against 11 / 12 /
+    // 16 us; 300 000 cells of 8 / 16 / 48 pairs 0.49 / 1.06 / 3.4 ms against
+    // 0.69 / 0.81 / 1.2 ms.  So AUTO goes by lanes to LANE_MAX pairs at most,
+    // and not at all while the wave kernel has a workgroup for every cell
+    // (10 000 cells of 4 pairs 26 us, of which the lanes alone would take 11
+    // and the launches after them 10).
+    constexpr int32_t LANE_MAX = 8;
     int32_t thr = block_threshold();
+    if (thr > LANE_MAX) thr = LANE_MAX;
+    if (n_cells <= (int64_t)device_cus() * match_schedule().wave_per_cu) thr = 0;
     bool use_wave = true;
     if (schedule == DSMC_SCHED_LANE) thr = INT32_MAX;
     if (schedule == DSMC_SCHED_BLOCK) { thr = 0; use_wave = false; }
@@ -880,11 +893,12 @@ int phase_b(int rule, int dtype, int32_t n_cells, const int32_t* cell_start, dsm
         const CellList list{reinterpret_cast<int32_t*>(d.f),                                \
                             (cap + 1) * (int64_t)sizeof(T) / 4};                            \
         if (need_lane) {                                                                    \
-            k_phaseB_lane<T, R><<<lb, 256, 0, s>>>(n_cells, pr, v3<T>(v), d, thr);          \
+            k_phaseB_lane<T, R><<<lb, 256, 0, s>>>(n_cells, pr, v3<T>(v), d, thr,           \
+                                                   need_rest ? list.p : nullptr);           \
             DSMC_LAUNCH_CHECK("phaseB:lane");                                               \
         }                                                                                   \
         if (need_rest && use_wave) {                                                        \
-            k_zero_list<<<1, 1, 0, s>>>(list.p);                                            \
+            if (!need_lane) k_zero_list<<<1, 1, 0, s>>>(list.p);                            \
             DSMC_LAUNCH_CHECK("phaseB:list");                                               \
             k_phaseB_wave<T, R><<<wb, 64, 0, s>>>(n_cells, pr, v3<T>(v), d, thr + 1, list); \
             DSMC_LAUNCH_CHECK("phaseB:wave");                                               \

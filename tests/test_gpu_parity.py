@@ -365,6 +365,38 @@ def test_schedules_bit_identical(dev, api, case):
         assert np.array_equal(out[0], o)
 
 
+@pytest.mark.parametrize("extra", [0, 1, 3000])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_auto_schedule_many_cells(dev, api, dtype, extra):
+    # AUTO takes lanes for small cells only past one workgroup per cell; cells
+    # of 0 to 40 pairs, so both sides of the 8-pair limit are there
+    say("auto schedule", dtype, extra)
+    n_cells = torch.cuda.get_device_properties(0).multi_processor_count * \
+        api.get_match_schedule()[0] + extra
+    g = torch.Generator().manual_seed(n_cells)
+    N = 24
+    cnt = torch.randint(0, 41, (n_cells,), generator=g)
+    cnt[::7] = 8 + (torch.arange(n_cells)[::7] % 2)
+    off = torch.cumsum(cnt, 0) - cnt
+    cap = int(cnt.sum())
+    cell = torch.arange(n_cells).repeat_interleave(cnt)
+    i = torch.randint(0, N, (cap,), generator=g)
+    j = (i + torch.randint(1, N, (cap,), generator=g)) % N
+    pairs = api.PairList(n_cells, cap, dev)
+    pairs.off.copy_(off)
+    pairs.cnt.copy_(cnt)
+    pairs.i[:cap] = (cell * N + i).to(dev)
+    pairs.j[:cap] = (cell * N + j).to(dev)
+    pairs.cell[:cap] = cell.to(dev)
+    v = (300.0 * torch.randn(3, N * n_cells, generator=g, dtype=torch.float64)).to(dtype).to(dev)
+    out = []
+    for code in (api.L.SCHED_LANE, api.L.SCHED_AUTO, api.L.SCHED_AUTO):
+        vs = v.clone()
+        api.collide_vhs(vs, pairs, 3, 9, schedule=code)
+        out.append(vs)
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 def test_moment_match_apply_modes(orc, dev, api, dtype):
     say("moment match modes", dtype)
