@@ -17,14 +17,17 @@
 // through the tiled GEMM, which also wrote and read the bf16 activations:
 // 7.6 ms); the 512 x 512 table, which keeps nothing, is bound by the matrix
 // cores and the epilogues they wait for: 0.44 ms, 0.83 PFLOP/s (1.67 ms).
-// A training step at 4 096 rows (forward, backward, Adam): 0.20 ms (0.66 ms).
+// A training step at 4 096 rows (forward, backward, Adam): 0.17 ms (0.66 ms).
 //
 // Backward: the same walk from the output down with W^T fragments; the
-// epilogue multiplies by SiLU' of the stored pre-activation, adds the bias
-// gradient's column sums from the FP32 values and writes delta and h = SiLU(z)
-// in bf16.  One launch over all layers' 128 x 128 weight-gradient tiles times
-// a K split forms dW = delta^T h (both operands transposed in registers while
-// they are staged), and one launch adds the splits in a fixed order.
+// epilogue multiplies by SiLU' of the stored pre-activation and writes delta
+// in FP32 and bf16 and h = SiLU(z) in bf16.  One launch over all layers'
+// 128 x 128 weight-gradient tiles times a K split forms dW = delta^T h (both
+// operands transposed in registers while they are staged), one the column
+// sums of the FP32 deltas, and one adds the splits and chunks.  Every sum is
+// taken in the order of the tiled GEMM's path, so the gradients are the same
+// bit for bit: a training run amplifies a rounding (a bf16 weight that flips)
+// to 1e-6 of the next loss.
 #include <math.h>
 
 #include "anet_fused.hpp"
@@ -55,9 +58,7 @@ struct AfDev {
     float* z[AF_MAX_LAYERS];
     __bf16* h[AF_MAX_LAYERS];
     __bf16* delta[AF_MAX_LAYERS];
-    float* red;
-    int red_off[AF_MAX_LAYERS];      // first column of layer l's sums in a tile's row of red
-    int red_ld;
+    float* dz[AF_MAX_LAYERS];
 };
 
 __device__ __forceinline__ float af_sigm(float z)
@@ -319,42 +320,22 @@ k_anet_fused_fwd(AfDev n, int64_t R, const float* __restrict__ x, float* __restr
 // ------------------------------------------------------------------------
 // Backward
 // ------------------------------------------------------------------------
-// Sum over the 32 lanes of each half-wave of the 16 values v[4 q + i] (unit
-// 8 q + 4 half + i): halves of the values are exchanged with halves of the
-// lanes, so 16 exchanges leave lane 2 u of a half the sum of its u-th value.
-__device__ __forceinline__ float af_row_sum(float (&v)[16], int lane)
-{
-#pragma unroll
-    for (int s = 8; s >= 1; s >>= 1) {
-        const bool up = (lane & (2 * s)) != 0;
-#pragma unroll
-        for (int i = 0; i < s; ++i) {
-            const float send = up ? v[i] : v[i + s], kept = up ? v[i + s] : v[i];
-            v[i] = kept + __shfl_xor(send, 2 * s, 64);
-        }
-    }
-    return v[0] + __shfl_xor(v[0], 1, 64);
-}
-
-// Epilogue of dL/dz of layer j (width N): acc * SiLU'(z), its row sums (and
-// with x those of the layer-0 weights), delta and h in bf16.
+// Epilogue of dL/dz of layer j (width N): acc * SiLU'(z) in FP32 (blocks, for
+// the column sums; zero past the last row), delta and h in bf16.
 template <int NU, int NR>
 __device__ __forceinline__ void af_store_bwd(const AfDev& n, int j, const floatx16a (&acc)[NU][NR],
-                                             int u0, int rb0, int64_t row0, int64_t R,
-                                             const float* xs, float* __restrict__ red, __bf16* hs)
+                                             int u0, int rb0, int64_t row0, int64_t R, __bf16* hs)
 {
     const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
     const int N = n.d[j + 1];
     const float* __restrict__ z = n.z[j];
+    float* __restrict__ dz = n.dz[j];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        float s[16], s0[16], s1[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = s0[i] = s1[i] = 0.0f;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             const int row = (rb0 + r) * 32 + col;
-            const bool in = row0 + row < R;
+            const bool in = row0 + row < R, blk = row0 + (rb0 + r) * 32 < R;
             const int64_t o = (row0 + row) * N + (u0 + u) * 32 + 4 * half;
             floatx4a zz[4];
 #pragma unroll
@@ -362,22 +343,19 @@ __device__ __forceinline__ void af_store_bwd(const AfDev& n, int j, const floatx
                 zz[q] = in ? *reinterpret_cast<const floatx4a*>(
                                  z + af_zoff(row0, rb0 + r, N, u0 + u, q))
                            : floatx4a{0.f, 0.f, 0.f, 0.f};
-            const float x0 = xs[2 * row], x1 = xs[2 * row + 1];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 bf16x4a dv, hv;
+                floatx4a d4;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float zi = zz[q][i], sg = af_sigm(zi);
                     const float d = acc[u][r][4 * q + i] * (sg * (1.0f + zi * (1.0f - sg)));
                     dv[i] = (__bf16)d;
                     hv[i] = (__bf16)(zi * sg);
-                    s[4 * q + i] += d;
-                    if (j == 0) {
-                        s0[4 * q + i] += d * x0;
-                        s1[4 * q + i] += d * x1;
-                    }
+                    d4[i] = in ? d : 0.0f;
                 }
+                if (blk) *reinterpret_cast<floatx4a*>(dz + af_zoff(row0, rb0 + r, N, u0 + u, q)) = d4;
                 if (in) *reinterpret_cast<bf16x4a*>(n.h[j] + o + 8 * q) = hv;
                 if (j > 0) {
                     if (in) *reinterpret_cast<bf16x4a*>(n.delta[j] + o + 8 * q) = dv;
@@ -386,27 +364,13 @@ __device__ __forceinline__ void af_store_bwd(const AfDev& n, int j, const floatx
                 }
             }
         }
-        // value index held by this lane after the exchanges: bits of the lane
-        const int vi = ((lane >> 4) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 +
-                       ((lane >> 1) & 1);
-        const int unit = (u0 + u) * 32 + 8 * (vi >> 2) + 4 * half + (vi & 3);
-        float* o = red + n.red_off[j] + (j == 0 ? 3 * unit : unit);
-        const float a = af_row_sum(s, lane);
-        if ((lane & 1) == 0) o[0] = a;
-        if (j == 0) {
-            const float a0 = af_row_sum(s0, lane), a1 = af_row_sum(s1, lane);
-            if ((lane & 1) == 0) {
-                o[1] = a0;
-                o[2] = a1;
-            }
-        }
     }
 }
 
 template <int NU, int NR, int PF>
 __device__ __forceinline__ void af_layer_bwd(const AfDev& n, int j, int u0, int rb0, bool active,
                                              const __bf16* d_out, int64_t row0, int64_t R,
-                                             const float* xs, float* red, __bf16* hs)
+                                             __bf16* hs)
 {
     floatx16a acc[NU][NR];
     const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
@@ -434,12 +398,10 @@ __device__ __forceinline__ void af_layer_bwd(const AfDev& n, int j, int u0, int 
         }
     }
     __syncthreads();
-    if (active) af_store_bwd<NU, NR>(n, j, acc, u0, rb0, row0, R, xs, red, hs);
+    if (active) af_store_bwd<NU, NR>(n, j, acc, u0, rb0, row0, R, hs);
     __syncthreads();
 }
 
-// Tile b writes its sums to row b of red; a 128-unit layer's two row halves
-// (RB > 1) write rows b and tiles + b, which are added by the final kernel.
 template <int RB, int PF>
 __global__ void __launch_bounds__(AF_THREADS)
 k_anet_fused_bwd(AfDev n, int64_t R, const float* __restrict__ dy)
@@ -447,46 +409,135 @@ k_anet_fused_bwd(AfDev n, int64_t R, const float* __restrict__ dy)
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     constexpr int ROWS = 32 * RB;
     __bf16* hs = reinterpret_cast<__bf16*>(smem);
-    float* xs = reinterpret_cast<float*>(smem + (size_t)ROWS * n.ld * sizeof(__bf16));
-    __bf16* ds = reinterpret_cast<__bf16*>(xs + 2 * ROWS);
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    __bf16* ds = reinterpret_cast<__bf16*>(smem + (size_t)ROWS * n.ld * sizeof(__bf16));
+    const int t = threadIdx.x, w = t >> 6;
     const int64_t row0 = (int64_t)blockIdx.x * ROWS;
-    float* red = n.red + (int64_t)blockIdx.x * n.red_ld;
-    float d = 0.0f;
     if (t < ROWS) {
         const int64_t g = row0 + t;
-        const bool in = g < R;
-        xs[2 * t] = in ? n.x[2 * g] : 0.0f;
-        xs[2 * t + 1] = in ? n.x[2 * g + 1] : 0.0f;
-        if (in) d = dy[g] / (1.0f + expf(-n.z[n.L - 1][g]));
+        float d = 0.0f;
+        if (g < R) {
+            d = dy[g] / (1.0f + expf(-n.z[n.L - 1][g]));
+            n.dz[n.L - 1][g] = d;
+            n.delta[n.L - 1][g] = (__bf16)d;
+        }
         ds[t] = (__bf16)d;
-        if (in) n.delta[n.L - 1][g] = (__bf16)d;
-    }
-    if (w < (RB + 1) / 2) {   // sum of the tile's output deltas, one value per wave
-        float s = d;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if (lane == 0) red[n.red_off[n.L - 1] + w] = s;
     }
     __syncthreads();
     for (int j = n.L - 2; j >= 0; --j) {
         const __bf16* d_out = j == n.L - 2 ? ds : nullptr;
         const int nt = n.d[j + 1] >> 5;
         if (nt > 8) {
-            af_layer_bwd<2, RB, PF>(n, j, 2 * w, 0, 2 * w < nt, d_out, row0, R, xs, red, hs);
+            af_layer_bwd<2, RB, PF>(n, j, 2 * w, 0, 2 * w < nt, d_out, row0, R, hs);
         } else if (nt > 4) {
-            af_layer_bwd<1, RB, PF>(n, j, w, 0, w < nt, d_out, row0, R, xs, red, hs);
+            af_layer_bwd<1, RB, PF>(n, j, w, 0, w < nt, d_out, row0, R, hs);
         } else {
             constexpr int NR = RB > 1 ? RB / 2 : 1;
-            float* r2 = red + (int64_t)(w >> 2) * gridDim.x * n.red_ld;
             af_layer_bwd<1, NR, PF>(n, j, w & 3, (w >> 2) * NR, RB > 1 || w < 4, d_out, row0, R,
-                                    xs, r2, hs);
+                                    hs);
         }
     }
 }
 
+// Column sums of dL/dz in the order of the tiled GEMM's path (so a network
+// trains the same whichever path its widths take): chunks of 256 rows, in a
+// chunk rows w, w + 4, ... of each w < 4 one after the other, the four sums
+// added in order.  A wave takes one chunk and 64 units of a layer: lane
+// (block, four units, w) reads 16 bytes a row from the FP32 blocks.
+struct AfCols {
+    int L;
+    int d[AF_MAX_LAYERS + 1];
+    const float* dz[AF_MAX_LAYERS];
+    const float* x;
+    int first[AF_MAX_LAYERS + 1];    // first group of 64 units of each hidden layer
+    int red_off[AF_MAX_LAYERS];      // first column of layer l's sums in a chunk's row of red
+    int red_ld;
+    int64_t R, chunks;
+    float* red;                      // [chunks][red_ld]
+};
+constexpr int AC_ROWS = 256;
+
+__global__ void __launch_bounds__(64)
+k_anet_cols(AfCols g)
+{
+    const int lane = threadIdx.x, ph = lane & 3;
+    const int groups = g.first[g.L - 1];
+    const int64_t job = blockIdx.x;
+    if (job >= g.chunks * groups) {
+        // the output's single column: 16 chunks per wave
+        const int64_t ch = (job - g.chunks * groups) * 16 + (lane >> 2);
+        float s = 0.0f;
+        if (ch < g.chunks) {
+            const int64_t r1 = (ch + 1) * AC_ROWS < g.R ? (ch + 1) * AC_ROWS : g.R;
+            const float* dz = g.dz[g.L - 1];
+#pragma unroll 8
+            for (int64_t r = ch * AC_ROWS + ph; r < r1; r += 4) s += dz[r];
+        }
+        const int b = lane & ~3;
+        const float a0 = __shfl(s, b, 64), a1 = __shfl(s, b + 1, 64), a2 = __shfl(s, b + 2, 64),
+                    a3 = __shfl(s, b + 3, 64);
+        if (ph == 0 && ch < g.chunks)
+            g.red[ch * g.red_ld + g.red_off[g.L - 1]] = ((a0 + a1) + a2) + a3;
+        return;
+    }
+    const int64_t ch = job / groups;
+    const int gr = (int)(job - ch * groups);
+    int l = 0;
+    while (gr >= g.first[l + 1]) ++l;
+    const int N = g.d[l + 1], u = 2 * (gr - g.first[l]) + (lane >> 5), qh = (lane >> 2) & 7;
+    const float* dz = g.dz[l] + (int64_t)u * 1024 + (qh >> 1) * 256 + (qh & 1) * 128 + ph * 4;
+    floatx4a s = {0.f, 0.f, 0.f, 0.f}, s0 = s, s1 = s;
+    const int64_t b0 = ch * (AC_ROWS / 32), nb = (g.R + 31) / 32;
+    const int64_t b1 = b0 + AC_ROWS / 32 < nb ? b0 + AC_ROWS / 32 : nb;
+    for (int64_t b = b0; b < b1; ++b) {
+        floatx4a v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v[e] = *reinterpret_cast<const floatx4a*>(dz + b * (N >> 5) * 1024 + e * 16);
+        if (l == 0) {
+            float x0[8], x1[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int64_t r = b * 32 + 4 * e + ph;
+                x0[e] = r < g.R ? g.x[2 * r] : 0.0f;
+                x1[e] = r < g.R ? g.x[2 * r + 1] : 0.0f;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    s0[i] = __builtin_fmaf(v[e][i], x0[e], s0[i]);
+                    s1[i] = __builtin_fmaf(v[e][i], x1[e], s1[i]);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] += v[e][i];
+    }
+    // lane ph of the four writes unit ph
+    const int base = lane & ~3, unit = u * 32 + 4 * qh + ph;
+    auto total = [&](const floatx4a& a) {
+        float t = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float a0 = __shfl(a[i], base, 64), a1 = __shfl(a[i], base + 1, 64);
+            const float a2 = __shfl(a[i], base + 2, 64), a3 = __shfl(a[i], base + 3, 64);
+            const float q = ((a0 + a1) + a2) + a3;
+            t = ph == i ? q : t;
+        }
+        return t;
+    };
+    float* o = g.red + ch * g.red_ld + g.red_off[l] + (l == 0 ? 3 * unit : unit);
+    o[0] = total(s);
+    if (l == 0) {
+        o[1] = total(s0);
+        o[2] = total(s1);
+    }
+}
+
 // dW_l = delta_l^T h_{l-1} for all layers l >= 1 at once: 128 x 128 tiles,
-// K (the batch) split over workgroups.  Rows are staged 64 at a time, both
+// K (the batch) split over AF_SPLITS workgroups, in the tiled GEMM's lengths
+// (and so with its results).  Rows are staged 64 at a time, both
 // operands transposed in registers (8 rows x 4 units per thread) into
 // [unit][k] LDS rows of 128 bytes whose eight 16-byte chunks are permuted by
 // (unit ^ unit / 4) & 7, which keeps the writes and the fragment reads free
@@ -505,7 +556,6 @@ struct AdArgs {
     AdLayer l[AF_MAX_LAYERS];
     int tiles;
     int64_t R, kc, total;
-    int splits;
     float* partial;
 };
 
@@ -554,7 +604,7 @@ k_anet_dw(AdArgs g)
 {
     __shared__ __attribute__((aligned(16))) __bf16 As[2][AD_T * AD_K];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[2][AD_T * AD_K];
-    const int split = blockIdx.x % g.splits, tile = blockIdx.x / g.splits;
+    const int split = blockIdx.x % AF_SPLITS, tile = blockIdx.x / AF_SPLITS;
     int l = 0;
     while (l + 1 < g.n && tile >= g.l[l + 1].first) ++l;
     const AdLayer& y = g.l[l];
@@ -623,23 +673,21 @@ k_anet_dw(AdArgs g)
             }
 }
 
-// The weight gradients: K splits added in split order, one output per thread.
-// The bias and layer-0 gradients: the tiles' sums, 64 columns per workgroup;
-// its four waves take every fourth tile and are added in wave order.
+// The weight gradients: the AF_SPLITS partials of an element, sums of every
+// fourth one added in order.  The bias and layer-0 gradients: 16 sums of every
+// 16th chunk, added in order; 64 columns per workgroup.
 struct AfFinal {
     int n;
     float* dW[AF_MAX_LAYERS];     // layers 1 .. n
     int64_t off[AF_MAX_LAYERS + 1];
     const float* partial;
-    int splits;
     int64_t total;
     int wblocks;                  // workgroups of the weight part
     const float* red;
     int red_ld;
-    int64_t tiles;
+    int64_t chunks;
     int nl;                       // weight layers (columns of red)
     int red_off[AF_MAX_LAYERS + 1];
-    int rows2[AF_MAX_LAYERS];     // two rows of sums per tile
     float* db[AF_MAX_LAYERS];
     float* dW0;
 };
@@ -647,65 +695,49 @@ struct AfFinal {
 __global__ void __launch_bounds__(256)
 k_anet_final(AfFinal g)
 {
+    static_assert(AF_SPLITS == 16, "four sums of four partials");
     if ((int)blockIdx.x < g.wblocks) {
         for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < g.total;
              q += (int64_t)g.wblocks * 256) {
-            float v = 0.0f;
-            int s = 0;
-            for (; s + 4 <= g.splits; s += 4) {
-                const float a0 = g.partial[s * g.total + q];
-                const float a1 = g.partial[(s + 1) * g.total + q];
-                const float a2 = g.partial[(s + 2) * g.total + q];
-                const float a3 = g.partial[(s + 3) * g.total + q];
-                v += a0; v += a1; v += a2; v += a3;
+            float a[AF_SPLITS], v[4];
+#pragma unroll
+            for (int s = 0; s < AF_SPLITS; ++s) a[s] = g.partial[s * g.total + q];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                v[w] = 0.0f;
+#pragma unroll
+                for (int s = w; s < AF_SPLITS; s += 4) v[w] += a[s];
             }
-            for (; s < g.splits; ++s) v += g.partial[s * g.total + q];
             int l = 0;
             while (q >= g.off[l + 1]) ++l;
-            g.dW[l][q - g.off[l]] = v;
+            g.dW[l][q - g.off[l]] = ((v[0] + v[1]) + v[2]) + v[3];
         }
         return;
     }
-    __shared__ float part[4][64];
+    __shared__ float part[16][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int c = ((int)blockIdx.x - g.wblocks) * 64 + lane;
-    int l = 0;
-    if (c < g.red_off[g.nl])
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (c < g.red_ld) {
+        const float* p = g.red + c;
+        for (int64_t r = 0; r < g.chunks; r += 16)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (r + 4 * w + e < g.chunks) v[e] += p[(r + 4 * w + e) * g.red_ld];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) part[4 * w + e][lane] = v[e];
+    __syncthreads();
+    if (w == 0 && c < g.red_ld) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sum += part[q][lane];
+        int l = 0;
         while (c >= g.red_off[l + 1]) ++l;
-    float v = 0.0f;
-    if (c < g.red_off[g.nl]) {
-        const int64_t rows = g.rows2[l] ? 2 * g.tiles : g.tiles;
-        int64_t r = w;
-        for (; r + 12 < rows; r += 16) {
-            const float a0 = g.red[r * g.red_ld + c], a1 = g.red[(r + 4) * g.red_ld + c];
-            const float a2 = g.red[(r + 8) * g.red_ld + c], a3 = g.red[(r + 12) * g.red_ld + c];
-            v += a0; v += a1; v += a2; v += a3;
-        }
-        for (; r < rows; r += 4) v += g.red[r * g.red_ld + c];
-    }
-    part[w][lane] = v;
-    __syncthreads();
-    if (w == 0 && c < g.red_off[g.nl]) {
-        const float sum = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
         const int k = c - g.red_off[l];
-        if (l == 0) {
-            if (k % 3 == 0) g.db[0][k / 3] = sum;
-            else g.dW0[2 * (k / 3) + k % 3 - 1] = sum;
-        } else if (l < g.nl - 1) {
-            g.db[l][k] = sum;
-        } else {
-            part[0][lane] = sum;   // the output bias: one column per wave of a tile
-        }
-    }
-    __syncthreads();
-    // the output layer's columns are the last ones: one to two of them
-    if (threadIdx.x == 0) {
-        const int c0 = g.red_off[g.nl - 1], first = ((int)blockIdx.x - g.wblocks) * 64;
-        if (c0 >= first && c0 < first + 64) {
-            float sum = part[0][c0 - first];
-            for (int k = c0 + 1; k < g.red_off[g.nl]; ++k) sum += part[0][k - first];
-            g.db[g.nl - 1][0] = sum;
-        }
+        if (l > 0) g.db[l][k] = sum;
+        else if (k % 3 == 0) g.db[0][k / 3] = sum;
+        else g.dW0[2 * (k / 3) + k % 3 - 1] = sum;
     }
 }
 
@@ -737,19 +769,20 @@ static int bwd_row_blocks(int64_t R) { return R <= 8192 ? 1 : 2; }
 
 static int64_t tiles_of(int64_t R, int rb) { return (R + 32 * rb - 1) / (32 * rb); }
 
-// Columns of a tile's row of sums: three per unit of layer 0, one per unit
-// of layers 1 .. L-2, then the output's (one per wave of the tile's rows).
-// Padded so the output's columns do not straddle a group of 64.
+// Columns of a chunk's row of sums: three per unit of layer 0, one per unit
+// of every other layer.
 static int red_columns(const AnetShape& a, int* off)
 {
     int c = 0;
-    for (int l = 0; l < a.L - 1; ++l) {
+    for (int l = 0; l < a.L; ++l) {
         if (off) off[l] = c;
         c += l == 0 ? 3 * a.d[1] : a.d[l + 1];
     }
-    if (off) off[a.L - 1] = c;   // a multiple of 128
-    return c + 2;
+    if (off) off[a.L] = c;
+    return c;
 }
+
+static int64_t chunks_of(int64_t R) { return (R + AC_ROWS - 1) / AC_ROWS; }
 
 static int64_t weights_of(const AnetShape& a)
 {
@@ -770,13 +803,15 @@ AnetFusedWs anet_fused_layout(void* base, const AnetShape& a, int64_t R)
         w.z[l] = reinterpret_cast<float*>(
             take(sizeof(float) * (l < a.L - 1 ? blocks * a.d[l + 1] : n)));
         if (l < a.L - 1) w.h[l] = reinterpret_cast<__bf16*>(take(sizeof(__bf16) * n));
+        w.dz[l] = reinterpret_cast<float*>(
+            take(sizeof(float) * (l < a.L - 1 ? blocks * a.d[l + 1] : n)));
         if (l > 0) w.delta[l] = reinterpret_cast<__bf16*>(take(sizeof(__bf16) * n));
         w.b[l] = reinterpret_cast<float*>(take(sizeof(float) * a.d[l + 1]));
         if (l > 0 && l < a.L - 1)
             w.wp[l] = reinterpret_cast<__bf16*>(take(sizeof(__bf16) * (size_t)a.d[l] * a.d[l + 1]));
     }
     w.red = reinterpret_cast<float*>(
-        take(sizeof(float) * 2 * (size_t)tiles_of(R, bwd_row_blocks(R)) * (size_t)red_columns(a, nullptr)));
+        take(sizeof(float) * (size_t)chunks_of(R) * (size_t)red_columns(a, nullptr)));
     w.partial = reinterpret_cast<float*>(take(sizeof(float) * AF_SPLITS * (size_t)weights_of(a)));
     w.bytes = o;
     return w;
@@ -797,9 +832,8 @@ static AfDev dev_of(const dsmc_anet* net, const AnetShape& a, const AnetFusedWs&
         n.z[l] = w.z[l];
         n.h[l] = w.h[l];
         n.delta[l] = w.delta[l];
+        n.dz[l] = w.dz[l];
     }
-    n.red = w.red;
-    n.red_ld = red_columns(a, n.red_off);
     return n;
 }
 
@@ -914,37 +948,42 @@ int anet_fused_backward(const dsmc_anet* net, const AnetShape& a, int64_t R, con
     }
     g.R = R;
     g.total = off;
-    // splits of at least 512 rows: enough workgroups for the chip at the
-    // training batches without more partials than the sum is worth
-    int64_t splits = (R + 511) / 512;
-    if (splits > AF_SPLITS) splits = AF_SPLITS;
-    g.kc = ((R + splits - 1) / splits + AD_K - 1) / AD_K * AD_K;
-    splits = (R + g.kc - 1) / g.kc;
-    g.splits = (int)splits;
+    g.kc = ((R + AF_SPLITS - 1) / AF_SPLITS + 31) / 32 * 32;   // trailing splits may be empty
     g.partial = w.partial;
-    k_anet_dw<<<(unsigned)(g.tiles * splits), 256, 0, s>>>(g);
+    k_anet_dw<<<(unsigned)(g.tiles * AF_SPLITS), 256, 0, s>>>(g);
     DSMC_LAUNCH_CHECK("anet:dw");
+
+    AfCols q{};
+    q.L = a.L;
+    for (int l = 0; l <= a.L; ++l) q.d[l] = a.d[l];
+    for (int l = 0; l < a.L; ++l) {
+        q.dz[l] = w.dz[l];
+        if (l + 1 < a.L) q.first[l + 1] = q.first[l] + a.d[l + 1] / 64;
+    }
+    q.x = w.x;
+    q.red_ld = red_columns(a, f.red_off);
+    for (int l = 0; l < a.L; ++l) q.red_off[l] = f.red_off[l];
+    q.R = R;
+    q.chunks = chunks_of(R);
+    q.red = w.red;
+    const int64_t jobs = q.chunks * q.first[a.L - 1] + (q.chunks + 15) / 16;
+    if (jobs > 2147483647) return arg_error("anet: too many rows");
+    k_anet_cols<<<(unsigned)jobs, 64, 0, s>>>(q);
+    DSMC_LAUNCH_CHECK("anet:cols");
 
     f.n = g.n;
     f.partial = w.partial;
-    f.splits = g.splits;
     f.total = off;
     int64_t wb = (off + 255) / 256;
     const int pb = persistent_blocks(256);
     f.wblocks = (int)(wb < pb ? wb : pb);
     f.red = w.red;
-    f.red_ld = n.red_ld;
-    f.tiles = tiles_of(R, rb);
+    f.red_ld = q.red_ld;
+    f.chunks = q.chunks;
     f.nl = a.L;
-    for (int l = 0; l < a.L; ++l) {
-        f.red_off[l] = n.red_off[l];
-        f.db[l] = db[l];
-        f.rows2[l] = (l < a.L - 1 && a.d[l + 1] == 128 && rb > 1) ? 1 : 0;
-    }
-    f.red_off[a.L] = n.red_off[a.L - 1] + (rb + 1) / 2;
+    for (int l = 0; l < a.L; ++l) f.db[l] = db[l];
     f.dW0 = dW[0];
-    const int cb = (f.red_off[a.L] + 63) / 64;
-    k_anet_final<<<f.wblocks + cb, 256, 0, s>>>(f);
+    k_anet_final<<<f.wblocks + (f.red_ld + 63) / 64, 256, 0, s>>>(f);
     DSMC_LAUNCH_CHECK("anet:final");
     return DSMC_OK;
 }

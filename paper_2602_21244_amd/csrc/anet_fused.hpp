@@ -6,7 +6,7 @@
 namespace dsmc {
 
 constexpr int AF_MAX_LAYERS = DSMC_ANET_MAX_LAYERS;
-constexpr int AF_SPLITS = 16;   // most K splits of the weight-gradient kernel
+constexpr int AF_SPLITS = 16;   // K splits of the weight-gradient kernel (those of the tiled GEMM's)
 
 struct AnetShape {
     int L;                        // weight layers
@@ -21,10 +21,11 @@ struct AnetFusedWs {
     float* x;                     // inputs [R][2]
     float* z[AF_MAX_LAYERS];      // pre-activations of hidden layers (blocks of 32 x 32), output [R]
     __bf16* h[AF_MAX_LAYERS];     // hidden activations [R][d_{l+1}] (backward)
+    float* dz[AF_MAX_LAYERS];     // dL/dz_l in FP32, laid out as z (backward)
     __bf16* delta[AF_MAX_LAYERS]; // dL/dz_l [R][d_{l+1}], l >= 1 (backward)
     __bf16* wp[AF_MAX_LAYERS];    // weights in fragment order (layers 1 .. L-2)
     float* b[AF_MAX_LAYERS];      // biases, aligned copies
-    float* red;                   // per-tile sums of the bias and layer-0 gradients
+    float* red;                   // per-chunk sums of the bias and layer-0 gradients
     float* partial;               // [splits][weights of layers 1 .. L-1]
     size_t bytes;
 };

@@ -110,6 +110,39 @@ def test_anet_row_tiles_match_fp64(orc, dev, api, dims, rows):
         assert eW < 3e-2 and eb < 3e-2
 
 
+@pytest.mark.parametrize("dims", [(2, 128, 1), (2, 384, 128, 256, 1)])
+@pytest.mark.parametrize("rows", [1, 33, 257, 4096, 8193, 32833])
+def test_anet_paths_agree_bitwise(dev, api, dims, rows):
+    """A layer widened by 32 units without weights takes the tiled GEMM path
+    and adds only zeros: outputs and gradients are the same bit for bit, twice
+    from one forward."""
+    say("anet paths", dims, rows)
+    net, _, _ = _net(api, dev, 5, dims)
+    wide = [d + 32 if 0 < q < len(dims) - 1 else d for q, d in enumerate(dims)]
+    Ws, bs = [], []
+    for q, (w, b) in enumerate(zip(net.master_W, net.b)):
+        W2, b2 = torch.zeros(wide[q + 1], wide[q]), torch.zeros(wide[q + 1])
+        W2[:w.shape[0], :w.shape[1]], b2[:w.shape[0]] = w.cpu(), b.cpu()
+        Ws.append(W2)
+        bs.append(b2)
+    net2 = api.AngleNet(Ws, bs)
+    g = torch.Generator().manual_seed(rows)
+    x = (2.0 * torch.rand(rows, 2, generator=g) - 1.0).to(dev)
+    dy = (torch.randn(rows, generator=g) / rows).to(dev)
+    out = []
+    for n in (net, net2):
+        y, ws = api.anet_forward(n, x)
+        for _ in range(2):
+            dW = [torch.full_like(w, float("nan")) for w in n.master_W]
+            db = [torch.full_like(b, float("nan")) for b in n.b]
+            api.anet_backward(n, dy, dW, db, ws)
+        out.append((y, dW, db))
+    assert torch.equal(out[0][0], out[1][0])
+    for l, (w, b) in enumerate(zip(out[0][1], out[0][2])):
+        assert torch.equal(w, out[1][1][l][:w.shape[0], :w.shape[1]]), l
+        assert torch.equal(b, out[1][2][l][:b.shape[0]]), l
+
+
 def test_huber_loss_matches_oracle(orc, dev, api):
     say("huber loss")
     rng = np.random.default_rng(2)
