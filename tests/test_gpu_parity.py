@@ -803,6 +803,33 @@ def test_neural_rows_bf16(orc, dev, api):
     np.testing.assert_allclose(np.linalg.norm(vr.double().cpu().numpy(), axis=1), rows["g"], rtol=1e-5)
 
 
+@pytest.mark.parametrize("dims", [(8, 64, 3), (8, 128, 128, 128, 3), (11, 256, 20)])
+def test_neural_rows_tiles_and_alignment_bitwise(dev, api, dims):
+    """A row's output does not depend on the number of rows (how the tiles are
+    dealt out changes with one per wave of the chip, 65 536 rows on 256 CUs at
+    width 64 and 128) nor on the weights' alignment (8-byte loads or single
+    elements)."""
+    say("neural rows tiles", dims)
+    Ws, bs = _net_params(13, dims)
+    net = api.Net(Ws, bs, device=dev)
+    odd = api.Net(Ws, bs, device=dev)
+    odd.W = [torch.cat([w.new_zeros(1), w.flatten()])[1:] for w in net.W]
+    odd.refresh()
+    assert any(w.data_ptr() % 8 for w in odd.W)
+    n = 70_001
+    g = torch.Generator().manual_seed(3)
+    x = torch.randn(n, dims[0], generator=g).to(dev)
+    sp = torch.ones(n, device=dev)
+    y, vr = api.neural_forward_rows(net, x, sp)
+    assert torch.isfinite(y).all()
+    for rows in (1, 33, 8_193, 32_768, 32_769, 65_536, 65_537, n):
+        for m in (net, odd):
+            y2, vr2 = api.neural_forward_rows(m, x[:rows].contiguous(), sp[:rows])
+            assert torch.equal(y2, y[:rows]), rows
+            if dims[-1] == 3:
+                assert torch.equal(vr2, vr[:rows]), rows
+
+
 def test_backward_fp64_against_oracle(orc, dev, api):
     say("backward fp64")
     rows = W.training_rows(seed=7, n=700)
