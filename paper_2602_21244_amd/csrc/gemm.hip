@@ -138,8 +138,7 @@ __device__ __forceinline__ void store_tile(const TileRegs& R, bool kcontig, __bf
 // Double-buffered main loop: the next k tile is loaded into registers while
 // the current one is multiplied from LDS, then stored into the other buffer;
 // one barrier per k tile.
-__global__ void __launch_bounds__(G_THREADS, 3)
-k_gemm_bf16(GemmArgs g)
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int64_t wid)
 {
     __shared__ __attribute__((aligned(16))) __bf16 As[2][GM * GLD];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[2][GN * GLD];
@@ -155,7 +154,6 @@ k_gemm_bf16(GemmArgs g)
     // every XCD.  With fewer than eight m tiles (a short, wide C) the tiles
     // are dealt m fastest: the few A rows are shared by every XCD anyway.
     const int64_t m_tiles = (g.M + GM - 1) / GM, n_tiles = (g.N + GN - 1) / GN;
-    const int64_t wid = blockIdx.x;
     int64_t mt, nt, split = 0;
     const int64_t splits = g.ksplits > 1 ? g.ksplits : 1;
     if (splits > 1) {
@@ -290,17 +288,40 @@ k_gemm_bf16(GemmArgs g)
     }
 }
 
+__global__ void __launch_bounds__(G_THREADS, 3)
+k_gemm_bf16(GemmArgs g)
+{
+    gemm_tile(g, blockIdx.x);
+}
+
+// Several products in one launch: workgroup w belongs to the last one whose
+// first workgroup is not past it.
+struct GemmGroup {
+    int n;
+    int32_t first[GEMM_GROUP_MAX + 1];    // of the product, then of the reduction
+    int32_t rfirst[GEMM_GROUP_MAX + 1];
+    int splits;
+    GemmArgs g[GEMM_GROUP_MAX];
+};
+
+__global__ void __launch_bounds__(G_THREADS, 3)
+k_gemm_group(GemmGroup q)
+{
+    int p = 0;
+    while ((int)blockIdx.x >= q.first[p + 1]) ++p;
+    gemm_tile(q.g[p], blockIdx.x - q.first[p]);
+}
+
 // Sum of the K-split partials, then the epilogue.  A workgroup takes 64
 // outputs; its four waves sum interleaved quarters of the splits (split
 // s to wave s % 4, in split order), and the four sums are added in wave
 // order: a fixed order whatever the launch.
-__global__ void __launch_bounds__(256)
-k_gemm_reduce(GemmArgs g, int splits)
+__device__ __forceinline__ void gemm_reduce(const GemmArgs& g, int splits, int bid, int nblk)
 {
     __shared__ float part[4][64];
     const int64_t total = g.M * g.N;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int64_t q0 = (int64_t)blockIdx.x * 64; q0 < total; q0 += (int64_t)gridDim.x * 64) {
+    for (int64_t q0 = (int64_t)bid * 64; q0 < total; q0 += (int64_t)nblk * 64) {
         const int64_t q = q0 + lane;
         float v = 0.0f;
         if (q < total) {
@@ -329,8 +350,8 @@ k_gemm_reduce(GemmArgs g, int splits)
     // workgroups of the grid
     if (g.asum_out) {
         const int64_t nb = (g.M + 63) / 64;
-        const int64_t b = (int64_t)gridDim.x - 1 - blockIdx.x;
-        for (int64_t mb = b; mb < nb; mb += gridDim.x) {
+        const int64_t b = (int64_t)nblk - 1 - bid;
+        for (int64_t mb = b; mb < nb; mb += nblk) {
             const int64_t m = mb * 64 + lane;
             float v = 0.0f;
             if (m < g.M) {
@@ -353,6 +374,20 @@ k_gemm_reduce(GemmArgs g, int splits)
             __syncthreads();
         }
     }
+}
+
+__global__ void __launch_bounds__(256)
+k_gemm_reduce(GemmArgs g, int splits)
+{
+    gemm_reduce(g, splits, blockIdx.x, gridDim.x);
+}
+
+__global__ void __launch_bounds__(256)
+k_gemm_group_reduce(GemmGroup q)
+{
+    int p = 0;
+    while ((int)blockIdx.x >= q.rfirst[p + 1]) ++p;
+    gemm_reduce(q.g[p], q.splits, blockIdx.x - q.rfirst[p], q.rfirst[p + 1] - q.rfirst[p]);
 }
 
 // Column sums in two fixed-order stages.  Partial: a workgroup takes
@@ -457,29 +492,73 @@ int colsum_f32(const float* a, int64_t R, int n, const float* x2, float* red, fl
     return DSMC_OK;
 }
 
-int gemm_bf16(const GemmArgs& g0, int splits, hipStream_t s)
+// Workgroups of a product and of its split reduction.
+static int64_t gemm_tiles(const GemmArgs& g, int splits)
 {
-    GemmArgs g = g0;
-    if (g.M <= 0 || g.N <= 0) return DSMC_OK;
-    if (splits < 1) splits = 1;
     const int64_t gx = (g.M + GM - 1) / GM, gy = (g.N + GN - 1) / GN;
-    const int64_t tiles = splits > 1 ? gx * gy * splits : (gx >= 8 ? (gx + 7) / 8 * 8 * gy : gx * gy);
-    if (tiles > 2147483647 || splits > 65535) return arg_error("gemm: grid too large");
+    return splits > 1 ? gx * gy * splits : (gx >= 8 ? (gx + 7) / 8 * 8 * gy : gx * gy);
+}
+
+static int64_t reduce_blocks(const GemmArgs& g)
+{
+    const int64_t blocks = (g.M * g.N + 63) / 64;
+    const int pb = persistent_blocks(256);
+    return blocks > pb ? pb : blocks;
+}
+
+static int check_gemm(GemmArgs& g, int splits)
+{
+    if (gemm_tiles(g, splits) > 2147483647 || splits > 65535)
+        return arg_error("gemm: grid too large");
     if (splits > 1 && !g.partial) return arg_error("gemm: split-K needs a partial buffer");
     if (splits > 1 && g.asum_out && !g.asum_part)
         return arg_error("gemm: split-K row sums need a partial buffer");
     if (splits == 1) g.partial = nullptr;
     g.ksplits = splits;
-    dim3 grid((unsigned)tiles, 1u, 1u);
-    k_gemm_bf16<<<grid, G_THREADS, 0, s>>>(g);
+    return DSMC_OK;
+}
+
+int gemm_bf16(const GemmArgs& g0, int splits, hipStream_t s)
+{
+    GemmArgs g = g0;
+    if (g.M <= 0 || g.N <= 0) return DSMC_OK;
+    if (splits < 1) splits = 1;
+    const int rc = check_gemm(g, splits);
+    if (rc) return rc;
+    k_gemm_bf16<<<(unsigned)gemm_tiles(g, splits), G_THREADS, 0, s>>>(g);
     DSMC_LAUNCH_CHECK("gemm_bf16");
     if (splits > 1) {
-        const int64_t total = g.M * g.N;
-        int64_t blocks = (total + 63) / 64;
-        const int pb = persistent_blocks(256);
-        if (blocks > pb) blocks = pb;
-        k_gemm_reduce<<<(int)blocks, 256, 0, s>>>(g, splits);
+        k_gemm_reduce<<<(int)reduce_blocks(g), 256, 0, s>>>(g, splits);
         DSMC_LAUNCH_CHECK("gemm_reduce");
+    }
+    return DSMC_OK;
+}
+
+int gemm_group_bf16(const GemmArgs* gs, int n, int splits, hipStream_t s)
+{
+    if (n < 1 || n > GEMM_GROUP_MAX) return arg_error("gemm_group: %d products", n);
+    if (splits < 1) splits = 1;
+    GemmGroup q{};
+    int64_t tiles = 0, red = 0;
+    for (int p = 0; p < n; ++p) {
+        GemmArgs& g = q.g[p];
+        g = gs[p];
+        if (g.M <= 0 || g.N <= 0) return arg_error("gemm_group: empty product");
+        const int rc = check_gemm(g, splits);
+        if (rc) return rc;
+        tiles += gemm_tiles(g, splits);
+        red += reduce_blocks(g);
+        if (tiles > 2147483647) return arg_error("gemm: grid too large");
+        q.first[p + 1] = (int32_t)tiles;
+        q.rfirst[p + 1] = (int32_t)red;
+    }
+    q.n = n;
+    q.splits = splits;
+    k_gemm_group<<<(unsigned)tiles, G_THREADS, 0, s>>>(q);
+    DSMC_LAUNCH_CHECK("gemm_group");
+    if (splits > 1) {
+        k_gemm_group_reduce<<<(unsigned)red, 256, 0, s>>>(q);
+        DSMC_LAUNCH_CHECK("gemm_group_reduce");
     }
     return DSMC_OK;
 }

@@ -51,6 +51,11 @@ struct GemmArgs {
 // summed in a fixed order).
 int gemm_bf16(const GemmArgs& g, int splits, hipStream_t s);
 
+// n products (none empty) in one launch, their split sums in a second; the
+// same results as one by one.
+constexpr int GEMM_GROUP_MAX = 6;
+int gemm_group_bf16(const GemmArgs* g, int n, int splits, hipStream_t s);
+
 // Column sums of a[R][n] (FP32) in a fixed order: out[c] = sum_r a[r][c]
 // (+= when accumulate); with x2 != null also out2[2c + q] = sum_r a[r][c] x2[r][q].
 // red: colsum_ws_floats(R, n) floats of workspace.

@@ -1054,55 +1054,227 @@ static int backward_impl(const MlpDev& d, int64_t B, const T* X, const T* Z, con
 // db) and bf16 (the GEMM operand); h_{l-1} is the bf16 activation the forward
 // used.
 struct Bf16BwdWs {
-    __bf16* dt[2];  // delta^T, row-blocked (ping-pong): k-contiguous A of the weight-gradient GEMM
-    float* part;
-    float* apart;   // per-split row sums of delta^T (bias gradient)
+    __bf16* dt[MLP_MAX_LAYERS];   // delta_l^T, row-blocked: k-contiguous A of the weight-gradient GEMM
+    float* part[MLP_MAX_LAYERS];
+    float* apart[MLP_MAX_LAYERS]; // per-split row sums of delta^T (bias gradient)
     size_t bytes;
 };
 
 constexpr int BWD_SPLITS_MAX = 256;
 
+static int bwd_splits(int64_t B)
+{
+    const int64_t n = B / 256;
+    return (int)(n < 1 ? 1 : (n > BWD_SPLITS_MAX ? BWD_SPLITS_MAX : n));
+}
+
 static Bf16BwdWs bf16_bwd_layout(void* base, const MlpDev& d, int64_t B)
 {
-    int wmax = 8;
-    for (int l = 0; l <= d.L; ++l) wmax = wmax > d.dims[l] ? wmax : d.dims[l];
     Bf16BwdWs w{};
     uint8_t* p = static_cast<uint8_t*>(base);
     size_t o = 0;
     auto take = [&](size_t b) { uint8_t* r = p ? p + o : nullptr; o += align_up(b); return r; };
     const size_t Bp = (size_t)(row_blocks(B) * GEMM_RB);
-    for (int q = 0; q < 2; ++q)
-        w.dt[q] = reinterpret_cast<__bf16*>(take(sizeof(__bf16) * Bp * wmax));
-    w.part = reinterpret_cast<float*>(take(sizeof(float) * BWD_SPLITS_MAX * (size_t)wmax * wmax));
-    w.apart = reinterpret_cast<float*>(take(sizeof(float) * BWD_SPLITS_MAX * (size_t)wmax));
+    for (int l = 0; l < d.L; ++l) {
+        const size_t out = d.dims[l + 1], in = d.dims[l];
+        w.dt[l] = reinterpret_cast<__bf16*>(take(sizeof(__bf16) * Bp * out));
+        w.part[l] = reinterpret_cast<float*>(take(sizeof(float) * bwd_splits(B) * out * in));
+        w.apart[l] = reinterpret_cast<float*>(take(sizeof(float) * bwd_splits(B) * out));
+    }
     w.bytes = o;
     return w;
 }
 
-// Projection backward of the bf16 rows form, written as delta^T of the output
-// layer in bf16 (row-blocked, three units): the same arithmetic as
-// k_project_backward.
+// Projection backward of the bf16 rows form: delta of the output layer, the
+// same arithmetic as k_project_backward.
+__device__ __forceinline__ void project_row_backward(const float* Y, const float* g,
+                                                     const float* G, int64_t r, float (&o)[3])
+{
+    const float y0 = Y[r * 3], y1 = Y[r * 3 + 1], y2 = Y[r * 3 + 2];
+    const float n = dev_sqrt<float>(y0 * y0 + y1 * y1 + y2 * y2);
+    o[0] = o[1] = o[2] = 0.f;
+    if (n > 1e-30f) {
+        const float u0 = y0 / n, u1 = y1 / n, u2 = y2 / n;
+        const float G0 = G[3 * r], G1 = G[3 * r + 1], G2 = G[3 * r + 2];
+        const float Gu = G0 * u0 + G1 * u1 + G2 * u2;
+        const float f = g[r] / n;
+        o[0] = f * (G0 - Gu * u0);
+        o[1] = f * (G1 - Gu * u1);
+        o[2] = f * (G2 - Gu * u2);
+    }
+}
+
+// Written as delta^T in bf16 (row-blocked, three units).
 __global__ void __launch_bounds__(256)
 k_project_backward_t16(int64_t B, const float* __restrict__ Y, const float* __restrict__ g,
                        const float* __restrict__ G, __bf16* __restrict__ dt)
 {
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < B;
          r += (int64_t)gridDim.x * blockDim.x) {
-        const float y0 = Y[r * 3], y1 = Y[r * 3 + 1], y2 = Y[r * 3 + 2];
-        const float n = dev_sqrt<float>(y0 * y0 + y1 * y1 + y2 * y2);
-        float o[3] = {0.f, 0.f, 0.f};
-        if (n > 1e-30f) {
-            const float u0 = y0 / n, u1 = y1 / n, u2 = y2 / n;
-            const float G0 = G[3 * r], G1 = G[3 * r + 1], G2 = G[3 * r + 2];
-            const float Gu = G0 * u0 + G1 * u1 + G2 * u2;
-            const float f = g[r] / n;
-            o[0] = f * (G0 - Gu * u0);
-            o[1] = f * (G1 - Gu * u1);
-            o[2] = f * (G2 - Gu * u2);
-        }
+        float o[3];
+        project_row_backward(Y, g, G, r, o);
 #pragma unroll
         for (int c = 0; c < 3; ++c) dt[gemm_off(c, r, 0, 3 * GEMM_RB)] = (__bf16)o[c];
     }
+}
+
+// All deltas in one kernel, for hidden layers of equal width H: a wave takes
+// 32 rows from the output layer down, delta^T in the MFMA result layout (lane
+// = row, registers = units).  W^T sits in LDS in fragment order, as the
+// forward's W does.  Two exchanges between the lane halves per 16 units put
+// delta's bf16 values where the next layer's B operand has them in the tiled
+// GEMM (k = 8 half + e), so every sum is the GEMM's, bit for bit.  Each layer
+// reads z^T and writes delta^T once (row-blocked, a lane's row, so 128- and
+// 64-byte runs); the next layer's z is loaded before this layer's MFMAs.
+// Bound by those bytes: 65 536 rows of four 128-unit layers move 0.2 GB in
+// 55 us (40 us at the rate of a copy); the four tiled products and the five
+// of the weight gradients, one launch each, took 276 us.
+struct ChainArgs {
+    int L;
+    const __bf16* W[MLP_MAX_LAYERS];   // layers 1 .. L-1
+    const float *Y, *g, *G;
+    const float* z[MLP_MAX_LAYERS];    // z^T of hidden layer l (output of layer l)
+    __bf16* dt[MLP_MAX_LAYERS];
+    int64_t B;
+};
+
+static size_t chain_lds(int L, int H)
+{
+    return sizeof(__bf16) * ((size_t)(L - 2) * H * H + (size_t)H * 16);
+}
+
+template <int ACT>
+__device__ __forceinline__ float act_slope(float z)
+{
+    if (ACT == DSMC_ACT_RELU) return z > 0.0f ? 1.0f : 0.0f;
+    const float s = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
+    return s * (1.0f + z * (1.0f - s));
+}
+
+template <int H, int ACT>
+__global__ void __launch_bounds__(512)
+k_mlp_chain(ChainArgs c)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __bf16* wl = reinterpret_cast<__bf16*>(smem);
+    constexpr int NB = H / 32, KS = H / 16, FR = NB * KS;
+    const int lane = threadIdx.x & 63, h = lane >> 5, col = lane & 31;
+    const int waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int L = c.L;
+    // fragment (u, ks) of W_l^T: lane l has k = 16 ks + 8 (l / 32) + e of unit
+    // 32 u + l % 32; the output layer's first (k < 3), then layers 1 .. L-2
+    for (int f = wave; f < NB + (L - 2) * FR; f += waves) {
+        bf16x8 v;
+        if (f < NB) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                v[e] = (h == 0 && e < 3) ? c.W[L - 1][e * H + f * 32 + col] : (__bf16)0.0f;
+        } else {
+            const int l = 1 + (f - NB) / FR, r = (f - NB) % FR, u = r / KS, ks = r % KS;
+            const __bf16* p = c.W[l] + (size_t)(16 * ks + 8 * h) * H + 32 * u + col;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = p[(size_t)e * H];
+        }
+        *reinterpret_cast<bf16x8*>(wl + (size_t)f * 512 + lane * 8) = v;
+    }
+    __syncthreads();
+
+    const floatx16 zero = {};
+    // tiles to the workgroups in turn, so that few of them have a CU each
+    const int64_t tiles = (c.B + 31) / 32;
+    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < tiles;
+         tile += (int64_t)gridDim.x * waves) {
+        const int64_t row = tile * 32 + col;
+        const bool valid = row < c.B;
+        const int64_t blk = row / GEMM_RB, in = row % GEMM_RB;
+        const size_t zbase = (size_t)blk * H * GEMM_RB + in + (size_t)4 * h * GEMM_RB;
+        float z[NB][16];
+        auto load_z = [&](int l) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    z[u][r] = valid ? c.z[l][zbase + (size_t)(32 * u + 8 * (r >> 2) + (r & 3)) * GEMM_RB]
+                                    : 0.0f;
+        };
+        load_z(L - 2);
+        float o[3] = {0.f, 0.f, 0.f};
+        if (valid) project_row_backward(c.Y, c.g, c.G, row, o);
+        bf16x8 ob;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ob[e] = (__bf16)((h == 0 && e < 3) ? o[e < 3 ? e : 0] : 0.0f);
+        if (valid && h == 0) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                c.dt[L - 1][(size_t)blk * 3 * GEMM_RB + (size_t)e * GEMM_RB + in] = ob[e];
+        }
+        floatx16 acc[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+            acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(wl, 0, u, lane), ob, zero, 0,
+                                                             0, 0);
+        for (int l = L - 2; l >= 0; --l) {
+            bf16x8 b[KS];
+            __bf16* dt = c.dt[l];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                uint32_t pk[8];   // units 8 (q / 2) + 4 half + 2 (q & 1), two each
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    bf16x2 t;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int r = 2 * q + e;
+                        t[e] = (__bf16)(acc[u][r] * act_slope<ACT>(z[u][r]));
+                        if (valid)
+                            dt[zbase + (size_t)(32 * u + 8 * (r >> 2) + (r & 3)) * GEMM_RB] = t[e];
+                    }
+                    pk[q] = __builtin_bit_cast(uint32_t, t);
+                }
+                // half 0 has units 0-3, 8-11 of each 16 and half 1 the others
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    uint32_t w[4];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const auto x = __builtin_amdgcn_permlane32_swap(pk[4 * s + e],
+                                                                        pk[4 * s + 2 + e], false,
+                                                                        false);
+                        w[e] = x[0];
+                        w[2 + e] = x[1];
+                    }
+                    b[2 * u + s] = __builtin_bit_cast(bf16x8, w);
+                }
+            }
+            if (l == 0) break;
+            load_z(l - 1);
+            const int off = (NB + (l - 1) * FR) * 512;
+#pragma unroll
+            for (int u = 0; u < NB; ++u) acc[u] = zero;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int u = 0; u < NB; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        lds_frag(wl, off, u * KS + ks, lane), b[ks], acc[u], 0, 0, 0);
+        }
+    }
+}
+
+template <int H, int ACT>
+static int launch_chain(const ChainArgs& c, hipStream_t s)
+{
+    const size_t lds = chain_lds(c.L, H);
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)k_mlp_chain<H, ACT>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_check(e, "mlp_bwd16: set LDS attribute");
+    const int64_t tiles = (c.B + 31) / 32;
+    const int cus = device_cus();
+    k_mlp_chain<H, ACT><<<(int)(tiles < cus ? tiles : cus), 512, lds, s>>>(c);
+    DSMC_LAUNCH_CHECK("mlp_bwd16:chain");
+    return DSMC_OK;
 }
 
 // Backward of the bf16 rows form.  Everything runs on transposed ([unit][row])
@@ -1112,8 +1284,12 @@ k_project_backward_t16(int64_t B, const float* __restrict__ Y, const float* __re
 // is needed:
 //   dW_l = delta_l^T h_{l-1}     (h^T and x^T from the forward's act_save)
 //   db_l = row sums of delta_l^T (summed by the same GEMM from its A tiles)
-//   delta_{l-1}^T = (W_l^T delta_l^T) * act'(z_{l-1}^T)   (a GEMM with
-//   M = units, N = batch, whose epilogue reads z^T and writes delta^T)
+//   delta_{l-1}^T = (W_l^T delta_l^T) * act'(z_{l-1}^T)   (k_mlp_chain, or a
+//   GEMM with M = units, N = batch, whose epilogue reads z^T and writes
+//   delta^T, per layer)
+// The weight gradients of all layers go in one launch (256 splits of 256 rows
+// alone leave a tile per CU), their split sums in a second: 67 and 18 us at
+// 65 536 rows; one by one the sums alone took 57 us.
 static int backward_bf16(const MlpDev& d, int64_t B, const float* X, const float* Z,
                          const float* Y, const float* g, const float* G, float* const* dW,
                          float* const* db, float* dx, int accumulate, void* ws, hipStream_t s)
@@ -1124,8 +1300,7 @@ static int backward_bf16(const MlpDev& d, int64_t B, const float* X, const float
         int64_t b = (n + 255) / 256;
         return (int)(b < 1 ? 1 : (b > pb ? pb : b));
     };
-    int splits = (int)(B / 256);
-    splits = splits < 1 ? 1 : (splits > BWD_SPLITS_MAX ? BWD_SPLITS_MAX : splits);
+    const int splits = bwd_splits(B);
     const int64_t Bp = row_blocks(B) * GEMM_RB;
     int64_t zoff[MLP_MAX_LAYERS] = {0};
     for (int l = 1; l < d.L; ++l) zoff[l] = zoff[l - 1] + Bp * d.dims[l];
@@ -1134,40 +1309,36 @@ static int backward_bf16(const MlpDev& d, int64_t B, const float* X, const float
     const __bf16* Hs = reinterpret_cast<const __bf16*>(zb + hoff);
     const __bf16* Xs = reinterpret_cast<const __bf16*>(
         zb + hoff + align_up(sizeof(__bf16) * (size_t)zoff[d.L - 1]));
-    int cur = 0;
-    k_project_backward_t16<<<grid1(B), 256, 0, s>>>(B, Y, g, G, w.dt[cur]);
-    DSMC_LAUNCH_CHECK("mlp_bwd16:project");
-    const int gact = d.act == DSMC_ACT_RELU ? GEMM_ACT_RELU : GEMM_ACT_SILU;
-    for (int l = d.L - 1; l >= 0; --l) {
-        const int out = d.dims[l + 1], in = d.dims[l];
-        const __bf16* hT = (l > 0) ? Hs + zoff[l - 1] : Xs;   // saved by the forward
-        GemmArgs gw{};
-        gw.a = w.dt[cur];
-        gw.lda = GEMM_RB;
-        gw.bsa = (int64_t)out * GEMM_RB;
-        gw.ta = 0;
-        gw.b = hT;
-        gw.ldb = GEMM_RB;
-        gw.bsb = (int64_t)in * GEMM_RB;
-        gw.tb = 1;
-        gw.M = out;
-        gw.N = in;
-        gw.K = B;
-        gw.act = GEMM_ACT_NONE;
-        gw.accumulate = accumulate;
-        gw.out_f32 = dW[l];
-        gw.ldo = in;
-        gw.partial = w.part;
-        gw.asum_out = db[l];       // db_l = row sums of delta_l^T, the A operand
-        gw.asum_part = w.apart;
-        int rc = gemm_bf16(gw, splits, s);
+    int H = 0;
+    if (mfma_shape_ok(d, &H) && H <= 128 && chain_lds(d.L, H) <= MLP_LDS_BYTES) {
+        // (width 256: W^T of one layer alone fills most of the LDS)
+        ChainArgs c{};
+        c.L = d.L;
+        for (int l = 1; l < d.L; ++l) {
+            c.W[l] = static_cast<const __bf16*>(d.W[l]);
+            c.z[l - 1] = Z + zoff[l - 1];
+        }
+        for (int l = 0; l < d.L; ++l) c.dt[l] = w.dt[l];
+        c.Y = Y;
+        c.g = g;
+        c.G = G;
+        c.B = B;
+        const bool relu = d.act == DSMC_ACT_RELU;
+        const int rc = H == 128 ? (relu ? launch_chain<128, DSMC_ACT_RELU>(c, s)
+                                        : launch_chain<128, DSMC_ACT_SILU>(c, s))
+                                : (relu ? launch_chain<64, DSMC_ACT_RELU>(c, s)
+                                        : launch_chain<64, DSMC_ACT_SILU>(c, s));
         if (rc) return rc;
-        if (l > 0) {
+    } else {
+        k_project_backward_t16<<<grid1(B), 256, 0, s>>>(B, Y, g, G, w.dt[d.L - 1]);
+        DSMC_LAUNCH_CHECK("mlp_bwd16:project");
+        for (int l = d.L - 1; l > 0; --l) {
+            const int out = d.dims[l + 1], in = d.dims[l];
             GemmArgs gd{};
             gd.a = static_cast<const __bf16*>(d.W[l]);   // A(m = unit of l-1, k) = W[k][m]
             gd.lda = in;
             gd.ta = 1;
-            gd.b = w.dt[cur];                             // B(k, n = row) = delta^T[k][n]
+            gd.b = w.dt[l];                               // B(k, n = row) = delta^T[k][n]
             gd.ldb = GEMM_RB;
             gd.bsb = (int64_t)out * GEMM_RB;
             gd.tb = 0;
@@ -1177,33 +1348,55 @@ static int backward_bf16(const MlpDev& d, int64_t B, const float* X, const float
             gd.dact_z = Z + zoff[l - 1];                  // z^T, row-blocked
             gd.ldz = GEMM_RB;
             gd.bsz = (int64_t)in * GEMM_RB;
-            gd.act = gact;
-            gd.out_bf16 = w.dt[1 - cur];
+            gd.act = d.act == DSMC_ACT_RELU ? GEMM_ACT_RELU : GEMM_ACT_SILU;
+            gd.out_bf16 = w.dt[l - 1];
             gd.ldo = GEMM_RB;
             gd.bso = (int64_t)in * GEMM_RB;
-            rc = gemm_bf16(gd, 1, s);
-            if (rc) return rc;
-            cur = 1 - cur;
-        } else if (dx) {
-            GemmArgs gd{};
-            gd.a = w.dt[cur];                             // A(m = row, k) = delta^T[k][m]
-            gd.lda = GEMM_RB;
-            gd.bsa = (int64_t)out * GEMM_RB;
-            gd.ta = 1;
-            gd.b = static_cast<const __bf16*>(d.W[0]);   // B(k, n) = W[k][n]
-            gd.ldb = in;
-            gd.tb = 0;
-            gd.M = B;
-            gd.N = in;
-            gd.K = out;
-            gd.act = GEMM_ACT_NONE;
-            gd.out_f32 = dx;
-            gd.ldo = in;
-            rc = gemm_bf16(gd, 1, s);
+            const int rc = gemm_bf16(gd, 1, s);
             if (rc) return rc;
         }
     }
-    return DSMC_OK;
+    GemmArgs gw[MLP_MAX_LAYERS] = {};
+    static_assert(MLP_MAX_LAYERS <= GEMM_GROUP_MAX, "one group for all layers");
+    for (int l = 0; l < d.L; ++l) {
+        const int out = d.dims[l + 1], in = d.dims[l];
+        GemmArgs& q = gw[l];
+        q.a = w.dt[l];
+        q.lda = GEMM_RB;
+        q.bsa = (int64_t)out * GEMM_RB;
+        q.ta = 0;
+        q.b = l > 0 ? Hs + zoff[l - 1] : Xs;   // saved by the forward
+        q.ldb = GEMM_RB;
+        q.bsb = (int64_t)in * GEMM_RB;
+        q.tb = 1;
+        q.M = out;
+        q.N = in;
+        q.K = B;
+        q.act = GEMM_ACT_NONE;
+        q.accumulate = accumulate;
+        q.out_f32 = dW[l];
+        q.ldo = in;
+        q.partial = w.part[l];
+        q.asum_out = db[l];       // db_l = row sums of delta_l^T, the A operand
+        q.asum_part = w.apart[l];
+    }
+    int rc = gemm_group_bf16(gw, d.L, splits, s);
+    if (rc || !dx) return rc;
+    GemmArgs gd{};
+    gd.a = w.dt[0];                               // A(m = row, k) = delta^T[k][m]
+    gd.lda = GEMM_RB;
+    gd.bsa = (int64_t)d.dims[1] * GEMM_RB;
+    gd.ta = 1;
+    gd.b = static_cast<const __bf16*>(d.W[0]);   // B(k, n) = W[k][n]
+    gd.ldb = d.dims[0];
+    gd.tb = 0;
+    gd.M = B;
+    gd.N = d.dims[0];
+    gd.K = d.dims[1];
+    gd.act = GEMM_ACT_NONE;
+    gd.out_f32 = dx;
+    gd.ldo = d.dims[0];
+    return gemm_bf16(gd, 1, s);
 }
 
 static size_t backward_ws_bytes(const MlpDev& d, int64_t B, size_t es)

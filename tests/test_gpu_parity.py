@@ -830,6 +830,40 @@ def test_neural_rows_tiles_and_alignment_bitwise(dev, api, dims):
                 assert torch.equal(vr2, vr[:rows]), rows
 
 
+@pytest.mark.parametrize("act", ["silu", "relu"])
+@pytest.mark.parametrize("dims,wide", [((8, 128, 3), 256), ((8, 64, 3), 256),
+                                       ((8, 64, 64, 64, 3), 128)])
+@pytest.mark.parametrize("rows", [1, 33, 300, 8_193, 66_000])
+def test_neural_backward_paths_agree_bitwise(dev, api, dims, wide, rows, act):
+    """Hidden layers widened by units without weights: width 256 takes the
+    tiled products for its deltas, 64 and 128 the one kernel.  Only zeros are
+    added, so the gradients are the same bit for bit."""
+    say("neural backward paths", dims, wide, rows, act)
+    Ws, bs = _net_params(17, dims)
+    Ww, bw = [], []
+    for q, (w, b) in enumerate(zip(Ws, bs)):
+        o = wide if q + 2 < len(dims) else dims[-1]
+        W2, b2 = np.zeros((o, wide if q else dims[0])), np.zeros(o)
+        W2[:w.shape[0], :w.shape[1]], b2[:len(b)] = w, b
+        Ww.append(W2)
+        bw.append(b2)
+    g = torch.Generator().manual_seed(rows)
+    x, sp, dvr = (torch.randn(rows, n, generator=g).to(dev) for n in (dims[0], 1, 3))
+    out = []
+    for net in (api.Net(Ws, bs, act=act, device=dev), api.Net(Ww, bw, act=act, device=dev)):
+        save = api.workspace(api.neural_act_bytes(net, rows), dev)
+        y, _ = api.neural_forward_rows(net, x, sp, act_save=save)
+        dW = [torch.full(w.shape, float("nan"), device=dev) for w in net.W]
+        db = [torch.full(b.shape, float("nan"), device=dev) for b in net.b]
+        dx = torch.empty_like(x)
+        api.neural_backward(net, x, save, y, sp, dvr, dW, db, dx=dx)
+        out.append((y, dx, dW, db))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    for l, (w, b) in enumerate(zip(out[0][2], out[0][3])):
+        assert torch.equal(w, out[1][2][l][:w.shape[0], :w.shape[1]]), l
+        assert torch.equal(b, out[1][3][l][:b.shape[0]]), l
+
+
 def test_backward_fp64_against_oracle(orc, dev, api):
     say("backward fp64")
     rows = W.training_rows(seed=7, n=700)
