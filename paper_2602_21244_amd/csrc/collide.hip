@@ -407,6 +407,41 @@ __device__ __forceinline__ void cell_rounds(const PairsView& pr, V3<T> v, const 
     if (WB) unstage_cell(v, lo, span, L);
 }
 
+// One cell of at most 64 pairs by a single wave, a pair per lane: stage, then
+// apply a round's pairs from the registers as soon as the search has found
+// them (they share no particle and come after every pair they depend on).  A
+// round costs one pass of the update whether its pairs are packed or not, so
+// the buckets are left out: 40 000 cells of 12 pairs with matching, FP64:
+// 93 us against 129 us.
+template <typename T, int RULE, int NMAX, int PPL, int RMAX>
+__device__ __forceinline__ void cell_direct(V3<T> v, const PairBuf<T>& d, int32_t c, int64_t o,
+                                            int32_t lo, int32_t span, int32_t pa, int32_t pb,
+                                            const CellLds<T, RULE, 64, PPL, NMAX, RMAX>& L)
+{
+    const int t = threadIdx.x;
+    Payload<T, RULE> pl;
+    bool pend = t < c;
+    if (pend) pl.load(d, o + t);
+    stage_cell(v, lo, span, L);
+    for (int32_t q = t; q < span; q += 64) L.first[q] = INT32_MAX;
+    const int32_t a = pa - lo, b = pb - lo;
+    int32_t key = (ROUND_MAX << 16) | t;
+    __syncthreads();
+    while (__ballot(pend) != 0) {
+        if (pend) {
+            atomicMin(&L.first[a], key);
+            atomicMin(&L.first[b], key);
+        }
+        __syncthreads();
+        if (pend && L.first[a] == key && L.first[b] == key) {
+            apply_pair_lds<T, RULE>(L.lx, L.ly, L.lz, a, b, pl);
+            pend = false;
+        }
+        __syncthreads();
+        key -= 1 << 16;
+    }
+}
+
 // Min / max of the cell's pair slots over the workgroup.
 template <int NT>
 __device__ __forceinline__ void group_minmax(int32_t& lo, int32_t& hi, int32_t* red)
@@ -562,6 +597,11 @@ k_phaseB_wave(int32_t n_cells, PairsView pr, V3<T> v, PairBuf<T> d, int32_t min_
             if (lane == 0) list_cell<T>(list, (int32_t)k, cc, span);
             continue;
         }
+        if (cc <= 64) {
+            cell_direct(v, d, cc, o, lo, span, pa[0], pb[0], L);
+            unstage_cell(v, lo, span, L);
+            continue;
+        }
 #pragma unroll
         for (int m = 0; m < WV_PPL; ++m)
             if (lane + 64 * m >= cc) { pa[m] = lo; pb[m] = lo; }
@@ -711,14 +751,22 @@ struct MatchArgs {
     dsmc_status* st;
 };
 
+// A cell's captured mean velocity and the sum to restore (loaded first, their
+// latency overlaps the sums).
+struct MatchGoal {
+    double u0, u1, u2, t;
+    __device__ __forceinline__ MatchGoal(const double* m, int literal)
+        : u0(m[0]), u1(m[1]), u2(m[2]), t(literal ? m[5] : m[3])
+    {
+    }
+};
+
 template <typename T, typename LD>
-__device__ __forceinline__ void match_cell(LD ld, int32_t N, const double* m, int literal,
+__device__ __forceinline__ void match_cell(LD ld, int32_t N, const MatchGoal& m, int literal,
                                            V3<T> v, int32_t s0, dsmc_status* st)
 {
     const int lane = threadIdx.x & 63;
-    // the cell's captured moments are loaded first, their latency overlaps
-    // the sums
-    const double m0 = m[0], m1 = m[1], m2 = m[2], mt = literal ? m[5] : m[3];
+    const double m0 = m.u0, m1 = m.u1, m2 = m.u2, mt = m.t;
     double sx = 0, sy = 0, sz = 0;
     for (int32_t q = lane; q < N; q += 64) {
         sx += (double)ld.x(q);
@@ -813,10 +861,13 @@ k_phaseB_match_wave(int32_t n_cells, PairsView pr, V3<T> v, PairBuf<T> d, MatchA
                 pb[m] = pr.j[o + q];
             }
         }
-        cell_rounds<T, RULE, 64, WV_PPL, WV_NMAX, WV_RMAX, false>(pr, v, d, cc, o, b0, N, pa, pb,
-                                                                  L);
-        match_cell<T>(CellView<T>{L.lx, L.ly, L.lz}, N, ma.mom + 6 * (size_t)k, ma.literal, v, b0,
-                      ma.st);
+        if (cc <= 64)
+            cell_direct(v, d, cc, o, b0, N, pa[0], pb[0], L);
+        else
+            cell_rounds<T, RULE, 64, WV_PPL, WV_NMAX, WV_RMAX, false>(pr, v, d, cc, o, b0, N, pa,
+                                                                      pb, L);
+        const MatchGoal goal(ma.mom + 6 * (size_t)k, ma.literal);
+        match_cell<T>(CellView<T>{L.lx, L.ly, L.lz}, N, goal, ma.literal, v, b0, ma.st);
         __syncthreads();
     }
 }
@@ -837,7 +888,7 @@ k_phaseB_match_block(int32_t n_cells, PairsView pr, V3<T> v, PairBuf<T> d, Match
         const int32_t b0 = ma.cell_start[k], N = ma.cell_start[k + 1] - b0;
         const bool in_lds = block_cell<T, RULE, BIG, false>(pr, v, d, c, o, b0, N, smem);
         if (threadIdx.x < 64) {
-            const double* m = ma.mom + 6 * (size_t)k;
+            const MatchGoal m(ma.mom + 6 * (size_t)k, ma.literal);
             if (in_lds) {
                 const BlockLds<T, RULE, BIG> L(smem);
                 match_cell<T>(CellView<T>{L.lx, L.ly, L.lz}, N, m, ma.literal, v, b0, ma.st);
@@ -862,14 +913,14 @@ int phase_b(int rule, int dtype, int32_t n_cells, const int32_t* cell_start, dsm
     lb = lb < 1 ? 1 : (lb > pb ? pb : lb);
     // cells with at most `thr` pairs: LANE; larger: WAVE when they fit its
     // LDS tables (AUTO, WAVE), else BLOCK.  A lane takes about 1.8 us per pair
-    // of its cell, one after the other; a wave 9 to 12 us for up to 16 of
+    // of its cell, one after the other; a wave 9 to 11 us for up to 48 of
     // them, and they queue up from some 4 000 cells on.  LANE against WAVE,
-    // FP64: 200 cells of 4 / 16 / 48 pairs 8 / 29 / 85 us against 11 / 12 /
-    // 16 us; 300 000 cells of 8 / 16 / 48 pairs 0.49 / 1.06 / 3.4 ms against
-    // 0.69 / 0.81 / 1.2 ms.  So AUTO goes by lanes to LANE_MAX pairs at most,
+    // FP64: 200 cells of 4 / 16 / 48 pairs 8 / 29 / 84 us against 9 / 10 /
+    // 11 us; 300 000 cells of 8 / 16 / 48 pairs 0.48 / 1.06 / 3.4 ms against
+    // 0.57 / 0.63 / 0.82 ms.  So AUTO goes by lanes to LANE_MAX pairs at most,
     // and not at all while the wave kernel has a workgroup for every cell
-    // (10 000 cells of 4 pairs 26 us, of which the lanes alone would take 11
-    // and the launches after them 10).
+    // (10 000 cells of 4 pairs 20 us, of which the lanes alone would take 12
+    // and the launches after them 9).
     constexpr int32_t LANE_MAX = 8;
     int32_t thr = block_threshold();
     if (thr > LANE_MAX) thr = LANE_MAX;

@@ -365,6 +365,38 @@ def test_schedules_bit_identical(dev, api, case):
         assert np.array_equal(out[0], o)
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("N", [3, 40, 320])
+def test_wave_schedule_pair_counts(dev, api, dtype, N):
+    # a wave takes up to 64 pairs of a cell directly, more in buckets; few
+    # particles make every pair wait for the one before it
+    say("wave schedule", dtype, N)
+    cnt = torch.tensor([1, 2, 63, 64, 65, 0, 128, 256, 64, 1])
+    n_cells, g = len(cnt), torch.Generator().manual_seed(N)
+    off, cap = torch.cumsum(cnt, 0) - cnt, int(cnt.sum())
+    cell = torch.arange(n_cells).repeat_interleave(cnt)
+    i = torch.randint(0, N, (cap,), generator=g)
+    j = (i + torch.randint(1, N, (cap,), generator=g)) % N
+    pairs = api.PairList(n_cells, cap, dev)
+    pairs.off.copy_(off)
+    pairs.cnt.copy_(cnt)
+    pairs.i[:cap] = (cell * N + i).to(dev)
+    pairs.j[:cap] = (cell * N + j).to(dev)
+    pairs.cell[:cap] = cell.to(dev)
+    v = (300.0 * torch.randn(3, N * n_cells, generator=g, dtype=torch.float64)).to(dtype).to(dev)
+    cs = (N * torch.arange(n_cells + 1)).int().to(dev)
+    mom = torch.zeros(6 * n_cells, dtype=torch.float64, device=dev)
+    api.moment_match(cs, v, mom, api.L.MM_CAPTURE)
+    lane, wave, fused = v.clone(), v.clone(), v.clone()
+    api.collide_vhs(lane, pairs, 3, 9, schedule=api.L.SCHED_LANE)
+    api.collide_vhs(wave, pairs, 3, 9, schedule=api.L.SCHED_WAVE)
+    assert torch.equal(lane, wave)
+    ws = api.collide_vhs(fused, pairs, 3, 9, schedule=api.L.SCHED_DEFER)
+    api.apply_pairs_match(cs, fused, pairs, api.L.APPLY_DIRECTIONS, mom, ws)
+    api.moment_match(cs, lane, mom, api.L.MM_APPLY, pair_cnt=pairs.cnt)
+    assert torch.equal(lane, fused)
+
+
 @pytest.mark.parametrize("extra", [0, 1, 3000])
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 def test_auto_schedule_many_cells(dev, api, dtype, extra):
