@@ -229,7 +229,7 @@ __device__ __forceinline__ void count_root_fail(dsmc_status* st)
 //
 // What bounds it: VALU issue, two thirds of the cycles (7 000 instructions per
 // 64 pairs in FP64, half of them FP64 arithmetic), then the table reads (48
-// bytes per lane and node in FP64, 16 in FP32, at random rows).  2^20 pairs in FP64: 0.39 ms (2.2 ms with V
+// bytes per lane and node in FP64, 16 in FP32, at random rows).  2^20 pairs in FP64: 0.33 ms (2.2 ms with V
 // evaluated directly and a second pass for the flagged pairs, bound by the
 // FP64 VALU); Phase A of 3.5 million pairs in FP32: 0.70 ms (3.3 ms).
 // ------------------------------------------------------------------------
@@ -267,10 +267,15 @@ static void tab_args(const Pot& P, const QuadCfg& q, const GLRule& gl, TabArgs<T
 // LDS: FP64 coefficients, the rule, the list of items left for the workgroup
 // (from the front those to refine, from the back those whose range crosses
 // the branches' meeting point, with 1 / r_min), FP32 coefficients.
+// A wave takes a chunk of 64 items only while fewer than TAB_ITEMS -
+// TAB_THREADS are listed; each of the workgroup's waves may then still add 64.
+constexpr int TAB_ITEMS = 3 * TAB_THREADS / 2;
 struct TabList {
-    double b[TAB_THREADS], E[TAB_THREADS], w[TAB_THREADS];
-    int64_t i[TAB_THREADS];
-    int n, kinks;
+    double b[TAB_ITEMS], E[TAB_ITEMS], w[TAB_ITEMS];
+    int64_t i[TAB_ITEMS];
+    alignas(8) int n;
+    int kinks;
+    int next;      // the workgroup's next chunk
 };
 constexpr size_t TAB_GL = sizeof(double) * CT_N * CT_C;
 constexpr size_t TAB_LIST = TAB_GL + align_up(sizeof(GLRule));
@@ -279,6 +284,7 @@ template <typename T> constexpr size_t tab_lds()
 {
     return TAB_F32 + (sizeof(T) == 4 ? sizeof(float) * CT_N * CT_CF : 0);
 }
+static_assert(tab_lds<float>() <= 160 * 1024, "LDS of one CU");
 
 // Value of lane `src` (the same for the whole wave).
 __device__ __forceinline__ double lane_value(double x, int src)
@@ -437,55 +443,73 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
     TabList& list = *reinterpret_cast<TabList*>(smem + TAB_LIST);
     const TabPot t = tab_build<T>(a, smem);
     const GLRule& gl = tab_gl<T>(a, smem);
-    if (threadIdx.x == 0) list.n = list.kinks = 0;
+    if (threadIdx.x == 0) list.n = list.kinks = list.next = 0;
     __syncthreads();
     constexpr int WAVES = TAB_THREADS / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t lt = (1ull << lane) - 1;
-    // rounds of one chunk per wave of the grid: in a round, wave w of block b
-    // takes chunk w gridDim + b, moved on by a few blocks in each round so a
-    // wave does not meet the same part of a periodic input again
+    // Chunk q of the workgroup: rounds of WAVES chunks, gridDim apart, moved
+    // on by a few blocks in each round so a workgroup does not meet the same
+    // part of a periodic input again.  The waves take them in turn as they get
+    // free (the four of a SIMD are not served evenly) until the list may fill,
+    // then all work through the list: 2^20
+    // FP64 pairs 334 us, 391 us with a fixed chunk per wave and a barrier each.
     const int64_t per_round = (int64_t)gridDim.x * WAVES;
-    for (int64_t rd = 0; rd * per_round < chunks; ++rd) {
-        const int64_t blk = (blockIdx.x + 37 * rd) % gridDim.x;
-        const int64_t ch = rd * per_round + (int64_t)wave * gridDim.x + blk;
-        const int64_t i = ch * 64 + lane;
-        const bool active = i < n;
-        double b = 0.0, E = 1.0;
-        CtLane<T> c{T(0), false, 0.0};
-        if (active) {
-            job.inputs(i, b, E);
-            c = chi_tab_lane(t, a.q, gl, a.nd, b, E);
-        }
-        const bool pending = active && c.flag && a.q.refine;
-        const bool kink = active && !pending && c.kink_w > 0.0;
-        if (active && !pending && !kink) {
-            if (c.chi != c.chi) {
-                count_root_fail(st);
-                job.fail(i);
-            } else {
-                job.store(i, c.chi);
-            }
-        }
-        const uint64_t pend = __ballot(pending), kinks = __ballot(kink);
-        if (pend | kinks) {
-            int at = 0, ak = 0;
+    for (;;) {
+        for (;;) {
+            int q = -1;
             if (lane == 0) {
-                if (pend) at = atomicAdd(&list.n, (int)__popcll(pend));
-                if (kinks) ak = atomicAdd(&list.kinks, (int)__popcll(kinks));
+                // both counts in one read
+                const uint64_t nk = __hip_atomic_load(reinterpret_cast<uint64_t*>(&list.n),
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if ((int)(uint32_t)nk + (int)(nk >> 32) < TAB_ITEMS - TAB_THREADS)
+                    q = atomicAdd(&list.next, 1);
             }
-            at = __builtin_amdgcn_readfirstlane(at) + (int)__popcll(pend & lt);
-            ak = TAB_THREADS - 1 - (__builtin_amdgcn_readfirstlane(ak) + (int)__popcll(kinks & lt));
-            if (pending | kink) {
-                const int k = pending ? at : ak;
-                list.b[k] = b;
-                list.E[k] = E;
-                list.w[k] = c.kink_w;
-                list.i[k] = i;
+            q = __builtin_amdgcn_readfirstlane(q);
+            if (q < 0) break;
+            const int64_t rd = q / WAVES;
+            if (rd * per_round >= chunks) break;
+            const int64_t blk = (blockIdx.x + 37 * rd) % gridDim.x;
+            const int64_t ch = rd * per_round + (int64_t)(q % WAVES) * gridDim.x + blk;
+            const int64_t i = ch * 64 + lane;
+            const bool active = i < n;
+            double b = 0.0, E = 1.0;
+            CtLane<T> c{T(0), false, 0.0};
+            if (active) {
+                job.inputs(i, b, E);
+                c = chi_tab_lane(t, a.q, gl, a.nd, b, E);
+            }
+            const bool pending = active && c.flag && a.q.refine;
+            const bool kink = active && !pending && c.kink_w > 0.0;
+            if (active && !pending && !kink) {
+                if (c.chi != c.chi) {
+                    count_root_fail(st);
+                    job.fail(i);
+                } else {
+                    job.store(i, c.chi);
+                }
+            }
+            const uint64_t pend = __ballot(pending), kinks = __ballot(kink);
+            if (pend | kinks) {
+                int at = 0, ak = 0;
+                if (lane == 0) {
+                    if (pend) at = atomicAdd(&list.n, (int)__popcll(pend));
+                    if (kinks) ak = atomicAdd(&list.kinks, (int)__popcll(kinks));
+                }
+                at = __builtin_amdgcn_readfirstlane(at) + (int)__popcll(pend & lt);
+                ak = TAB_ITEMS - 1 - (__builtin_amdgcn_readfirstlane(ak) + (int)__popcll(kinks & lt));
+                if (pending | kink) {
+                    const int k = pending ? at : ak;
+                    list.b[k] = b;
+                    list.E[k] = E;
+                    list.w[k] = c.kink_w;
+                    list.i[k] = i;
+                }
             }
         }
         __syncthreads();
         const int pairs = list.n, nk = list.kinks;
+        const bool done = list.next / WAVES * per_round >= chunks;
         for (int k = wave; k < pairs; k += WAVES) {
             const double cr = ct_refine_wave(t, gl, list.b[k], list.E[k]);
             if (lane == 0) {
@@ -499,7 +523,7 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
         }
         // eight lanes per kinked pair
         for (int k = threadIdx.x >> 3; k < nk; k += TAB_THREADS / 8) {
-            const int e = TAB_THREADS - 1 - k;
+            const int e = TAB_ITEMS - 1 - k;
             const double w = list.w[e], beta = list.b[e] * w, iE = 1.0 / list.E[e];
             const double Vmin = ct_value<double>(t, w), tsw = sqrt(1.0 - t.s.w_sw / w);
             double I = 0.0;
@@ -518,6 +542,7 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
                 }
             }
         }
+        if (done) break;
         __syncthreads();
         if (threadIdx.x == 0) list.n = list.kinks = 0;
         // (the next append comes after each wave's lane rule; a barrier keeps

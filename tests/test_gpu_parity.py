@@ -620,6 +620,27 @@ def test_deflect_potential_table_edges(orc, dev, api, n, change, g_hi):
         check_chi(got[ok], ref[ok], kind, f"{n} {kind}")
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_deflect_many_refined_pairs_bitwise(dev, api, dtype):
+    """Orbiting pairs alone, 1 600 of them per CU of 256: each workgroup's list
+    of pairs to refine fills and is worked through several times.  A pair's
+    angle does not depend on its neighbours."""
+    say("deflect many refined", dtype)
+    b, g, mr = W.deflection_batch(seed=23, n=1 << 17)
+    pot = api.potential_jager(W.JAGER_PLACEHOLDER)
+    b, g = (torch.as_tensor(x, dtype=dtype, device=dev) for x in (b, g))
+    hard = api.deflect_jager(b, g, mr, pot).abs() > np.pi
+    b, g = b[hard].contiguous(), g[hard].contiguous()
+    n = int(b.numel())
+    assert n > 100
+    one = api.deflect_jager(b, g, mr, pot)
+    k = 409_600 // n + 1
+    st = api.new_status(dev)
+    many = api.deflect_jager(b.repeat(k), g.repeat(k), mr, pot, st=st)
+    assert api.read_status(st).root_fail == 0
+    assert torch.isfinite(one).all() and torch.equal(many, one.repeat(k))
+
+
 def test_deflect_refinement_off_is_worse(orc, dev, api):
     """With the FP64 refinement switched off every pair keeps the one-rule
     result: the orbiting pairs (sharp integrand peaks) then miss the bound the
