@@ -11,11 +11,22 @@
 // Intervals: CT_LR equal ones on [0, 1/r_sw] for the dispersion branch (w = 0
 // is r = infinity, V = 0), CT_SR on [1/r_sw, CT_SPAN/r_sw] for the screened
 // Coulomb branch, direct evaluation beyond.  Degree 5 through six Chebyshev
-// nodes in FP64: the interpolation error is below the rounding of V (1e-15 of
-// the two branches' magnitude for the argon set), so FP64 results keep their
-// error.  FP32 polynomials are the same ones cut to degree 3 (1e-9).  Set-up
-// compares a potential's table with the direct evaluation on the host, and
-// parameters that the intervals do not resolve keep the direct kernels.
+// nodes in FP64; FP32 polynomials are the same ones cut to degree 3.
+//
+// In the first intervals V ~ w^6 falls below the table's error, which is an
+// absolute one there (1e-16 K for the argon set), and the angle sees it divided
+// by E.  Pairs below an energy that this error sets (e_far: 0.12 K, 10 m/s, for
+// argon; one pair in 10^5 of a gas at 273 K) therefore take V at w < w_far from
+// the dispersion sum itself (ct_slow_lane, in FP64, and their refinement):
+// damping and repulsion are below rounding there, and the sum has V's relative
+// accuracy down to w = 0.  Their angles keep the direct rule's error (at 1 mm/s
+// and 100 nm 1e-16; 2e-8 by the table alone).  From e_far on the table's error,
+// some roundings of V's terms, shows where the integrand is peaked: 1.5e-14 RMS
+// at 10-30 m/s and 6e-15 at 600-5000 m/s against 4e-15 and 2e-15 (argon, pairs
+// that are not refined; in FP32 5e-7 against 9e-7).  Taking the sum at all
+// energies would cost the refinement 3 % of a batch's time.  Set-up measures
+// both errors against the direct evaluation on the host; parameters that the
+// intervals do not resolve keep the direct kernels.
 #pragma once
 
 #include "chi_quad.hpp"
@@ -26,6 +37,7 @@ constexpr int CT_LR = 1024, CT_SR = 256, CT_N = CT_LR + CT_SR;
 constexpr int CT_C = 6;             // FP64 coefficients per interval
 constexpr int CT_CF = 4;            // FP32 coefficients per interval
 constexpr double CT_SPAN = 4.0;     // the short-range intervals end at CT_SPAN / r_sw
+constexpr double CT_FAR = 0.125;    // w_far is at most CT_FAR / r_sw
 
 // Interpolation on [-1/2, 1/2]: nodes x and the matrix m that takes the values
 // at the nodes to the coefficients of 1, x, .., x^(CT_C - 1).  (About the
@@ -40,6 +52,7 @@ struct CtRule {
 // there (the smaller of the two lines, as inv_sr < inv_lr).
 struct CtScale {
     double w_sw, w_end, inv_lr, inv_sr, k_sr;
+    double w_far;   // no damping (x >= DAMP_OFF) below
 };
 
 CQ_HD CtScale ct_scale(const Pot& P)
@@ -50,6 +63,8 @@ CQ_HD CtScale ct_scale(const Pot& P)
     s.inv_lr = CT_LR * P.r_sw;
     s.inv_sr = CT_SR / ((CT_SPAN - 1.0) * s.w_sw);
     s.k_sr = CT_LR - s.w_sw * s.inv_sr;
+    const double wd = P.p.beta_tt / DAMP_OFF, wm = CT_FAR * s.w_sw;
+    s.w_far = wd < wm ? wd : wm;
     return s;
 }
 
@@ -150,10 +165,32 @@ template <typename T> CQ_HD int ct_index(const CtScale& s, T w, T& x)
     return i < CT_N - 1 ? i : CT_N - 1;
 }
 
-// V and (DERIV) dV/dw in FP64.
-template <bool DERIV>
+// V at w < w_far, -sum C_n w^n, with its first and second derivative in w: a
+// polynomial p in s = w^2 and its derivatives by Horner's scheme, V = -s^3 p.
+CQ_HD double ct_tail(const dsmc_potential& p, double w, double& dVw, double& d2Vw)
+{
+    const double s = w * w;
+    double v = 0.0, d = 0.0, e = 0.0;
+#pragma unroll
+    for (int k = 5; k >= 0; --k) {
+        e = fma(e, s, d);
+        d = fma(d, s, v);
+        v = fma(v, s, p.C[k]);
+    }
+    const double s2 = s * s, d1 = s2 * fma(s, d, 3.0 * v);   // -dV/ds
+    dVw = -2.0 * w * d1;
+    d2Vw = -2.0 * (d1 + 4.0 * s2 * fma(s, fma(s, e, 3.0 * d), 3.0 * v));
+    return -(s2 * s) * v;
+}
+
+// V and (DERIV) dV/dw in FP64; FAR: from the dispersion sum at w < w_far.
+template <bool DERIV, bool FAR = false>
 CQ_HD double ct_V(const TabPot& t, double w, double& dVw)
 {
+    if (FAR && w < t.s.w_far) {
+        double unused;
+        return ct_tail(t.P.p, w, dVw, unused);
+    }
     if (!(w <= t.s.w_end)) {
         const double V = ct_near(t.P, w);
         if (DERIV) dVw = V * (1.0 / w + t.P.p.a_sr / (w * w));
@@ -170,9 +207,10 @@ CQ_HD double ct_V(const TabPot& t, double w, double& dVw)
 }
 
 // V and (DERIV) dV/dw in FP32.
-template <bool DERIV>
+template <bool DERIV, bool FAR = false>
 CQ_HD float ct_V(const TabPot& t, float w, float& dVw)
 {
+    static_assert(!FAR, "slow pairs and the refinement are FP64");
     if (!(w <= float(t.s.w_end))) {
         const float V = float(t.P.p.A_sr) * w * expf(-float(t.P.p.a_sr) / w);
         if (DERIV) dVw = V * (1.0f / w + float(t.P.p.a_sr) / (w * w));
@@ -188,15 +226,17 @@ CQ_HD float ct_V(const TabPot& t, float w, float& dVw)
     return c0 + x * (c1 + x * (c2 + x * c3));
 }
 
-template <typename T> CQ_HD T ct_value(const TabPot& t, T w)
+template <typename T, bool FAR = false> CQ_HD T ct_value(const TabPot& t, T w)
 {
     T unused;
-    return ct_V<false>(t, w, unused);
+    return ct_V<false, FAR>(t, w, unused);
 }
 
 // V, dV/dw and d2V/dw2 in FP64.
+template <bool FAR>
 CQ_HD double ct_V2(const TabPot& t, double w, double& dVw, double& d2Vw)
 {
+    if (FAR && w < t.s.w_far) return ct_tail(t.P.p, w, dVw, d2Vw);
     if (!(w <= t.s.w_end)) {
         const double a = t.P.p.a_sr / w, V = ct_near(t.P, w);
         dVw = V * (1.0 + a) / w;
@@ -242,7 +282,7 @@ template <typename T> struct CtRoot {
 
 // Largest root of D = 1 - b^2 w^2 - V(w)/E (smallest w), as chi_lane finds
 // it, in w = 1/r.
-template <typename T>
+template <typename T, bool FAR = false>
 CQ_HD CtRoot<T> ct_root(const TabPot& t, const QuadCfg& q, T b, T E, bool low)
 {
     CtRoot<T> R;
@@ -253,7 +293,7 @@ CQ_HD CtRoot<T> ct_root(const TabPot& t, const QuadCfg& q, T b, T E, bool low)
     const T rz = T(t.P.r_zero);
     const T r_top = b > rz ? b : rz;
     T w1 = T(1) / r_top;
-    T f1 = T(1) - b2 * (w1 * w1) - ct_value<T>(t, w1) * iE;
+    T f1 = T(1) - b2 * (w1 * w1) - ct_value<T, FAR>(t, w1) * iE;
     if (f1 <= T(0)) {
         R.w = w1;
         R.flag = low;
@@ -266,7 +306,7 @@ CQ_HD CtRoot<T> ct_root(const TabPot& t, const QuadCfg& q, T b, T E, bool low)
     int it = 0;
     for (; it < 4000; ++it) {
         w2 = w1 * step;
-        f2 = T(1) - b2 * (w2 * w2) - ct_value<T>(t, w2) * iE;
+        f2 = T(1) - b2 * (w2 * w2) - ct_value<T, FAR>(t, w2) * iE;
         if (!(f2 > T(0)) || (f1 < f0 && f1 < f2) || w2 > T(1e4)) break;
         w0 = w1;
         f0 = low ? f1 : f0;
@@ -308,7 +348,7 @@ CQ_HD CtRoot<T> ct_root(const TabPot& t, const QuadCfg& q, T b, T E, bool low)
     T w = ws, fp = T(0);
     for (int it = 0; it < q.max_iter; ++it) {
         T dV = T(0);
-        const T V = ct_V<true>(t, w, dV);
+        const T V = ct_V<true, FAR>(t, w, dV);
         const T f = T(1) - b2 * (w * w) - V * iE;
         if (f > T(0)) wa = w; else wb = w;
         fp = -T(2) * b2 * w - dV * iE;
@@ -333,7 +373,7 @@ CQ_HD CtRoot<T> ct_root(const TabPot& t, const QuadCfg& q, T b, T E, bool low)
 
 // 2 t / sqrt(F) at t in (0, 1), F as in chi_quad.hpp with the potential
 // difference near r_min as the integral of dV/dw (2-point Gauss-Legendre).
-template <typename T>
+template <typename T, bool FAR = false>
 CQ_HD T ct_node(const TabPot& t, T w, T beta2, T Vmin, T iE, T tt, T& smax, int& nonpos)
 {
     const T g1 = T(0.5) - T(0.28867513459481287);
@@ -350,18 +390,18 @@ CQ_HD T ct_node(const TabPot& t, T w, T beta2, T Vmin, T iE, T tt, T& smax, int&
             const T h1 = w - wsw, h2 = wsw - (w - h), over = wsw * (T(1) + Consts<T>::rtol);
             T dc, dd;
             const T wa = w - g1 * h1, wb = w - g2 * h1;
-            ct_V<true>(t, wa > over ? wa : over, da);
-            ct_V<true>(t, wb > over ? wb : over, db);
-            ct_V<true>(t, wsw - g1 * h2, dc);
-            ct_V<true>(t, wsw - g2 * h2, dd);
+            ct_V<true, FAR>(t, wa > over ? wa : over, da);
+            ct_V<true, FAR>(t, wb > over ? wb : over, db);
+            ct_V<true, FAR>(t, wsw - g1 * h2, dc);
+            ct_V<true, FAR>(t, wsw - g2 * h2, dd);
             dV = T(0.5) * (h1 * (da + db) + h2 * (dc + dd)) + T(t.P.v_jump);
         } else {
-            ct_V<true>(t, w - g1 * h, da);
-            ct_V<true>(t, w - g2 * h, db);
+            ct_V<true, FAR>(t, w - g1 * h, da);
+            ct_V<true, FAR>(t, w - g2 * h, db);
             dV = T(0.5) * h * (da + db);
         }
     } else {
-        dV = Vmin - ct_value<T>(t, w * u);
+        dV = Vmin - ct_value<T, FAR>(t, w * u);
     }
     const T F = beta2 * (t2 * (T(2) - t2)) + dV * iE;
     if (!(F > T(0))) {
@@ -543,6 +583,30 @@ CQ_HD CtLane<float> chi_tab_lane(const TabPot& t, const QuadCfg& q, const GLRule
     return o;
 }
 
+// chi of a slow pair (0 < E < e_far) by the lane rule in FP64.
+CQ_HD CtLane<double> ct_slow_lane(const TabPot& t, const QuadCfg& q, const GLRule& gl, double b,
+                                  double E)
+{
+    CtLane<double> o{0.0, false, 0.0};
+    const CtRoot<double> R = ct_root<double, true>(t, q, b, E, true);
+    o.flag = R.flag;
+    if (R.done || R.fail) {
+        o.chi = R.done ? 0.0 : NAN;
+        return o;
+    }
+    const double beta = b * R.w, beta2 = beta * beta, iE = 1.0 / E;
+    const double Vmin = ct_value<double, true>(t, R.w);
+    double I = 0.0, smax = 0.0;
+    int nonpos = 0;
+#pragma unroll 1
+    for (int k = 0; k < gl.n; ++k)
+        I += gl.w[k] * ct_node<double, true>(t, R.w, beta2, Vmin, iE, gl.t[k], smax, nonpos);
+    if (ct_peaked<double>(R, smax * smax * LaneTol<double>::QN_FLAG > 4.0 || nonpos > 0))
+        o.flag = true;
+    o.chi = Consts<double>::pi - 2.0 * beta * I;
+    return o;
+}
+
 // Node m (0 <= m < 2 n) of a pair whose range crosses the branches' meeting
 // point, a kink of the integrand: n nodes on either side of it.
 CQ_HD double ct_kink_node(const TabPot& t, const GLRule& gl, double w, double beta, double Vmin,
@@ -596,15 +660,18 @@ inline void make_ct_nodes(const GLRule& gl, CtNodeF* nd)
 }
 
 // Whether the table kernels take the potential: below the orbiting energy
-// every root lies on the dispersion branch, and the table resolves V: within 2e-14 of the direct
-// value at points between the interpolation nodes of every interval, relative
-// to the two terms' magnitude there plus a hundredth of the well depth (the
-// argon set: 8e-15).
-inline bool ct_resolves(const Pot& P, const CtRule& rule)
+// every root lies on the dispersion branch, and the table resolves V.  That is,
+// at points between the interpolation nodes of every interval, within 2e-14 of
+// the direct value relative to its terms' magnitude (the argon set: 8e-15); at
+// w < w_far the dispersion sum has to, and the table's absolute error sets
+// *e_far, the energy from which it moves F = D(r(t)) by less than 1e-15 (twice
+// the largest error found at the points over 1e-15).
+constexpr double CT_E_FAR = 1e-3;   // most of the orbiting energy that e_far may be
+inline bool ct_resolves(const Pot& P, const CtRule& rule, double* e_far)
 {
     if (P.p.kind != DSMC_POT_JAGER || !(P.r_floor > 1.01 * P.r_sw)) return false;
     const CtScale s = ct_scale(P);
-    const double floor_V = 0.01 * fabs(V_of<double>(P, P.p.R_eps)) + 1e-12;
+    double far_err = 0.0;
     for (int i = 0; i < CT_N; ++i) {
         double c[CT_C];
         ct_build(P, s, rule, i, c);
@@ -612,16 +679,22 @@ inline bool ct_resolves(const Pot& P, const CtRule& rule)
             const double x = -0.4 + 0.25 * m, k = (i < CT_LR ? i : i - CT_LR) + (0.5 + x);
             const double w = i < CT_LR ? k / s.inv_lr : s.w_sw + k / s.inv_sr;
             const double V = i < CT_LR ? ct_far(P, w) : ct_near(P, w);
-            const double t = c[0] + x * (c[1] + x * (c[2] + x * (c[3] + x * (c[4] + x * c[5]))));
-            double mag = fabs(V) + floor_V;
+            double t = c[0] + x * (c[1] + x * (c[2] + x * (c[3] + x * (c[4] + x * c[5]))));
+            double mag = fabs(V);
             if (i < CT_LR) {
                 const double r = 1.0 / w;
                 mag += 2.0 * P.p.A * exp(P.p.a1 * r + P.p.a2 * r * r + P.p.am1 * w + P.p.am2 * w * w);
             }
+            if (w < s.w_far) {
+                double d, e;
+                if (!(fabs(t - V) <= far_err)) far_err = fabs(t - V);
+                t = ct_tail(P.p, w, d, e);
+            }
             if (!(fabs(t - V) <= 2e-14 * mag)) return false;
         }
     }
-    return true;
+    *e_far = 2e15 * far_err;
+    return *e_far <= CT_E_FAR * P.e_scan;
 }
 
 }  // namespace dsmc

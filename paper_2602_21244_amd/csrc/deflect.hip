@@ -191,16 +191,23 @@ static const CtRule& ct_rule()
     return r;
 }
 
-// *tab: the kernels with the potential in a table apply.
-static int get_pot(const dsmc_potential* pot, Pot* out, bool* tab)
+// Whether the kernels with the potential in a table apply, and from which energy
+// their lanes go by the table alone (ct_resolves).
+struct TabUse {
+    bool use;
+    double e_far;
+};
+
+static int get_pot(const dsmc_potential* pot, Pot* out, TabUse* tab)
 {
-    static thread_local bool have = false, cached_tab = false;
+    static thread_local bool have = false;
+    static thread_local TabUse cached_tab{false, 0.0};
     static thread_local Pot cached;
     if (!(have && pot && same_pot(cached.p, *pot))) {
         const int rc = make_pot(pot, out);
         if (rc) return rc;
         cached = *out;
-        cached_tab = ct_resolves(*out, ct_rule());
+        cached_tab.use = ct_resolves(*out, ct_rule(), &cached_tab.e_far);
         have = true;
     }
     *out = cached;
@@ -245,17 +252,19 @@ template <typename T> struct TabArgs {
     Pot P;
     QuadCfg q;
     CtRule rule;
+    double e_far;
     int n;
     double t[GL_MAX / 2], w[GL_MAX / 2];
     typename TabNode<T>::type nd[GL_MAX];
 };
 
 template <typename T>
-static void tab_args(const Pot& P, const QuadCfg& q, const GLRule& gl, TabArgs<T>* a)
+static void tab_args(const Pot& P, const QuadCfg& q, const GLRule& gl, double e_far, TabArgs<T>* a)
 {
     a->P = P;
     a->q = q;
     a->rule = ct_rule();
+    a->e_far = e_far;
     a->n = gl.n;
     for (int k = 0; k < (gl.n + 1) / 2; ++k) {
         a->t[k] = gl.t[k];
@@ -298,6 +307,7 @@ __device__ __forceinline__ double lane_value(double x, int src)
 // chi of one pair by the whole wave with V from the table: the steps of
 // chi_refine_wave in w = 1/r, where the nodes need no division, D'' comes
 // from the polynomial, and sinh and cosh of a node share one exponential.
+template <bool FAR>
 __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& gl, double b,
                                                  double E)
 {
@@ -307,7 +317,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
     const double rtop = b > t.P.r_zero ? b : t.P.r_zero;
     const double wtop = 1.0 / rtop;
     const double w = wtop * exp(lane * (log(rtop / (0.98 * t.P.r_floor)) * (1.0 / (REF_SAMPLES - 1))));
-    const double D = 1.0 - b2 * (w * w) - ct_value<double>(t, w) * iE;
+    const double D = 1.0 - b2 * (w * w) - ct_value<double, FAR>(t, w) * iE;
     const double Dup = __shfl(D, lane > 0 ? lane - 1 : 0, 64);
     const double Ddn = __shfl(D, lane < 63 ? lane + 1 : 63, 64);
     const uint64_t neg = __ballot(D <= 0.0);
@@ -324,7 +334,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
         for (int rd = 0; rd < REF_ROUNDS; ++rd) {
             const double x = ref_x(a, c, lane);
             double dV;
-            ct_V<true>(t, x, dV);
+            ct_V<true, FAR>(t, x, dV);
             const double f = -2.0 * b2 * x - dV * iE;
             const uint64_t pos = __ballot(f >= 0.0);
             const int L = ref_pick(pos ? __ffsll((unsigned long long)pos) - 1 : 64);
@@ -336,7 +346,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
         wm = (fc > fa) ? a - fa * (c - a) / (fc - fa) : 0.5 * (a + c);
         wm = fmin(fmax(wm, a), c);
         d2m = (fc - fa) / (c - a);
-        dm = 1.0 - b2 * (wm * wm) - ct_value<double>(t, wm) * iE;
+        dm = 1.0 - b2 * (wm * wm) - ct_value<double, FAR>(t, wm) * iE;
         if (dm <= 0.0) {   // the dip reaches zero: the largest root lies outside it
             wa = outer;
             wb = wm;
@@ -348,7 +358,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
     double fl = 1.0, fh = -1.0;
     for (int rd = 0; rd < REF_ROUNDS && wb > wa; ++rd) {
         const double x = ref_x(wa, wb, lane);
-        const double f = 1.0 - b2 * (x * x) - ct_value<double>(t, x) * iE;
+        const double f = 1.0 - b2 * (x * x) - ct_value<double, FAR>(t, x) * iE;
         const uint64_t np = __ballot(!(f > 0.0));
         const int L = ref_pick(np ? __ffsll((unsigned long long)np) - 1 : 64);
         wa = lane_value(x, L - 1);
@@ -359,7 +369,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
     double w0 = (wb > wa && fl > fh) ? wa + fl * (wb - wa) / (fl - fh) : wb;
     w0 = fmin(fmax(w0, wa), wb);
     double dV, d2V;
-    const double Vmin = ct_V2(t, w0, dV, d2V), beta = b * w0;
+    const double Vmin = ct_V2<FAR>(t, w0, dV, d2V), beta = b * w0;
     // sinh map of t around the interior peak, else around t = 0, where
     // F / t^2 ~ Q0 + Q2 t^2
     double c = 0.0, h;
@@ -388,7 +398,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
         const double e = exp(lo + len * (pnl + gl.t[j])), ei = 1.0 / e;
         const double tt = c + 0.5 * h * (e - ei);
         I += gl.w[j] * len * (0.5 * h * (e + ei)) *
-             ct_node<double>(t, w0, beta * beta, Vmin, iE, tt, smax, nonpos);
+             ct_node<double, FAR>(t, w0, beta * beta, Vmin, iE, tt, smax, nonpos);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) I += __shfl_xor(I, o, 64);
@@ -477,7 +487,12 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
             CtLane<T> c{T(0), false, 0.0};
             if (active) {
                 job.inputs(i, b, E);
-                c = chi_tab_lane(t, a.q, gl, a.nd, b, E);
+                if (__builtin_expect(E < a.e_far && T(E) != T(0), 0)) {
+                    const CtLane<double> d = ct_slow_lane(t, a.q, gl, b, E);
+                    c = CtLane<T>{T(d.chi), d.flag, d.kink_w};
+                } else {
+                    c = chi_tab_lane(t, a.q, gl, a.nd, b, E);
+                }
             }
             const bool pending = active && c.flag && a.q.refine;
             const bool kink = active && !pending && c.kink_w > 0.0;
@@ -511,7 +526,10 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
         const int pairs = list.n, nk = list.kinks;
         const bool done = list.next / WAVES * per_round >= chunks;
         for (int k = wave; k < pairs; k += WAVES) {
-            const double cr = ct_refine_wave(t, gl, list.b[k], list.E[k]);
+            const double b = list.b[k], E = list.E[k];
+            double cr;
+            if (__builtin_expect(E < a.e_far, 0)) cr = ct_refine_wave<true>(t, gl, b, E);
+            else cr = ct_refine_wave<false>(t, gl, b, E);
             if (lane == 0) {
                 if (cr != cr) {
                     count_root_fail(st);
@@ -553,10 +571,10 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
 
 template <typename T, class Job>
 static int launch_tab(const Job& job, int64_t n, const Pot& P, const QuadCfg& q, const GLRule& gl,
-                      dsmc_status* st, hipStream_t s, const char* what)
+                      const TabUse& tab, dsmc_status* st, hipStream_t s, const char* what)
 {
     TabArgs<T> a;
-    tab_args(P, q, gl, &a);
+    tab_args(P, q, gl, tab.e_far, &a);
     static_assert(sizeof(TabArgs<T>) + sizeof(Job) + 16 <= 4096, "kernel arguments");
     const size_t lds = tab_lds<T>();
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_chi_tab<T, Job>),
@@ -898,7 +916,7 @@ extern "C" int dsmc_deflect_jager(int64_t n, int32_t dtype, const void* b, const
     if (n > 0 && (!b || !g || !chi)) return arg_error("dsmc_deflect_jager: null pointer");
     if (!(m_red > 0)) return arg_error("dsmc_deflect_jager: m_red must be > 0");
     Pot P;
-    bool tab;
+    TabUse tab;
     int rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
@@ -910,14 +928,14 @@ extern "C" int dsmc_deflect_jager(int64_t n, int32_t dtype, const void* b, const
     hipStream_t s = as_stream(stream);
     if (dtype != DSMC_F64 && dtype != DSMC_F32)
         return arg_error("dsmc_deflect_jager: dtype %d", dtype);
-    if (tab && dtype == DSMC_F64)
+    if (tab.use && dtype == DSMC_F64)
         return launch_tab<double>(DeflectTab<double>{(const double*)b, (const double*)g,
                                                      (double*)chi, hmk, fold},
-                                  n, P, q, gl, st, s, "deflect_jager");
-    if (tab)
+                                  n, P, q, gl, tab, st, s, "deflect_jager");
+    if (tab.use)
         return launch_tab<float>(DeflectTab<float>{(const float*)b, (const float*)g, (float*)chi,
                                                    hmk, fold},
-                                 n, P, q, gl, st, s, "deflect_jager");
+                                 n, P, q, gl, tab, st, s, "deflect_jager");
     int blocks = (int)((n + 255) / 256);
     const int pb = persistent_blocks(256);
     if (blocks > pb) blocks = pb;
@@ -949,7 +967,7 @@ extern "C" int dsmc_collide_jager(int32_t n_cells, int32_t dtype, dsmc_vec3 v, d
     if (schedule < DSMC_SCHED_AUTO || schedule > DSMC_SCHED_WAVE)
         return arg_error("dsmc_collide_jager: schedule %d", schedule);
     Pot P;
-    bool tab;
+    TabUse tab;
     rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
@@ -960,17 +978,17 @@ extern "C" int dsmc_collide_jager(int32_t n_cells, int32_t dtype, dsmc_vec3 v, d
     const PairsView pr = PairsView::of(pairs);
     const int pb = persistent_blocks(256);
     const double hmk = 0.5 * m_red / KB;
-    if (tab) {
+    if (tab.use) {
         if (dtype == DSMC_F64)
             rc = launch_tab<double>(
                 PhaseAJagerTab<double>{pr, rng, v3<const double>(v), hmk, b_max * 1e10,
                                        PairBuf<double>::of(ws, pairs.cap), n_cells},
-                pairs.cap, P, q, gl, st, s, "collide_jager:phaseA");
+                pairs.cap, P, q, gl, tab, st, s, "collide_jager:phaseA");
         else
             rc = launch_tab<float>(
                 PhaseAJagerTab<float>{pr, rng, v3<const float>(v), hmk, b_max * 1e10,
                                       PairBuf<float>::of(ws, pairs.cap), n_cells},
-                pairs.cap, P, q, gl, st, s, "collide_jager:phaseA");
+                pairs.cap, P, q, gl, tab, st, s, "collide_jager:phaseA");
         if (rc) return rc;
         if (schedule == DSMC_SCHED_DEFER) return DSMC_OK;
         return phase_b(RULE_CHI, dtype, n_cells, nullptr, v, pairs, ws, pairs.cap, schedule, s);
@@ -1010,7 +1028,7 @@ extern "C" int dsmc_harvest_rows(int64_t B, const double* vr, const double* xi, 
     if (!(sigma_v > 0) || !(b_max > 0) || !(m_red > 0))
         return arg_error("dsmc_harvest_rows: sigma_v, b_max, m_red must be > 0");
     Pot P;
-    bool tab;
+    TabUse tab;
     int rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
@@ -1018,10 +1036,10 @@ extern "C" int dsmc_harvest_rows(int64_t B, const double* vr, const double* xi, 
     rc = make_cfg(quad, &q, &gl);
     if (rc) return rc;
     if (B == 0) return DSMC_OK;
-    if (tab)
+    if (tab.use)
         return launch_tab<double>(HarvestTab{vr, xi, z, 1.0 / sigma_v, b_max * 1e10,
                                              0.5 * m_red / KB, x_out, g_out, target_out, chi_out},
-                                  B, P, q, gl, st, as_stream(stream), "harvest_rows");
+                                  B, P, q, gl, tab, st, as_stream(stream), "harvest_rows");
     int blocks = (int)((B + 255) / 256);
     const int pb = persistent_blocks(256);
     if (blocks > pb) blocks = pb;
@@ -1221,7 +1239,7 @@ static int q2_impl(int64_t n_E, const double* E, double b_cut, int n_panels, int
                    dsmc_status* st, hipStream_t s)
 {
     Pot P;
-    bool tab;
+    TabUse tab;
     int rc = get_pot(pot, &P, &tab);
     if (rc) return rc;
     QuadCfg q;
@@ -1234,13 +1252,13 @@ static int q2_impl(int64_t n_E, const double* E, double b_cut, int n_panels, int
     const int64_t items = n_E * (int64_t)n_b;
     double* terms = static_cast<double*>(ws);
     const int pb = persistent_blocks(256);
-    if (tab && bgl.n <= Q2_TAB_GL) {
+    if (tab.use && bgl.n <= Q2_TAB_GL) {
         Q2Tab job{E, terms, n_b, bgl.n, b_cut * 1e10 / n_panels, {}, {}};
         for (int k = 0; k < (bgl.n + 1) / 2; ++k) {
             job.t[k] = bgl.t[k];
             job.w[k] = bgl.w[k];
         }
-        rc = launch_tab<double>(job, items, P, q, gl, st, s, "q2:terms");
+        rc = launch_tab<double>(job, items, P, q, gl, tab, st, s, "q2:terms");
         if (rc) return rc;
     } else {
         int64_t blocks = (items + 255) / 256;
