@@ -573,6 +573,7 @@ template <typename T, class Job>
 static int launch_tab(const Job& job, int64_t n, const Pot& P, const QuadCfg& q, const GLRule& gl,
                       const TabUse& tab, dsmc_status* st, hipStream_t s, const char* what)
 {
+    if (n <= 0) return DSMC_OK;
     TabArgs<T> a;
     tab_args(P, q, gl, tab.e_far, &a);
     static_assert(sizeof(TabArgs<T>) + sizeof(Job) + 16 <= 4096, "kernel arguments");

@@ -686,6 +686,29 @@ def test_deflect_refinement_off_is_worse(orc, dev, api):
     assert d.max() > CHI_TOL["f64"]["orbit"]
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("rule", ["vhs", "jager", "jager direct"])
+def test_collide_empty_pair_list(dev, api, dtype, rule):
+    """A pair list without room for a pair (cap = 0) is a list without pairs: no
+    rule refuses it and no velocity changes, with Phase B or without."""
+    say("collide empty list", dtype, rule)
+    v = torch.randn(3, 10, generator=torch.Generator().manual_seed(1), dtype=dtype).to(dev)
+    pairs = api.PairList(4, 0, dev)
+    pairs.off.zero_()
+    pairs.cnt.zero_()
+    p = W.JAGER_PLACEHOLDER
+    if rule == "jager direct":   # a wall that the potential's table does not resolve
+        p = dataclasses.replace(p, a1=-11.7, A=4e20)
+    for schedule in (api.L.SCHED_AUTO, api.L.SCHED_DEFER):
+        got, st = v.clone(), api.new_status(dev)
+        if rule == "vhs":
+            api.collide_vhs(got, pairs, 4, 2, schedule=schedule)
+        else:
+            api.collide_jager(got, pairs, 4, 2, W.AR_MASS / 2, W.B_MAX, api.potential_jager(p),
+                              schedule=schedule, st=st)
+        assert torch.equal(got, v) and api.read_status(st).root_fail == 0
+
+
 @pytest.mark.parametrize("dtype,T", [(torch.float64, 2000.0), (torch.float64, 200.0),
                                      (torch.float32, 200.0), (torch.float32, 2000.0)])
 def test_collide_jager_step(orc, dev, api, dtype, T):
