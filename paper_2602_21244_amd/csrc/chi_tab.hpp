@@ -155,14 +155,14 @@ struct TabPot {
     const float* c32;
 };
 
-// Interval and position in it, measured from its middle.
+// Interval and position in it, measured from its middle (0 <= w <= w_end).
 template <typename T> CQ_HD int ct_index(const CtScale& s, T w, T& x)
 {
     const T a = w * T(s.inv_lr), b = w * T(s.inv_sr) + T(s.k_sr);
-    const T y = (a < b ? a : b) - T(0.5), f = rint(y);
+    const T y = (a < b ? a : b) - T(0.5), r = rint(y);
+    const T f = r < T(CT_N - 1) ? r : T(CT_N - 1);   // (w = w_end: the last interval's end)
     x = y - f;
-    const uint32_t i = (uint32_t)(int)f;
-    return i < CT_N - 1 ? i : CT_N - 1;
+    return (int)f;
 }
 
 // V at w < w_far, -sum C_n w^n, with its first and second derivative in w: a
@@ -437,7 +437,8 @@ struct CtNodeF {
 template <typename T> struct CtLane {
     T chi;
     bool flag;      // needs the FP64 refinement
-    double kink_w;  // 1 / r_min of a pair whose range crosses the branches' meeting point (0: none)
+    double kink_w;  // 1 / r_min of a pair whose range crosses the branches' meeting point (0: none);
+                    // flagged as well, it is refined
 };
 
 // chi(b, E) as chi_lane gives it (b in Angstrom, E / k_B in K), FP64.
@@ -457,7 +458,8 @@ CQ_HD CtLane<double> chi_tab_lane(const TabPot& t, const QuadCfg& q, const GLRul
         o.chi = R.done ? 0.0 : NAN;
         return o;
     }
-    if (!low && R.w > t.s.w_sw) {
+    if (R.w > t.s.w_sw) {     // (below: the node loops index the dispersion branch)
+        o.flag = o.flag || low;   // below e_scan an iteration that did not converge
         o.kink_w = R.w;
         return o;
     }
@@ -532,7 +534,8 @@ CQ_HD CtLane<float> chi_tab_lane(const TabPot& t, const QuadCfg& q, const GLRule
         w = w0;
         if (low) o.flag = true;
     }
-    if (!low && w > t.s.w_sw) {
+    if (w > t.s.w_sw) {
+        o.flag = o.flag || low;
         o.kink_w = w;
         return o;
     }
@@ -589,7 +592,7 @@ CQ_HD CtLane<double> ct_slow_lane(const TabPot& t, const QuadCfg& q, const GLRul
 {
     CtLane<double> o{0.0, false, 0.0};
     const CtRoot<double> R = ct_root<double, true>(t, q, b, E, true);
-    o.flag = R.flag;
+    o.flag = R.flag || R.w > t.s.w_sw;
     if (R.done || R.fail) {
         o.chi = R.done ? 0.0 : NAN;
         return o;

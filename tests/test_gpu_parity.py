@@ -670,6 +670,54 @@ def test_deflect_slow_distant_pairs(orc, dev, api, dtype, g_lo, g_hi, b_lo, b_hi
     assert err < (1e-12 if dtype == torch.float64 else 64 * 2.0 ** -24)
 
 
+@pytest.mark.parametrize("max_iter,ratio", [(1, 0.55), (60, 0.9), (60, 0.99)])
+def test_deflect_table_root_settings(orc, dev, api, max_iter, ratio):
+    """Root settings off their defaults, for the argon set and one whose branches
+    meet (smoothly) just inside the smallest root below the orbiting energy.
+    One Newton step from r_zero with a coarse bracket then ends beyond the
+    meeting point for part of its pairs: they are refined, and so keep the
+    batch's bound."""
+    say("deflect root settings", max_iter, ratio)
+    pa = W.JAGER_PLACEHOLDER
+    r_sw = 0.4 * 7.75
+    V_sw = orc.potential_V(orc.potential_jager(dataclasses.replace(pa, R_eps=1.0)), r_sw)
+    near = dataclasses.replace(pa, R_eps=7.75, a_sr=1.9, A_sr=V_sw * r_sw * math.exp(1.9 * r_sw))
+    rng = np.random.default_rng(7)
+    n = 2049
+    E = rng.uniform(5.0, 280.0, n)
+    b = 3e-10 * rng.random(n) if max_iter == 1 else 1e-9 * np.sqrt(rng.random(n))
+    g = np.sqrt(2 * W.KB * E / (W.AR_MASS / 2))
+    for p in (pa, near):
+        P = orc.potential_jager(p)
+        keep = np.ones(n, bool)
+        if max_iter == 1:
+            lo, hi = 3.0, 4.0
+            for _ in range(100):
+                m = 0.5 * (lo + hi)
+                lo, hi = (m, hi) if orc.potential_V(P, m) > 0 else (lo, m)
+            w1, h = 1.0 / hi, 1e-6
+            dV = (orc.potential_V(P, 1 / (w1 + h)) - orc.potential_V(P, 1 / (w1 - h))) / (2 * h)
+            bA = b * 1e10
+            wn = w1 + (1 - (bA * w1) ** 2) / (2 * bA ** 2 * w1 + dV / E)
+            wn = np.where(wn < w1 / ratio, wn, 0.5 * (w1 + w1 / ratio))
+            keep = wn > (1 + 1e-6) / (0.4 * p.R_eps)
+            assert keep.any() == (p is near)
+        ref, bad = orc.chi_batch(P, b, g, W.AR_MASS / 2, n_threads=8)
+        for dtype, kind in ((torch.float64, "f64"), (torch.float32, "f32")):
+            got = api.deflect_jager(torch.as_tensor(b, dtype=dtype, device=dev),
+                                    torch.as_tensor(g, dtype=dtype, device=dev), W.AR_MASS / 2,
+                                    api.potential_jager(p),
+                                    quad=api.quad_struct(64, max_iter=max_iter, scan_ratio=ratio))
+            got = got.double().cpu().numpy()
+            if kind == "f32":
+                ref, bad = orc.chi_batch(P, b.astype(np.float32).astype(float),
+                                         g.astype(np.float32).astype(float), W.AR_MASS / 2,
+                                         n_threads=8)
+            ok = keep & (bad == 0)
+            if ok.any():
+                check_chi(got[ok], ref[ok], kind, f"{kind} {ok.sum()} pairs")
+
+
 def test_deflect_refinement_off_is_worse(orc, dev, api):
     """With the FP64 refinement switched off every pair keeps the one-rule
     result: the orbiting pairs (sharp integrand peaks) then miss the bound the
