@@ -454,9 +454,10 @@ int dsmc_step_vhs_fused(int32_t n_cells, const int32_t* cell_start, int32_t dtyp
                         dsmc_stream_t stream);
 
 /* Tuning knobs (host): threshold in pairs above which AUTO leaves the LANE
- * schedule; the autotuner in the Python package sets it.  AUTO leaves it above
- * 8 pairs whatever the threshold, and does without it for so few cells that
- * each has a wave of its own; every choice gives the same results. */
+ * schedule; the autotuner in the Python package sets it.  With the default, 48,
+ * AUTO chooses by itself: it leaves LANE above 8 pairs, and does without it for
+ * so few cells that each has a wave of its own.  Every choice gives the same
+ * results. */
 int dsmc_set_block_threshold(int32_t pairs);
 int32_t dsmc_get_block_threshold(void);
 

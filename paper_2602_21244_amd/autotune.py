@@ -1,11 +1,13 @@
 """Autotuner of the Phase-B schedules.
 
 Phase B can walk a cell's pairs in one lane (LANE) or spread a cell over a
-workgroup in dependency rounds (BLOCK).  AUTO uses BLOCK for cells with more
-pairs than a threshold.  The best threshold depends on the cell-size
-histogram, so it is measured on the actual pair list: each candidate
-threshold is timed with HIP events on a scratch copy of the velocities and the
-fastest is installed with dsmc_set_block_threshold.  The fused Phase B +
+wave or a workgroup in dependency rounds (WAVE, BLOCK).  AUTO leaves LANE for
+cells with more pairs than a threshold, or, with the default threshold 48, by
+a rule of its own (8 pairs, none for few cells).  The best choice depends on
+the cell-size histogram, so it is measured on the actual pair list: each
+candidate threshold, the default among them, is timed with HIP events on a
+scratch copy of the velocities and the fastest is installed with
+dsmc_set_block_threshold.  The fused Phase B +
 moment matching of the timed step (dsmc_apply_pairs_match) runs three
 persistent kernels (wave per cell, medium and big block per cell) whose grid
 sizes are tuned the same way (dsmc_set_match_schedule).  Results are cached
@@ -55,7 +57,9 @@ def tune_block_threshold(v, pairs, ws, kind=api.L.APPLY_DIRECTIONS, reps=3, use_
 
     v: sorted velocities [3, N]; pairs/ws: a selection and the Phase-A results
     of a collide call made with schedule DSMC_SCHED_DEFER."""
-    key = f"{torch.cuda.get_device_name(v.device)}|{kind}|{_signature(pairs)}"
+    # (entries without "auto48" were measured while the threshold had no effect
+    # above 8, or before the default chose by itself)
+    key = f"{torch.cuda.get_device_name(v.device)}|auto48|{kind}|{_signature(pairs)}"
     cache = _load_cache() if use_cache else {}
     if key in cache:
         api.set_block_threshold(cache[key]["threshold"])

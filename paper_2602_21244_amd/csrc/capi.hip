@@ -9,7 +9,7 @@
 namespace dsmc {
 
 static thread_local char g_err[512] = "";
-static int32_t g_block_threshold = 48;
+static int32_t g_block_threshold = BLOCK_THRESHOLD_DEFAULT;
 static dsmc_match_schedule g_match_schedule = {40, 2, 1, 0};
 
 void set_error(const char* fmt, ...)

@@ -917,14 +917,15 @@ int phase_b(int rule, int dtype, int32_t n_cells, const int32_t* cell_start, dsm
     // them, and they queue up from some 4 000 cells on.  LANE against WAVE,
     // FP64: 200 cells of 4 / 16 / 48 pairs 8 / 29 / 84 us against 9 / 10 /
     // 11 us; 300 000 cells of 8 / 16 / 48 pairs 0.48 / 1.06 / 3.4 ms against
-    // 0.57 / 0.63 / 0.82 ms.  So AUTO goes by lanes to LANE_MAX pairs at most,
+    // 0.57 / 0.63 / 0.82 ms, in FP32 0.39 / 0.84 / 3.2 ms against 0.36 / 0.41 /
+    // 0.53 ms.  So AUTO goes by lanes to LANE_MAX pairs at most,
     // and not at all while the wave kernel has a workgroup for every cell
     // (10 000 cells of 4 pairs 20 us, of which the lanes alone would take 12
-    // and the launches after them 9).
+    // and the launches after them 9).  A threshold that was set stands.
     constexpr int32_t LANE_MAX = 8;
     int32_t thr = block_threshold();
-    if (thr > LANE_MAX) thr = LANE_MAX;
-    if (n_cells <= (int64_t)device_cus() * match_schedule().wave_per_cu) thr = 0;
+    if (thr == BLOCK_THRESHOLD_DEFAULT)
+        thr = n_cells <= (int64_t)device_cus() * match_schedule().wave_per_cu ? 0 : LANE_MAX;
     bool use_wave = true;
     if (schedule == DSMC_SCHED_LANE) thr = INT32_MAX;
     if (schedule == DSMC_SCHED_BLOCK) { thr = 0; use_wave = false; }

@@ -260,7 +260,9 @@ int exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, void* ws, hip
 int fill_i32(int32_t* p, int32_t value, int64_t n, hipStream_t s);
 int fill_bytes_zero(void* p, size_t bytes, hipStream_t s);
 
-// Schedule threshold (pairs per cell above which AUTO uses the BLOCK schedule).
+// Schedule threshold: pairs per cell above which AUTO leaves the LANE schedule;
+// the default leaves the choice to phase_b.
+constexpr int32_t BLOCK_THRESHOLD_DEFAULT = 48;
 int32_t block_threshold();
 
 }  // namespace dsmc

@@ -194,6 +194,49 @@ def test_autotune_installs_best_threshold(dev, api):
     assert times[thr] == min(times.values())
 
 
+@pytest.mark.parametrize("n_cells", [256, 40_000])
+def test_block_threshold_that_was_set_stands(dev, api, n_cells):
+    """Cells of 64 pairs: one lane takes some 0.1 ms for a cell, a wave
+    a fraction of it.  A threshold of 64 sends them by lanes, 63 and the
+    default, which chooses by itself, do not; the velocities are the same."""
+    say("block threshold", n_cells)
+    before = api.get_block_threshold()
+    N, c = 64, 64
+    g = torch.Generator().manual_seed(5)
+    i = torch.randint(0, N, (n_cells * c,), generator=g)
+    j = (i + torch.randint(1, N, (n_cells * c,), generator=g)) % N
+    cell = torch.arange(n_cells).repeat_interleave(c)
+    pairs = api.PairList(n_cells, n_cells * c, dev)
+    pairs.off.copy_(c * torch.arange(n_cells))
+    pairs.cnt.fill_(c)
+    for t, x in ((pairs.i, cell * N + i), (pairs.j, cell * N + j), (pairs.cell, cell)):
+        t[:n_cells * c] = x.to(dev)
+    v = 300.0 * torch.randn(3, N * n_cells, generator=g, dtype=torch.float64)
+    v = v.to(dev)
+    ws = api.collide_vhs(v.clone(), pairs, 3, 1, schedule=api.L.SCHED_DEFER)
+    out, ms = {}, {}
+    try:
+        for thr in (48, 63, 64, 1 << 30):
+            api.set_block_threshold(thr)
+            assert api.get_block_threshold() == thr
+            times = []
+            for _ in range(5):
+                w = v.clone()
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record()
+                api.apply_pairs(w, pairs, api.L.APPLY_DIRECTIONS, ws, schedule=api.L.SCHED_AUTO)
+                e1.record()
+                torch.cuda.synchronize()
+                times.append(e0.elapsed_time(e1))
+            out[thr], ms[thr] = w, min(times)
+    finally:
+        api.set_block_threshold(before)
+    say("  ms:", ms)
+    for thr in (63, 64, 1 << 30):
+        assert torch.equal(out[thr], out[48])
+    assert min(ms[64], ms[1 << 30]) > 1.5 * max(ms[48], ms[63])
+
+
 def test_autotune_match_schedule(dev, api):
     """The launch shape of the fused Phase B + moment matching: every shape
     gives the same velocities bit for bit, and the tuner installs the
