@@ -211,7 +211,8 @@ int dsmc_status_clear(dsmc_status* st, dsmc_stream_t stream);
  * ws: dsmc_sort_cells_ws(n, n_cells) bytes (about 12 n + 4 KiB per 4096
  * particles, plus a few bytes per thousand cells for the count scan; from 512
  * to 262 143 cells and up to 2^27 particles 32 n more, through which input in
- * no particular order is moved). */
+ * no particular order is moved).  Those are not required: 16 n of them do for
+ * FP32, and with less the same result takes longer. */
 size_t dsmc_sort_cells_ws(int32_t n, int32_t n_cells);
 int dsmc_sort_cells(int32_t n, int32_t n_cells, const int32_t* cell_of, int32_t dtype,
                     dsmc_vec3 v_in, dsmc_vec3 v_out, int32_t* cell_start, int32_t* perm,

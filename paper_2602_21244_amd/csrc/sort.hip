@@ -637,6 +637,12 @@ static size_t sort_base_ws(int32_t n, int32_t n_cells)
            align_up(sizeof(int32_t) * (size_t)RADIX) + scan_ws_bytes(n_cells) + 256;
 }
 
+// What the records of n particles take beyond that.
+template <typename T> static size_t sort_rec_ws(int32_t n)
+{
+    return align_up(sizeof(int2) * FAR_TILES) + align_up(sizeof(SortRec<T>) * (size_t)n);
+}
+
 // Offsets of a pass's digits: up to DIRECT_TILES tiles the down pass adds the
 // histogram rows itself (two launches a pass instead of five; both passes of
 // 62 tiles: 49 us against 64 us, of which the down kernels 38 and 28; at 245
@@ -826,8 +832,7 @@ extern "C" size_t dsmc_sort_cells_ws(int32_t n, int32_t n_cells)
 {
     if (n < 0 || n_cells < 0) return 0;
     size_t b = sort_base_ws(n, n_cells);
-    if (may_carry(n, n_cells))
-        b += align_up(sizeof(int2) * FAR_TILES) + align_up(sizeof(SortRec<double>) * (size_t)n);
+    if (may_carry(n, n_cells)) b += sort_rec_ws<double>(n);
     return b;
 }
 
@@ -843,13 +848,15 @@ extern "C" int dsmc_sort_cells(int32_t n, int32_t n_cells, const int32_t* cell_o
         return arg_error("dsmc_sort_cells: null pointer");
     if (v_in.x == v_out.x || v_in.y == v_out.y || v_in.z == v_out.z)
         return arg_error("dsmc_sort_cells: v_in and v_out must be distinct buffers");
-    if (ws_bytes < dsmc_sort_cells_ws(n, n_cells))
-        return arg_error("dsmc_sort_cells: workspace %zu < %zu", ws_bytes,
-                         dsmc_sort_cells_ws(n, n_cells));
+    const size_t base = sort_base_ws(n, n_cells);
+    if (ws_bytes < base)
+        return arg_error("dsmc_sort_cells: workspace %zu < %zu", ws_bytes, base);
     hipStream_t s = as_stream(stream);
     if (dtype == DSMC_F64)
-        return sort_impl<double>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, true, st, s);
+        return sort_impl<double>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws,
+                                 ws_bytes >= base + sort_rec_ws<double>(n), st, s);
     if (dtype == DSMC_F32)
-        return sort_impl<float>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws, true, st, s);
+        return sort_impl<float>(n, n_cells, cell_of, v_in, v_out, cell_start, perm, ws,
+                                ws_bytes >= base + sort_rec_ws<float>(n), st, s);
     return arg_error("dsmc_sort_cells: dtype %d", dtype);
 }

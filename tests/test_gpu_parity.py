@@ -106,6 +106,48 @@ def test_sort_sizes_bitexact(dev, api, n, n_cells, order, f32):
         assert torch.equal(o.cpu(), v[:, torch.from_numpy(perm)])
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("n,n_cells", [(5000, 512), (300_001, 20_000)])
+def test_sort_workspace_sizes_bitexact(dev, api, dtype, n, n_cells):
+    """Shuffled input with a workspace that has no room for the particles' records
+    (three index arrays, two digit tables, two of their chunks' sums, one row and
+    the scan's sums: all that is required), one byte less than room for them, just
+    room, and more; one byte less than what is required is refused."""
+    say("sort workspaces", dtype, n, n_cells)
+
+    def up(x):
+        return (x + 255) // 256 * 256
+
+    tiles = (n + 4095) // 4096
+    base = (3 * up(4 * n) + 2 * up(4 * 512 * tiles) + 2 * up(4 * 512 * ((tiles + 31) // 32)) +
+            up(4 * 512) + up(4 * ((n_cells + 4095) // 4096 + 1)) + 256)
+    rec = up(8 * 64) + up((32 if dtype == torch.float64 else 16) * n)
+    full = api.lib().dsmc_sort_cells_ws(n, n_cells)
+    assert full == base + up(8 * 64) + up(32 * n)
+    g = torch.Generator().manual_seed(n)
+    cell = torch.randint(0, n_cells, (n,), generator=g, dtype=torch.int32)
+    perm = torch.argsort(cell, stable=True)
+    v = torch.randn(3, n, generator=g, dtype=dtype)
+    vd, cd = v.to(dev), cell.to(dev)
+    vo, st = torch.empty_like(vd), api.new_status(dev)
+    csd = torch.empty(n_cells + 1, dtype=torch.int32, device=dev)
+    pd = torch.empty(n, dtype=torch.int32, device=dev)
+
+    def sort(wsb):
+        ws = torch.full((wsb,), 255, dtype=torch.uint8, device=dev)
+        return api.lib().dsmc_sort_cells(n, n_cells, api._ptr(cd), api._dtype(vd), api._vec3(vd),
+                                         api._vec3(vo), api._ptr(csd), api._ptr(pd), api._ptr(ws),
+                                         wsb, api._ptr(st), api._stream(None))
+
+    assert sort(base - 1) == api.L.DSMC_E_ARG
+    for wsb in (base, base + rec - 1, base + rec, full):
+        vo.zero_()
+        pd.zero_()
+        api.check(sort(wsb), "dsmc_sort_cells")
+        assert torch.equal(pd.cpu().long(), perm) and torch.equal(vo.cpu(), v[:, perm]), wsb
+        assert torch.equal(csd.cpu()[1:].long(), torch.cumsum(torch.bincount(cell, minlength=n_cells), 0))
+
+
 @pytest.mark.parametrize("case", ["c1", "ragged", "bigcells", "empty_tail", "bad_ids", "f32",
                                   "three_pass", "one_cell", "shuffled", "tiny", "all_bad",
                                   "sorted_runs"])
