@@ -27,7 +27,10 @@
 // sums of the FP32 deltas, and one adds the splits and chunks.  Every sum is
 // taken in the order of the tiled GEMM's path, so the gradients are the same
 // bit for bit: a training run amplifies a rounding (a bf16 weight that flips)
-// to 1e-6 of the next loss.
+// to 1e-6 of the next loss.  The walk and the column sums go by slabs of AF_SLAB
+// rows, whose FP32 deltas share one buffer: 2^20 rows of the paper's network
+// take 16.7 GB instead of 22.4 (17.8 layer by layer) and 13.7 ms instead of
+// 13.6 (46 ms).
 #include <math.h>
 
 #include "anet_fused.hpp"
@@ -59,6 +62,7 @@ struct AfDev {
     __bf16* h[AF_MAX_LAYERS];
     __bf16* delta[AF_MAX_LAYERS];
     float* dz[AF_MAX_LAYERS];
+    int64_t slab0;                   // first row of dz
 };
 
 __device__ __forceinline__ float af_sigm(float z)
@@ -355,7 +359,9 @@ __device__ __forceinline__ void af_store_bwd(const AfDev& n, int j, const floatx
                     hv[i] = (__bf16)(zi * sg);
                     d4[i] = in ? d : 0.0f;
                 }
-                if (blk) *reinterpret_cast<floatx4a*>(dz + af_zoff(row0, rb0 + r, N, u0 + u, q)) = d4;
+                if (blk)
+                    *reinterpret_cast<floatx4a*>(
+                        dz + af_zoff(row0 - n.slab0, rb0 + r, N, u0 + u, q)) = d4;
                 if (in) *reinterpret_cast<bf16x4a*>(n.h[j] + o + 8 * q) = hv;
                 if (j > 0) {
                     if (in) *reinterpret_cast<bf16x4a*>(n.delta[j] + o + 8 * q) = dv;
@@ -411,13 +417,13 @@ k_anet_fused_bwd(AfDev n, int64_t R, const float* __restrict__ dy)
     __bf16* hs = reinterpret_cast<__bf16*>(smem);
     __bf16* ds = reinterpret_cast<__bf16*>(smem + (size_t)ROWS * n.ld * sizeof(__bf16));
     const int t = threadIdx.x, w = t >> 6;
-    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    const int64_t row0 = n.slab0 + (int64_t)blockIdx.x * ROWS;
     if (t < ROWS) {
         const int64_t g = row0 + t;
         float d = 0.0f;
         if (g < R) {
             d = dy[g] / (1.0f + expf(-n.z[n.L - 1][g]));
-            n.dz[n.L - 1][g] = d;
+            n.dz[n.L - 1][g - n.slab0] = d;
             n.delta[n.L - 1][g] = (__bf16)d;
         }
         ds[t] = (__bf16)d;
@@ -451,10 +457,11 @@ struct AfCols {
     int first[AF_MAX_LAYERS + 1];    // first group of 64 units of each hidden layer
     int red_off[AF_MAX_LAYERS];      // first column of layer l's sums in a chunk's row of red
     int red_ld;
-    int64_t R, chunks;
+    int64_t R, chunks;               // rows and chunks of the slab
     float* red;                      // [chunks][red_ld]
 };
 constexpr int AC_ROWS = 256;
+static_assert(AF_SLAB % AC_ROWS == 0, "whole chunks (and tiles) in a slab");
 
 __global__ void __launch_bounds__(64)
 k_anet_cols(AfCols g)
@@ -677,7 +684,6 @@ k_anet_dw(AdArgs g)
 // fourth one added in order.  The bias and layer-0 gradients: 16 sums of every
 // 16th chunk, added in order; 64 columns per workgroup.
 struct AfFinal {
-    int n;
     float* dW[AF_MAX_LAYERS];     // layers 1 .. n
     int64_t off[AF_MAX_LAYERS + 1];
     const float* partial;
@@ -686,7 +692,6 @@ struct AfFinal {
     const float* red;
     int red_ld;
     int64_t chunks;
-    int nl;                       // weight layers (columns of red)
     int red_off[AF_MAX_LAYERS + 1];
     float* db[AF_MAX_LAYERS];
     float* dW0;
@@ -804,7 +809,7 @@ AnetFusedWs anet_fused_layout(void* base, const AnetShape& a, int64_t R)
             take(sizeof(float) * (l < a.L - 1 ? blocks * a.d[l + 1] : n)));
         if (l < a.L - 1) w.h[l] = reinterpret_cast<__bf16*>(take(sizeof(__bf16) * n));
         w.dz[l] = reinterpret_cast<float*>(
-            take(sizeof(float) * (l < a.L - 1 ? blocks * a.d[l + 1] : n)));
+            take(sizeof(float) * (blocks < AF_SLAB ? blocks : AF_SLAB) * a.d[l + 1]));
         if (l > 0) w.delta[l] = reinterpret_cast<__bf16*>(take(sizeof(__bf16) * n));
         w.b[l] = reinterpret_cast<float*>(take(sizeof(float) * a.d[l + 1]));
         if (l > 0 && l < a.L - 1)
@@ -887,15 +892,17 @@ static int fwd_launch(const AfDev& n, const AnetShape& a, int64_t R, const float
     return DSMC_OK;
 }
 
+// One slab of the walk back: rows n.slab0 .. below R1.
 template <int RB, int PF>
-static int bwd_launch(const AfDev& n, const AnetShape& a, int64_t R, const float* dy,
+static int bwd_launch(const AfDev& n, const AnetShape& a, int64_t R1, const float* dy,
                       hipStream_t s)
 {
     const size_t lds = lds_bytes(a, RB);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_anet_fused_bwd<RB, PF>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_check(e, "anet:bwd LDS");
-    k_anet_fused_bwd<RB, PF><<<(unsigned)tiles_of(R, RB), AF_THREADS, lds, s>>>(n, R, dy);
+    k_anet_fused_bwd<RB, PF><<<(unsigned)tiles_of(R1 - n.slab0, RB), AF_THREADS, lds, s>>>(n, R1,
+                                                                                       dy);
     DSMC_LAUNCH_CHECK("anet:bwd");
     return DSMC_OK;
 }
@@ -924,9 +931,6 @@ int anet_fused_backward(const dsmc_anet* net, const AnetShape& a, int64_t R, con
     if (tiles_of(R, rb) > 2147483647) return arg_error("anet: too many rows");
     int rc = pack(net, a, w, true, s);
     if (rc) return rc;
-    const AfDev n = dev_of(net, a, w);
-    rc = rb == 1 ? bwd_launch<1, 8>(n, a, R, dy, s) : bwd_launch<2, 8>(n, a, R, dy, s);
-    if (rc) return rc;
 
     AdArgs g{};
     AfFinal f{};
@@ -950,8 +954,6 @@ int anet_fused_backward(const dsmc_anet* net, const AnetShape& a, int64_t R, con
     g.total = off;
     g.kc = ((R + AF_SPLITS - 1) / AF_SPLITS + 31) / 32 * 32;   // trailing splits may be empty
     g.partial = w.partial;
-    k_anet_dw<<<(unsigned)(g.tiles * AF_SPLITS), 256, 0, s>>>(g);
-    DSMC_LAUNCH_CHECK("anet:dw");
 
     AfCols q{};
     q.L = a.L;
@@ -960,18 +962,28 @@ int anet_fused_backward(const dsmc_anet* net, const AnetShape& a, int64_t R, con
         q.dz[l] = w.dz[l];
         if (l + 1 < a.L) q.first[l + 1] = q.first[l] + a.d[l + 1] / 64;
     }
-    q.x = w.x;
     q.red_ld = red_columns(a, f.red_off);
     for (int l = 0; l < a.L; ++l) q.red_off[l] = f.red_off[l];
-    q.R = R;
-    q.chunks = chunks_of(R);
-    q.red = w.red;
-    const int64_t jobs = q.chunks * q.first[a.L - 1] + (q.chunks + 15) / 16;
-    if (jobs > 2147483647) return arg_error("anet: too many rows");
-    k_anet_cols<<<(unsigned)jobs, 64, 0, s>>>(q);
-    DSMC_LAUNCH_CHECK("anet:cols");
 
-    f.n = g.n;
+    AfDev n = dev_of(net, a, w);
+    for (int64_t r0 = 0; r0 < R; r0 += AF_SLAB) {
+        const int64_t r1 = r0 + AF_SLAB < R ? r0 + AF_SLAB : R;
+        n.slab0 = r0;
+        rc = rb == 1 ? bwd_launch<1, 8>(n, a, r1, dy, s) : bwd_launch<2, 8>(n, a, r1, dy, s);
+        if (rc) return rc;
+        if (r1 == R) {   // (before the sums: delta and h are still in the cache)
+            k_anet_dw<<<(unsigned)(g.tiles * AF_SPLITS), 256, 0, s>>>(g);
+            DSMC_LAUNCH_CHECK("anet:dw");
+        }
+        q.x = w.x + 2 * r0;
+        q.R = r1 - r0;
+        q.chunks = chunks_of(q.R);
+        q.red = w.red + r0 / AC_ROWS * q.red_ld;
+        const int64_t jobs = q.chunks * q.first[a.L - 1] + (q.chunks + 15) / 16;
+        k_anet_cols<<<(unsigned)jobs, 64, 0, s>>>(q);
+        DSMC_LAUNCH_CHECK("anet:cols");
+    }
+
     f.partial = w.partial;
     f.total = off;
     int64_t wb = (off + 255) / 256;
@@ -979,8 +991,7 @@ int anet_fused_backward(const dsmc_anet* net, const AnetShape& a, int64_t R, con
     f.wblocks = (int)(wb < pb ? wb : pb);
     f.red = w.red;
     f.red_ld = q.red_ld;
-    f.chunks = q.chunks;
-    f.nl = a.L;
+    f.chunks = chunks_of(R);
     for (int l = 0; l < a.L; ++l) f.db[l] = db[l];
     f.dW0 = dW[0];
     k_anet_final<<<f.wblocks + (f.red_ld + 63) / 64, 256, 0, s>>>(f);

@@ -69,6 +69,26 @@ def test_struct_layout_matches_header():
             assert int(got[f"{cname}.{fname}"]) == getattr(py, fname).offset, (cname, fname)
 
 
+@pytest.mark.parametrize("dims", [(2, 128, 256, 512, 512, 256, 128, 1), (2, 512, 512, 1)])
+@pytest.mark.parametrize("rows", [1 << 20, 12_000_000])
+def test_angle_network_workspace(lib, dims, rows):
+    """Of a large batch, the angle network's workspace holds per row no more than
+    the activations (x, z in FP32, h in bf16) and two ping-pong deltas of the
+    widest layer in FP32 and bf16, which the layer-by-layer path takes: the
+    largest batches that a card has memory for are the same on either path."""
+    from paper_2602_21244_amd import _lib as L
+    a = L.Anet()
+    a.n_layers = len(dims) - 1
+    for q, d in enumerate(dims):
+        a.dims[q] = d
+    keep = [C.create_string_buffer(16) for _ in range(2 * a.n_layers)]
+    for q in range(a.n_layers):
+        a.W[q] = C.addressof(keep[2 * q])
+        a.b[q] = C.addressof(keep[2 * q + 1])
+    per_row = 8 + 4 * sum(dims[1:]) + 2 * sum(dims[1:-1]) + 2 * (4 + 2) * max(dims)
+    assert 0 < lib.dsmc_anet_ws(C.byref(a), rows) <= per_row * rows
+
+
 def test_host_argument_errors(lib):
     from paper_2602_21244_amd import _lib as L
     # null pointers and bad sizes are rejected on the host without a GPU call

@@ -143,6 +143,13 @@ def test_anet_paths_agree_bitwise(dev, api, dims, rows):
         assert torch.equal(b, out[1][2][l][:b.shape[0]]), l
 
 
+def test_anet_backward_row_slabs_bitwise(dev, api):
+    """The backward goes by slabs of 262 144 rows: the last row of one and the
+    first 33 of the next against the layer-by-layer path, as above."""
+    say("anet row slabs")
+    test_anet_paths_agree_bitwise(dev, api, (2, 128, 256, 1), (1 << 18) + 33)
+
+
 def test_huber_loss_matches_oracle(orc, dev, api):
     say("huber loss")
     rng = np.random.default_rng(2)
