@@ -203,18 +203,14 @@ template <> struct Consts<float> {
     static constexpr float rtol = 2e-7f;
 };
 
-// PV: what evaluates the potential, a Pot (directly) or a table of it with the
-// same functions; plain() is the Pot of either.
-CQ_HD const Pot& plain(const Pot& P) { return P; }
-
 // D(r) = 1 - b^2/r^2 - V(r)/E and its derivative.
-template <typename T, class PV>
-CQ_HD T D_of(const PV& P, T b2, T E, T r)
+template <typename T>
+CQ_HD T D_of(const Pot& P, T b2, T E, T r)
 {
     return T(1) - b2 / (r * r) - V_of<T>(P, r) / E;
 }
-template <typename T, class PV>
-CQ_HD T dD_of(const PV& P, T b2, T E, T r)
+template <typename T>
+CQ_HD T dD_of(const Pot& P, T b2, T E, T r)
 {
     return T(2) * b2 / (r * r * r) - dV_of<T>(P, r) / E;
 }
@@ -225,24 +221,24 @@ CQ_HD T dD_of(const PV& P, T b2, T E, T r)
 // Near r_min the potential difference is -int V' dr by 2-point
 // Gauss-Legendre (no cancellation).  F <= 0 (only possible if r_min is not
 // the largest root) counts in *nonpos.
-template <typename T, class PV>
-CQ_HD T node_term(const PV& P, T rmin, T beta, T Vmin, T E, T D0, T t, T& f_over_t2, int& nonpos)
+template <typename T>
+CQ_HD T node_term(const Pot& P, T rmin, T beta, T Vmin, T E, T D0, T t, T& f_over_t2, int& nonpos)
 {
     const T g1 = T(0.5) - T(0.28867513459481287);
     const T g2 = T(0.5) + T(0.28867513459481287);
     const T t2 = t * t;
     const T dr = rmin * t2 / (T(1) - t2);
     T dV = T(0);
-    if (plain(P).p.kind != DSMC_POT_HS) {
+    if (P.p.kind != DSMC_POT_HS) {
         if (t2 < T(1e-3)) {
-            const T rs = T(plain(P).r_sw);
+            const T rs = T(P.r_sw);
             if (rmin < rs && rmin + dr > rs) {
                 // the two branches of the JAGER form meet inside the step:
                 // integrate each side on its own, plus the (set-up) jump
                 const T h1 = rs - rmin, h2 = rmin + dr - rs;
                 dV = -h1 * T(0.5) * (dV_of<T>(P, rmin + g1 * h1) + dV_of<T>(P, rmin + g2 * h1)) -
                      h2 * T(0.5) * (dV_of<T>(P, rs + g1 * h2) + dV_of<T>(P, rs + g2 * h2)) +
-                     T(plain(P).v_jump);
+                     T(P.v_jump);
             } else {
                 dV = -dr * T(0.5) * (dV_of<T>(P, rmin + g1 * dr) + dV_of<T>(P, rmin + g2 * dr));
             }
@@ -535,8 +531,7 @@ CQ_HD void ref_map(RefState& s, bool has_min, double rm, double dm, double d2m, 
 // Weighted integrand at node m (0 <= m < ref_nodes(s, gl)) of the mapped rule:
 // REF_PANELS equal panels in s on each side of the peak.
 CQ_HD int ref_nodes(const RefState& s, const GLRule& gl) { return s.sides * REF_PANELS * gl.n; }
-template <class PV>
-CQ_HD double ref_node(const PV& P, const GLRule& gl, const RefState& s, int m, int& nonpos)
+CQ_HD double ref_node(const Pot& P, const GLRule& gl, const RefState& s, int m, int& nonpos)
 {
     const int seg = m / gl.n, j = m - seg * gl.n;
     const int side = (s.sides == 2) ? seg / REF_PANELS : 1;

@@ -35,8 +35,7 @@ namespace dsmc {
 //     evaluated there; D'' at r_min by a central difference on two lanes.
 //  4. The sinh-mapped integral, its nodes spread over the lanes, summed by a
 //     fixed butterfly.
-template <class PV>
-__device__ double chi_refine_wave(const PV& P, const QuadCfg& q, const GLRule& gl, double b,
+__device__ double chi_refine_wave(const Pot& P, const QuadCfg& q, const GLRule& gl, double b,
                                   double E)
 {
     const int lane = threadIdx.x & 63;
@@ -44,7 +43,7 @@ __device__ double chi_refine_wave(const PV& P, const QuadCfg& q, const GLRule& g
     s.b2 = b * b;
     s.E = E;
     double rtop, rho;
-    ref_grid(plain(P), b, rtop, rho);
+    ref_grid(P, b, rtop, rho);
     const double r = ref_sample_r(rtop, rho, lane);
     const double D = D_of<double>(P, s.b2, E, r);
     const double Dup = __shfl(D, lane > 0 ? lane - 1 : 0, 64);

@@ -198,20 +198,9 @@ struct CandDraw {
     double U;
 };
 
-__device__ __forceinline__ CandDraw cand_draw_sn(int32_t s0, int32_t N, int32_t k, int32_t t,
-                                                 const dsmc_rng& rng)
+__device__ __forceinline__ CandDraw cand_draw(int32_t s0, int32_t N, int32_t k, int32_t t,
+                                              const dsmc_rng& rng)
 {
-    const U4 r = draw(rng, (uint32_t)t, (uint32_t)k, SLOT_CAND);
-    int32_t i = (int32_t)(((uint64_t)r.a * (uint64_t)N) >> 32);
-    int32_t j = (int32_t)(((uint64_t)r.b * (uint64_t)(N - 1)) >> 32);
-    if (j >= i) j += 1;
-    return CandDraw{s0 + i, s0 + j, unif53(r.c, r.d)};
-}
-
-__device__ __forceinline__ CandDraw cand_draw(const int32_t* __restrict__ cell_start, int32_t k,
-                                              int32_t t, const dsmc_rng& rng)
-{
-    const int32_t s0 = cell_start[k], N = cell_start[k + 1] - s0;
     const U4 r = draw(rng, (uint32_t)t, (uint32_t)k, SLOT_CAND);
     int32_t i = (int32_t)(((uint64_t)r.a * (uint64_t)N) >> 32);
     int32_t j = (int32_t)(((uint64_t)r.b * (uint64_t)(N - 1)) >> 32);
@@ -239,19 +228,9 @@ __device__ __forceinline__ bool cand_accept(const CandDraw& d, const V3<const T>
 // particle in slot t; its partner is drawn uniformly among the m = N-1-t
 // later slots and the pair collides with probability P = m lambda_k sigma(g) g
 // (values above 1 act as 1 and are counted).
-__device__ __forceinline__ CandDraw sbt_draw_sn(int32_t s0, int32_t N, int32_t k, int32_t t,
-                                                const dsmc_rng& rng, int32_t& m)
+__device__ __forceinline__ CandDraw sbt_draw(int32_t s0, int32_t N, int32_t k, int32_t t,
+                                             const dsmc_rng& rng, int32_t& m)
 {
-    m = N - 1 - t;
-    const U4 r = draw(rng, (uint32_t)t, (uint32_t)k, SLOT_SBT);
-    const int32_t j = t + 1 + (int32_t)(((uint64_t)r.a * (uint64_t)m) >> 32);
-    return CandDraw{s0 + t, s0 + j, unif53(r.c, r.d)};
-}
-
-__device__ __forceinline__ CandDraw sbt_draw(const int32_t* __restrict__ cell_start, int32_t k,
-                                             int32_t t, const dsmc_rng& rng, int32_t& m)
-{
-    const int32_t s0 = cell_start[k], N = cell_start[k + 1] - s0;
     m = N - 1 - t;
     const U4 r = draw(rng, (uint32_t)t, (uint32_t)k, SLOT_SBT);
     const int32_t j = t + 1 + (int32_t)(((uint64_t)r.a * (uint64_t)m) >> 32);
@@ -405,8 +384,8 @@ k_cand_decide(const int32_t* __restrict__ cell_start, int32_t n_cells,
                 const int32_t t = (int32_t)(cc[u] - au[u]);
                 mm[u] = 0;
                 if (!val[u]) dr[u] = CandDraw{0, 0, 1.0};
-                else if (SEL == SEL_NTC) dr[u] = cand_draw_sn(s0u[u], nu[u], kk[u], t, rng);
-                else dr[u] = sbt_draw_sn(s0u[u], nu[u], kk[u], t, rng, mm[u]);
+                else if (SEL == SEL_NTC) dr[u] = cand_draw(s0u[u], nu[u], kk[u], t, rng);
+                else dr[u] = sbt_draw(s0u[u], nu[u], kk[u], t, rng, mm[u]);
             }
             bool take[CAND_GROUP];
 #pragma unroll
