@@ -186,56 +186,11 @@ k_scan_down(const int32_t* in, int32_t* out, int64_t n, const int32_t* tile_off,
     }
 }
 
-// The whole scan in one workgroup, for few values: rows of 4 per thread, all
-// SCAN1_ROWS of a step loaded before one barrier.
-constexpr int SCAN1_THREADS = 1024;
-constexpr int SCAN1_ROWS = 4;
-constexpr int SCAN1_ROW = 4 * SCAN1_THREADS;
-
+// The whole scan in one workgroup, for few values.
 __global__ void __launch_bounds__(SCAN1_THREADS)
 k_scan_one(const int32_t* in, int32_t* out, int64_t n)
 {
-    __shared__ int32_t wsum[2][SCAN1_ROWS][SCAN1_THREADS / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t run = 0;
-    int par = 0;
-    for (int64_t b = 0; b < n; b += SCAN1_ROWS * SCAN1_ROW, par ^= 1) {
-        int32_t v[SCAN1_ROWS][4], s[SCAN1_ROWS], inc[SCAN1_ROWS];
-#pragma unroll
-        for (int q = 0; q < SCAN1_ROWS; ++q) {
-            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[q][e] = i + e < n ? in[i + e] : 0;
-        }
-#pragma unroll
-        for (int q = 0; q < SCAN1_ROWS; ++q) {
-            s[q] = inc[q] = v[q][0] + v[q][1] + v[q][2] + v[q][3];
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int32_t y = __shfl_up(inc[q], o, 64);
-                if (lane >= o) inc[q] += y;
-            }
-            if (lane == 63) wsum[par][q][w] = inc[q];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < SCAN1_ROWS; ++q) {
-            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
-            int32_t pre = run + inc[q] - s[q];
-#pragma unroll
-            for (int u = 0; u < SCAN1_THREADS / 64; ++u) {
-                const int32_t y = wsum[par][q][u];
-                if (u < w) pre += y;
-                run += y;
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (i + e < n) out[i + e] = pre;
-                pre += v[q][e];
-            }
-        }
-    }
-    if (threadIdx.x == 0) out[n] = run;
+    scan_one<false>(in, out, n, [](int64_t) {});
 }
 
 size_t scan_ws_bytes(int64_t n)
@@ -247,7 +202,7 @@ size_t scan_ws_bytes(int64_t n)
 // One or two steps of one workgroup (4 us for up to 16 384 values, 8 us for
 // 20 000) against three launches (11 and 16 us): a third and a fourth step, at
 // 4 us each, would take what they save.
-constexpr int64_t SCAN1_MAX = 2 * SCAN1_ROWS * SCAN1_ROW;
+constexpr int64_t SCAN1_MAX = 2 * SCAN1_STEP;
 
 int exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, void* ws, hipStream_t s)
 {

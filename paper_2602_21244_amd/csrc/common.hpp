@@ -242,6 +242,77 @@ __device__ __forceinline__ int wave_sum_i(int x)
     return x;
 }
 
+// Exclusive scan by one workgroup of SCAN1_THREADS, out[n] = total, SCAN1_STEP
+// values a step: rows of 4 per thread, all rows of a step loaded before one
+// barrier.  VEC: in and out are 16-byte aligned and distinct; without it out may
+// be in.  step(b): called by every thread in the step from value b on.
+constexpr int SCAN1_THREADS = 1024;
+constexpr int SCAN1_ROWS = 4;
+constexpr int SCAN1_ROW = 4 * SCAN1_THREADS;
+constexpr int SCAN1_STEP = SCAN1_ROWS * SCAN1_ROW;
+
+template <bool VEC, class Step>
+__device__ __forceinline__ void scan_one(const int32_t* in, int32_t* out, int64_t n,
+                                         const Step& step)
+{
+    __shared__ int32_t wsum[2][SCAN1_ROWS][SCAN1_THREADS / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int32_t run = 0;
+    int par = 0;
+    for (int64_t b = 0; b < n; b += SCAN1_STEP, par ^= 1) {
+        int32_t v[SCAN1_ROWS][4], s[SCAN1_ROWS], inc[SCAN1_ROWS];
+#pragma unroll
+        for (int q = 0; q < SCAN1_ROWS; ++q) {
+            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
+            if (VEC && i + 4 <= n) {
+                const int4 x = *reinterpret_cast<const int4*>(in + i);
+                v[q][0] = x.x;
+                v[q][1] = x.y;
+                v[q][2] = x.z;
+                v[q][3] = x.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[q][e] = i + e < n ? in[i + e] : 0;
+            }
+        }
+        step(b);
+#pragma unroll
+        for (int q = 0; q < SCAN1_ROWS; ++q) {
+            s[q] = inc[q] = v[q][0] + v[q][1] + v[q][2] + v[q][3];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int32_t y = __shfl_up(inc[q], o, 64);
+                if (lane >= o) inc[q] += y;
+            }
+            if (lane == 63) wsum[par][q][w] = inc[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < SCAN1_ROWS; ++q) {
+            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
+            int32_t pre = run + inc[q] - s[q];
+#pragma unroll
+            for (int u = 0; u < SCAN1_THREADS / 64; ++u) {
+                const int32_t y = wsum[par][q][u];
+                if (u < w) pre += y;
+                run += y;
+            }
+            if (VEC && i + 4 <= n) {
+                *reinterpret_cast<int4*>(out + i) =
+                    int4{pre, pre + v[q][0], pre + v[q][0] + v[q][1],
+                         pre + v[q][0] + v[q][1] + v[q][2]};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (i + e < n) out[i + e] = pre;
+                    pre += v[q][e];
+                }
+            }
+        }
+    }
+    if (threadIdx.x == 0) out[n] = run;
+}
+
 // Typed SoA view.
 template <typename T> struct V3 {
     T* x; T* y; T* z;

@@ -427,73 +427,20 @@ k_cand_decide(const int32_t* __restrict__ cell_start, int32_t n_cells,
 // atomically by the decide pass instead, one address per 64 chunks, cost it
 // more than this launch; its waves' atomic counts of clamped trials on the one
 // status word took 40 of its 55 us for a million trials.)
-constexpr int SCAN1_THREADS = 1024;
-constexpr int SCAN1_ROWS = 4;                     // rows of 4 096 counts per step
-constexpr int SCAN1_ROW = 4 * SCAN1_THREADS;
-
 template <int SEL>
 __global__ void __launch_bounds__(SCAN1_THREADS)
 k_chunk_scan(const SelTotals* __restrict__ tot, const int32_t* __restrict__ cnt,
              const int32_t* __restrict__ clamped, int32_t* __restrict__ off, dsmc_status* st)
 {
-    __shared__ int32_t wsum[2][SCAN1_ROWS][SCAN1_THREADS / 64];
     __shared__ int32_t csum[SCAN1_THREADS / 64];
     const int64_t n = tot->n_chunks;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t run = 0, nclamp = 0;
-    int par = 0;
-    for (int64_t b = 0; b < n; b += SCAN1_ROWS * SCAN1_ROW, par ^= 1) {
-        int4 v[SCAN1_ROWS];
-        int32_t s[SCAN1_ROWS], inc[SCAN1_ROWS];
-#pragma unroll
-        for (int q = 0; q < SCAN1_ROWS; ++q) {
-            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
-            v[q] = int4{0, 0, 0, 0};
-            if (i + 4 <= n) {
-                v[q] = *reinterpret_cast<const int4*>(cnt + i);
-            } else {
-                if (i < n) v[q].x = cnt[i];
-                if (i + 1 < n) v[q].y = cnt[i + 1];
-                if (i + 2 < n) v[q].z = cnt[i + 2];
-            }
-        }
+    int32_t nclamp = 0;
+    scan_one<true>(cnt, off, n, [&](int64_t b) {
         if (SEL == SEL_SBT)
-            for (int64_t i = b + threadIdx.x; i < n && i < b + SCAN1_ROWS * SCAN1_ROW;
-                 i += SCAN1_THREADS)
+            for (int64_t i = b + threadIdx.x; i < n && i < b + SCAN1_STEP; i += SCAN1_THREADS)
                 nclamp += clamped[i];
-#pragma unroll
-        for (int q = 0; q < SCAN1_ROWS; ++q) {
-            s[q] = inc[q] = v[q].x + v[q].y + v[q].z + v[q].w;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int32_t y = __shfl_up(inc[q], o, 64);
-                if (lane >= o) inc[q] += y;
-            }
-            if (lane == 63) wsum[par][q][w] = inc[q];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < SCAN1_ROWS; ++q) {
-            const int64_t i = b + q * SCAN1_ROW + 4 * threadIdx.x;
-            int32_t pre = run + inc[q] - s[q];
-#pragma unroll
-            for (int u = 0; u < SCAN1_THREADS / 64; ++u) {
-                const int32_t y = wsum[par][q][u];
-                if (u < w) pre += y;
-                run += y;
-            }
-            const int4 o = {pre, pre + v[q].x, pre + v[q].x + v[q].y,
-                            pre + v[q].x + v[q].y + v[q].z};
-            if (i + 4 <= n) {
-                *reinterpret_cast<int4*>(off + i) = o;
-            } else {
-                if (i < n) off[i] = o.x;
-                if (i + 1 < n) off[i + 1] = o.y;
-                if (i + 2 < n) off[i + 2] = o.z;
-            }
-        }
-    }
-    if (threadIdx.x == 0) off[n] = run;
+    });
     if (SEL == SEL_SBT && st) {
         nclamp = wave_sum_i(nclamp);
         if (lane == 0) csum[w] = nclamp;
