@@ -81,3 +81,27 @@ def test_cross_section_routes_agree(dev, api):
     c = api.transport_q2(E, 2.5e-9, pot, n_panels=48, n_gl=32).cpu().numpy()
     say("  Q2 routes: rel", np.abs(b / a - 1).max(), "48 panels:", np.abs(c / a - 1).max())
     assert np.all(np.abs(b / a - 1) <= 1e-9 + 4 * np.abs(c / a - 1))
+
+
+@pytest.mark.parametrize("n_gl", [2, 7, 8, 31, 32, 33])
+def test_cross_section_is_its_rules_sum(dev, api, n_gl):
+    """Q2 against the sum over the same panels and nodes of the batch entry point's
+    angles: rules of an even and an odd number of nodes on the table route and one
+    on the direct route, to 1e-10 (the angles' own bound is 1e-9 to 1e-7, of which
+    a node has a hundredth of the sum at most)."""
+    say("Q2 node by node", n_gl)
+    E = np.array([150.0, 300.0, 1000.0, 20000.0, 5e5])
+    pot, b_cut, n_panels = api.potential_jager(W.JAGER_PLACEHOLDER), 2.5e-9, 24
+    x, w = np.polynomial.legendre.leggauss(n_gl)
+    h = b_cut / n_panels
+    b = (h * (np.arange(n_panels)[:, None] + 0.5 * (1.0 + x))).ravel()
+    wb = np.tile(0.5 * h * w, n_panels) * b
+    g = np.sqrt(2.0 * W.KB * E / (W.AR_MASS / 2))
+    chi = api.deflect_jager(torch.as_tensor(np.tile(b, len(E)), device=dev),
+                            torch.as_tensor(np.repeat(g, b.size), device=dev), W.AR_MASS / 2, pot)
+    chi = chi.cpu().numpy().reshape(len(E), -1)
+    want = 2.0 * math.pi * np.sum(np.sin(chi) ** 2 * wb, axis=1)
+    Q = api.transport_q2(torch.as_tensor(E, device=dev), b_cut, pot, n_panels=n_panels, n_gl=n_gl)
+    err = np.abs(Q.cpu().numpy() / want - 1.0)
+    say("  rel", err)
+    assert err.max() < 1e-10

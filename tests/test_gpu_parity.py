@@ -335,6 +335,43 @@ def test_select_sizes_bitexact(orc, dev, api, n_cells, mean, lam_scale):
         assert np.array_equal(getattr(pairs, name)[:n].cpu().numpy(), sel["pair_" + name]), name
 
 
+@pytest.mark.parametrize("n_cells,mean,rule", [(1_048_577, 3, "ntc"), (1_048_577, 3, "sbt"),
+                                               (300_000, 30, "sbt")])
+def test_select_large_bitexact(orc, dev, api, n_cells, mean, rule):
+    """One cell more than 4 096 tiles of 256 hold (every tile then scans two
+    widths of cells), and enough trials (8.4 million) for the long chunks, some of
+    them clamped.  Pair lists and counts bit-exact."""
+    say("select large", n_cells, mean, rule)
+    pop = W.vhs_argon_1d(seed=n_cells, n=n_cells * mean, n_cells=n_cells)
+    cs, perm, vs, st = _gpu_sort(api, dev, pop, torch.float32)
+    v64 = vs.cpu().numpy().astype(np.float64)
+    if rule == "ntc":
+        mom = torch.zeros(6 * n_cells, dtype=torch.float64, device=dev)
+        api.moment_match(cs, vs, mom, api.L.MM_CAPTURE)
+        sel = orc.select_ntc(cs.cpu().numpy(), v64, pop.xs, pop.lam,
+                             mom.cpu().numpy().reshape(-1, 6), 5, 1)
+    else:
+        sel = orc.select_sbt(cs.cpu().numpy(), v64, pop.xs, pop.lam, 5, 1)
+    pairs = api.PairList(n_cells, int(sel["n_cand"]), dev)
+    lam = torch.as_tensor(pop.lam, device=dev)
+    if rule == "ntc":
+        api.select_pairs_ntc(cs, vs, pop.xs, lam, mom, 5, 1, pairs, st=st)
+    else:
+        api.select_pairs_sbt(cs, vs, pop.xs, lam, 5, 1, pairs, st=st)
+    s = api.read_status(st)
+    n = int(sel["pair_cnt"].sum())
+    say(f"  {sel['n_cand']} candidates or trials, {n} pairs")
+    assert s.n_cand == sel["n_cand"] and s.n_pairs == n
+    if rule == "sbt":
+        say(f"  {sel['n_clamped']} clamped")
+        assert s.prob_clamped == sel["n_clamped"]
+        assert mean < 30 or sel["n_cand"] >= 1 << 23
+    assert np.array_equal(pairs.cnt.cpu().numpy(), sel["pair_cnt"])
+    assert np.array_equal(pairs.off.cpu().numpy(), sel["pair_off"])
+    for name in ("i", "j", "cell"):
+        assert np.array_equal(getattr(pairs, name)[:n].cpu().numpy(), sel["pair_" + name]), name
+
+
 def test_sbt_step_and_overflow(orc, dev, api):
     say("sbt step")
     pop = W.ragged_population(15, 250, 120, empty_frac=0.1)
@@ -681,6 +718,60 @@ def test_deflect_many_refined_pairs_bitwise(dev, api, dtype):
     many = api.deflect_jager(b.repeat(k), g.repeat(k), mr, pot, st=st)
     assert api.read_status(st).root_fail == 0
     assert torch.isfinite(one).all() and torch.equal(many, one.repeat(k))
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_deflect_many_kinked_pairs_bitwise(orc, dev, api, dtype, mixed):
+    """Pairs whose range crosses the branches' meeting point (20 to 200 km/s,
+    b < 0.1 nm), 1 600 of them per CU of 256, alone and in turn with orbiting
+    ones: either end of a workgroup's list fills, and both do, several times over.
+    The batch's bounds, and a pair's angle does not depend on its neighbours."""
+    say("deflect many kinked", dtype, mixed)
+    rng = np.random.default_rng(41)
+    n, mr = 2048, W.AR_MASS / 2
+    pot = api.potential_jager(W.JAGER_PLACEHOLDER)
+    g = np.exp(rng.uniform(np.log(2e4), np.log(2e5), n))
+    b = 1e-10 * rng.random(n)
+    if mixed:
+        bo, go, _ = W.deflection_batch(seed=23, n=1 << 17)
+        hard = api.deflect_jager(torch.as_tensor(bo, device=dev), torch.as_tensor(go, device=dev),
+                                 mr, pot).abs().cpu().numpy() > np.pi
+        m = min(n // 2, int(hard.sum()))
+        b[:2 * m:2], g[:2 * m:2] = bo[hard][:m], go[hard][:m]
+        assert m > 50
+    b, g = torch.as_tensor(b).to(dtype), torch.as_tensor(g).to(dtype)
+    ref, bad = orc.chi_batch(orc.potential_jager(W.JAGER_PLACEHOLDER), b.double().numpy(),
+                             g.double().numpy(), mr, n_threads=8)
+    b, g = b.to(dev), g.to(dev)
+    one = api.deflect_jager(b, g, mr, pot)
+    assert not bad.any()
+    check_chi(one.double().cpu().numpy(), ref, "f64" if dtype == torch.float64 else "f32", "single")
+    st = api.new_status(dev)
+    many = api.deflect_jager(b.repeat(200), g.repeat(200), mr, pot, st=st)
+    assert api.read_status(st).root_fail == 0
+    assert torch.equal(many, one.repeat(200))
+
+
+def test_deflect_potentials_in_turn(dev, api):
+    """Calls with six potentials in turn, each with its own set-up: as with one
+    at a time, twice over."""
+    say("deflect potentials in turn")
+    b, g, mr = (torch.as_tensor(x, device=dev) if i < 2 else x
+                for i, x in enumerate(W.deflection_batch(seed=5, n=300)))
+    pa = W.JAGER_PLACEHOLDER
+    pots = [api.potential_jager(dataclasses.replace(pa, a1=pa.a1 * (1 + 0.001 * k)))
+            for k in range(4)]
+    pots += [api.potential_hs(3.0), api.potential_jager(dataclasses.replace(pa, a1=-11.7, A=4e20))]
+    alone = []
+    for p in pots:
+        for _ in range(2):
+            c = api.deflect_jager(b, g, mr, p)
+        alone.append(c)
+    assert len({tuple(c.cpu().numpy()[:50]) for c in alone}) == len(pots)
+    for _ in range(2):
+        for p, c in zip(pots, alone):
+            assert torch.equal(api.deflect_jager(b, g, mr, p), c)
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
