@@ -293,7 +293,10 @@ CQ_HD CtRoot<T> ct_root(const TabPot& t, const QuadCfg& q, T b, T E, bool low)
     const T rz = T(t.P.r_zero);
     const T r_top = b > rz ? b : rz;
     T w1 = T(1) / r_top;
-    T f1 = T(1) - b2 * (w1 * w1) - ct_value<T, FAR>(t, w1) * iE;
+    // At r = b > r_zero D is -V/E > 0, which the rounding of 1/b or, at w near 0,
+    // of the table would hide for distant pairs; b - b keeps an infinite b's NaN.
+    const T V1 = ct_value<T, FAR>(t, w1);
+    T f1 = b > rz ? (b - b) + fabs(V1) * iE : T(1) - b2 * (w1 * w1) - V1 * iE;
     if (f1 <= T(0)) {
         R.w = w1;
         R.flag = low;

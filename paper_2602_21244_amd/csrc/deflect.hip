@@ -492,6 +492,9 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
             CtLane<T> c{T(0), false, 0.0};
             if (active) {
                 job.inputs(i, b, E);
+                // finite distances whose square leaves the type's range
+                constexpr double B_TOP = sizeof(T) == 8 ? 1e100 : 1e15;
+                if (b > B_TOP && b < INFINITY) b = B_TOP;
                 if (__builtin_expect(E < a.e_far && T(E) != T(0), 0)) {
                     const CtLane<double> d = ct_slow_lane(t, a.q, gl, b, E);
                     c = CtLane<T>{T(d.chi), d.flag, d.kink_w};

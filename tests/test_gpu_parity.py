@@ -803,6 +803,27 @@ def test_deflect_slow_distant_pairs(orc, dev, api, dtype, g_lo, g_hi, b_lo, b_hi
     assert err < (1e-12 if dtype == torch.float64 else 64 * 2.0 ** -24)
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_deflect_distant_pairs_are_not_refined(dev, api, dtype):
+    """Below the orbiting energy, 6 nm to 10 um apart: V(b)/E is below rounding,
+    and the pairs keep the one-rule result, with the refinement and without.
+    Distances whose square leaves the type's range give no deflection either."""
+    say("deflect distant pairs", dtype)
+    g = torch.linspace(100.0, 480.0, 3000, dtype=dtype, device=dev)
+    b = torch.logspace(math.log10(6e-9), -5, 3000, dtype=dtype, device=dev).flip(0)
+    pot, mr = api.potential_jager(W.JAGER_PLACEHOLDER), W.AR_MASS / 2
+    on = api.deflect_jager(b, g, mr, pot)
+    off = api.deflect_jager(b, g, mr, pot, quad=api.quad_struct(refine=-1))
+    assert torch.equal(on, off) and on.abs().max() < 1e-3
+    b = torch.tensor([1e20, 1e150, 1e190, 1e290] if dtype == torch.float64 else [1e10, 1e25],
+                     dtype=dtype, device=dev)
+    st = api.new_status(dev)
+    for speed in (1.0, 300.0, 1e4):
+        c = api.deflect_jager(b, torch.full_like(b, speed), mr, pot, st=st)
+        assert c.abs().max() < (1e-14 if dtype == torch.float64 else 1e-6), (speed, c)
+    assert api.read_status(st).root_fail == 0
+
+
 @pytest.mark.parametrize("max_iter,ratio", [(1, 0.55), (60, 0.9), (60, 0.99)])
 def test_deflect_table_root_settings(orc, dev, api, max_iter, ratio):
     """Root settings off their defaults, for the argon set and one whose branches
