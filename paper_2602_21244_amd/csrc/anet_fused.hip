@@ -7,7 +7,7 @@
 // inputs) runs on the VALU in FP32; every further layer is D = W H^T with
 // v_mfma_f32_32x32x16_bf16, H read from LDS ([row][k], padded rows) and W
 // streamed from L2 in fragment order (one coalesced 1 KB load per fragment,
-// AF_PF fragments ahead), each wave holding the accumulators of its units for
+// PF fragments ahead), each wave holding the accumulators of its units for
 // every row of the tile, so the layer's output overwrites its input in LDS.
 // D = W H^T puts four consecutive units of one row in a lane: bias, SiLU,
 // one 16-byte store of the pre-activation and one 8-byte LDS write.
@@ -29,8 +29,8 @@
 // bit for bit: a training run amplifies a rounding (a bf16 weight that flips)
 // to 1e-6 of the next loss.  The walk and the column sums go by slabs of AF_SLAB
 // rows, whose FP32 deltas share one buffer: 2^20 rows of the paper's network
-// take 16.7 GB instead of 22.4 (17.8 layer by layer) and 13.7 ms instead of
-// 13.6 (46 ms).
+// take 17.2 GB instead of 23.2 (18.6 layer by layer) and 14.4 ms instead of
+// 14.2 (42 ms).
 #include <math.h>
 
 #include "anet_fused.hpp"
@@ -125,7 +125,7 @@ k_anet_pack(AfPack p)
 }
 
 // acc[u][r] += W(units of tile u0 + u) H(rows of block rb0 + r)^T over K.
-// Fragments are loaded AF_PF k steps ahead (K is a multiple of 16 AF_PF).
+// Fragments are loaded PF k steps ahead (K is a multiple of 16 PF).
 template <int NU, int NR, int PF>
 __device__ __forceinline__ void af_gemm(const __bf16* __restrict__ wp, int KS, int u0, int rb0,
                                         const __bf16* hs, int ld, floatx16a (&acc)[NU][NR])
@@ -769,6 +769,12 @@ static int widest(const AnetShape& a)
 // want many small tiles to spread over the CUs (4 096 rows are 128 tiles of
 // 32) and many rows want large ones to reuse each fragment; the backward's
 // epilogue holds too many values for 128 rows (76 registers spilled).
+// Forward with 32, 64 and 128 rows a tile: 8 192 rows 39, 48 and 71 us; 12 288
+// 63, 49 and 71; 16 384 66, 51 and 71; 24 576 92, 88 and 76; 32 768 118, 96 and
+// 84; 49 152 176, 140 and 150; 65 536 223, 187 and 167 (between 16 384 and
+// 65 536 the better of 64 and 128 alternates with how full the last wave is).
+// Backward with 32 and 64: 4 096 rows 88 and 108 us, 8 192 119 and 131, 16 384
+// 247 and 250, 65 536 908 and 935.
 static int fwd_row_blocks(int64_t R) { return R <= 8192 ? 1 : (R <= 32768 ? 2 : 4); }
 static int bwd_row_blocks(int64_t R) { return R <= 8192 ? 1 : 2; }
 

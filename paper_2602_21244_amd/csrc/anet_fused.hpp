@@ -6,9 +6,9 @@
 namespace dsmc {
 
 constexpr int AF_MAX_LAYERS = DSMC_ANET_MAX_LAYERS;
-// Rows of FP32 deltas held at a time (1.9 GB for the paper's network).  The
+// Rows of FP32 deltas held at a time (2 GB for the paper's network).  The
 // kernels of a slab drain before the next one starts: with 32 768 rows the
-// backward of 262 144 took 3.74 ms, as one slab 3.42 ms.
+// backward of 262 144 takes 3.82 ms, as one slab 3.56 ms.
 constexpr int64_t AF_SLAB = 1 << 18;
 constexpr int AF_SPLITS = 16;   // K splits of the weight-gradient kernel (those of the tiled GEMM's)
 

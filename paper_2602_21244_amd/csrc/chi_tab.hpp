@@ -668,7 +668,7 @@ inline void make_ct_nodes(const GLRule& gl, CtNodeF* nd)
 // Whether the table kernels take the potential: below the orbiting energy
 // every root lies on the dispersion branch, and the table resolves V.  That is,
 // at points between the interpolation nodes of every interval, within 2e-14 of
-// the direct value relative to its terms' magnitude (the argon set: 8e-15); at
+// the direct value relative to its terms' magnitude (the argon set: 4e-15); at
 // w < w_far the dispersion sum has to, and the table's absolute error sets
 // *e_far, the energy from which it moves F = D(r(t)) by less than 1e-15 (twice
 // the largest error found at the points over 1e-15).

@@ -239,11 +239,13 @@ __device__ __forceinline__ void count_root_fail(dsmc_status* st)
 // in runs: a wave that refined its own took up to 20 of its 64).  Chunks are
 // dealt to workgroups first, so a small batch spreads over the CUs.
 //
-// What bounds it: VALU issue, two thirds of the cycles (7 000 instructions per
-// 64 pairs in FP64, half of them FP64 arithmetic), then the table reads (48
-// bytes per lane and node in FP64, 16 in FP32, at random rows).  2^20 pairs in FP64: 0.33 ms (2.2 ms with V
-// evaluated directly and a second pass for the flagged pairs, bound by the
-// FP64 VALU); Phase A of 3.5 million pairs in FP32: 0.70 ms (3.3 ms).
+// What bounds it: VALU issue, three quarters of the cycles (9 300 instructions
+// per 64 pairs in FP64, the refinement's among them, 55 % of them FP64
+// arithmetic), then the table reads (48 bytes per lane and node in FP64, 16 in
+// FP32, at random rows: the LDS is busy a third of the cycles, half of that
+// with bank conflicts).  2^20 pairs in FP64: 0.34 ms (2.2 ms with V evaluated
+// directly and a second pass for the flagged pairs, bound by the FP64 VALU);
+// Phase A of 3.5 million pairs in FP32: 0.55 ms (3.3 ms).
 // ------------------------------------------------------------------------
 constexpr int TAB_THREADS = 1024;
 
@@ -467,8 +469,8 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
     // on by a few blocks in each round so a workgroup does not meet the same
     // part of a periodic input again.  The waves take them in turn as they get
     // free (the four of a SIMD are not served evenly) until the list may fill,
-    // then all work through the list: 2^20
-    // FP64 pairs 334 us, 391 us with a fixed chunk per wave and a barrier each.
+    // then all work through the list: 2^20 FP64 pairs 334 us, 391 us with a
+    // fixed chunk per wave and a barrier each.
     const int64_t per_round = (int64_t)gridDim.x * WAVES;
     for (;;) {
         for (;;) {

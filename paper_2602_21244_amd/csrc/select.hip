@@ -115,7 +115,10 @@ constexpr int CAND_WIN = 4;      // scalar cell window of a group (see k_cand_de
 // enough to give every wave a long chunk; then 16, whose staged runs are
 // longer and whose counts are fewer (53 million candidates: decide 0.46 ms
 // against 0.63 ms with 4, copy 0.07 against 0.14 ms; 17 000 candidates:
-// decide 13 us with 4 against 32 us with 16).
+// decide 13 us with 4 against 32 us with 16).  The stage with 4 and with 16
+// around the line: 3.1 million candidates 77 and 84 us, 4.7 million 100 and
+// 106, 6.2 million 126 and 123, 9.3 million 175 and 169, 74 million 1 287 and
+// 1 245.
 constexpr int CHUNK_MIN = 64 * CAND_GROUP;
 constexpr int64_t CHUNK_LONG_FROM = (int64_t)1 << 23;
 __device__ __forceinline__ int cand_rounds(int64_t total)

@@ -69,7 +69,8 @@ def test_struct_layout_matches_header():
             assert int(got[f"{cname}.{fname}"]) == getattr(py, fname).offset, (cname, fname)
 
 
-@pytest.mark.parametrize("dims", [(2, 128, 256, 512, 512, 256, 128, 1), (2, 512, 512, 1)])
+@pytest.mark.parametrize("dims", [(2, 512, 512, 512, 256, 128, 1), (2, 512, 512, 1),
+                                  (2, 128, 256, 512, 512, 256, 128, 1)])
 @pytest.mark.parametrize("rows", [1 << 20, 12_000_000])
 def test_angle_network_workspace(lib, dims, rows):
     """Of a large batch, the angle network's workspace holds per row no more than
