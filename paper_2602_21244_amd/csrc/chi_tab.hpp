@@ -14,8 +14,8 @@
 // nodes in FP64; FP32 polynomials are the same ones cut to degree 3.
 //
 // In the first intervals V ~ w^6 falls below the table's error, which is an
-// absolute one there (1e-16 K for the argon set), and the angle sees it divided
-// by E.  Pairs below an energy that this error sets (e_far: 0.12 K, 10 m/s, for
+// absolute one there (1e-17 K for the argon set), and the angle sees it divided
+// by E.  Pairs below an energy that this error sets (e_far: 0.15 K, 11 m/s, for
 // argon; one pair in 10^5 of a gas at 273 K) therefore take V at w < w_far from
 // the dispersion sum itself (ct_slow_lane, in FP64, and their refinement):
 // damping and repulsion are below rounding there, and the sum has V's relative
@@ -668,11 +668,14 @@ inline void make_ct_nodes(const GLRule& gl, CtNodeF* nd)
 // Whether the table kernels take the potential: below the orbiting energy
 // every root lies on the dispersion branch, and the table resolves V.  That is,
 // at points between the interpolation nodes of every interval, within 2e-14 of
-// the direct value relative to its terms' magnitude (the argon set: 4e-15); at
-// w < w_far the dispersion sum has to, and the table's absolute error sets
-// *e_far, the energy from which it moves F = D(r(t)) by less than 1e-15 (twice
-// the largest error found at the points over 1e-15).
-constexpr double CT_E_FAR = 1e-3;   // most of the orbiting energy that e_far may be
+// the direct value relative to its terms' magnitude (the argon set: 4e-15).
+// Where slow pairs are on the long-range side of that, 1e-12 does (the angle's
+// own bound is 1e-9): of the dispersion sum at w < w_far (the argon set: 4e-16;
+// shorter ranges of the damping leave more repulsion there) and of the table
+// just above (longer ones bring w_far down).  The table's absolute error at these points sets *e_far, the
+// energy from which it moves F = D(r(t)) by less than 2e-16 (twice the largest
+// error found over 2e-16).
+constexpr double CT_E_FAR = 0.05;   // most of the orbiting energy that e_far may be
 inline bool ct_resolves(const Pot& P, const CtRule& rule, double* e_far)
 {
     if (P.p.kind != DSMC_POT_JAGER || !(P.r_floor > 1.01 * P.r_sw)) return false;
@@ -685,21 +688,20 @@ inline bool ct_resolves(const Pot& P, const CtRule& rule, double* e_far)
             const double x = -0.4 + 0.25 * m, k = (i < CT_LR ? i : i - CT_LR) + (0.5 + x);
             const double w = i < CT_LR ? k / s.inv_lr : s.w_sw + k / s.inv_sr;
             const double V = i < CT_LR ? ct_far(P, w) : ct_near(P, w);
-            double t = c[0] + x * (c[1] + x * (c[2] + x * (c[3] + x * (c[4] + x * c[5]))));
-            double mag = fabs(V);
+            const double t = c[0] + x * (c[1] + x * (c[2] + x * (c[3] + x * (c[4] + x * c[5]))));
+            double mag = fabs(V), d, e;
             if (i < CT_LR) {
                 const double r = 1.0 / w;
                 mag += 2.0 * P.p.A * exp(P.p.a1 * r + P.p.a2 * r * r + P.p.am1 * w + P.p.am2 * w * w);
             }
-            if (w < s.w_far) {
-                double d, e;
-                if (!(fabs(t - V) <= far_err)) far_err = fabs(t - V);
-                t = ct_tail(P.p, w, d, e);
-            }
-            if (!(fabs(t - V) <= 2e-14 * mag)) return false;
+            if (w < s.w_far && !(fabs(ct_tail(P.p, w, d, e) - V) <= 1e-12 * mag)) return false;
+            const double err = fabs(t - V);
+            if (err <= 2e-14 * mag) continue;
+            if (i >= CT_LR || !(w < s.w_far || err <= 1e-12 * mag)) return false;
+            if (!(err <= far_err)) far_err = err;
         }
     }
-    *e_far = 2e15 * far_err;
+    *e_far = 1e16 * far_err;
     return *e_far <= CT_E_FAR * P.e_scan;
 }
 

@@ -777,23 +777,25 @@ def test_deflect_potentials_in_turn(dev, api):
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("g_lo,g_hi,b_lo,b_hi", [(1e-3, 1e-3, 3e-8, 1e-6), (0.03, 3.0, 3e-9, 3e-8),
                                                  (3.0, 30.0, 1e-9, 1e-8)])
-def test_deflect_slow_distant_pairs(orc, dev, api, dtype, g_lo, g_hi, b_lo, b_hi):
+@pytest.mark.parametrize("change", [{}, {"beta_tt": 3.0}, {"beta_tt": 4.6, "a1": -2.6}])
+def test_deflect_slow_distant_pairs(orc, dev, api, dtype, g_lo, g_hi, b_lo, b_hi, change):
     """Pairs far below collision speeds that pass so far apart that the deflection
     is weak (first order in V, 15 pi / 16 C_6 / (E b^6); chi = -1.1e-9 at 1 mm/s
     and 1 um): V is small beside its value at the usual distances but not beside
     E.  They keep the angle itself to the rounding of a sum of 64 nodes and the
-    oracle's own error: 1e-12, in FP32 64 ulp of 1."""
-    say("deflect slow distant pairs", dtype, g_lo, g_hi)
+    oracle's own error: 1e-12, in FP32 64 ulp of 1.  Also for a longer damping
+    and for a shorter one with more repulsion where it ends."""
+    say("deflect slow distant pairs", dtype, g_lo, g_hi, change)
     rng = np.random.default_rng(31)
-    n = 2049
+    n, p = 2049, dataclasses.replace(W.JAGER_PLACEHOLDER, **change)
     b = np.exp(rng.uniform(np.log(b_lo), np.log(b_hi), n))
     g = np.exp(rng.uniform(np.log(g_lo), np.log(g_hi), n))
     b[0], b[1], g[:2] = b_hi, b_hi / 10, g_lo
     b, g = torch.as_tensor(b).to(dtype), torch.as_tensor(g).to(dtype)
-    ref, bad = orc.chi_batch(orc.potential_jager(W.JAGER_PLACEHOLDER), b.double().numpy(),
+    ref, bad = orc.chi_batch(orc.potential_jager(p), b.double().numpy(),
                              g.double().numpy(), W.AR_MASS / 2, n_threads=8)
     got = api.deflect_jager(b.to(dev), g.to(dev), W.AR_MASS / 2,
-                            api.potential_jager(W.JAGER_PLACEHOLDER)).double().cpu().numpy()
+                            api.potential_jager(p)).double().cpu().numpy()
     E = 0.5 * (W.AR_MASS / 2) * g.double().numpy() ** 2 / W.KB
     first = 15 * np.pi / 16 * W.JAGER_PLACEHOLDER.C[0] / (E * (b.double().numpy() * 1e10) ** 6)
     weak = (first < 0.1) & (bad == 0)
