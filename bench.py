@@ -634,8 +634,8 @@ def phase_a_split_compare(api, L, nets, v, pairs, col_ws, st, stream, cap, n_pai
 
 
 def quadrature_valu_roofline(ms_phase_a):
-    """Executed VALU flop of the in-step quadrature (lane rule plus its FP64
-    refinement pass) from the committed rocprofv3 operation counts, over the
+    """Executed VALU flop of the in-step quadrature (lane rule and FP64
+    refinement of one kernel) from the committed rocprofv3 operation counts, over the
     live event time of that Phase A; null when the counts were taken on
     another build of deflect.hip."""
     from paper_2602_21244_amd.build import compile_signature
@@ -644,16 +644,15 @@ def quadrature_valu_roofline(ms_phase_a):
         return None
     try:
         blob = json.loads(open(path).read().split("```json", 1)[1].split("```", 1)[0])
-        ks = [blob["kernels"]["k_phaseA_jager_f32"], blob["kernels"]["k_refine<PhaseAJagerJob<float> >"]]
+        k = blob["kernels"]["k_chi_tab<float, PhaseAJagerTab<float> >"]
     except (IndexError, KeyError, ValueError):
         return None
     if blob.get("compile_signature") != compile_signature(blob.get("source", "deflect.hip")):
         return None
-    f32 = sum(k["fp32_flop"] for k in ks)
-    f64 = sum(k["fp64_flop"] for k in ks)
+    f32, f64 = k["fp32_flop"], k["fp64_flop"]
     t = ms_phase_a * 1e-3
     r32, r64 = f32 / t, f64 / t
-    return {"bound": "alu", "kernels": "k_phaseA_jager_f32 + k_refine (FP64)",
+    return {"bound": "alu", "kernels": "k_chi_tab (FP32 lanes, FP64 refinement)",
             "fp32_flop": f32, "fp64_flop": f64, "ms": ms_phase_a,
             "achieved_fp32_TFLOPs": r32 / 1e12, "achieved_fp64_TFLOPs": r64 / 1e12,
             "peak_fp32_TFLOPs": PEAK_FP32 / 1e12, "peak_fp64_TFLOPs": PEAK_FP64 / 1e12,
