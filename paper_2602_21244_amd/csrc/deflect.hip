@@ -239,13 +239,13 @@ __device__ __forceinline__ void count_root_fail(dsmc_status* st)
 // in runs: a wave that refined its own took up to 20 of its 64).  Chunks are
 // dealt to workgroups first, so a small batch spreads over the CUs.
 //
-// What bounds it: VALU issue, three quarters of the cycles (9 300 instructions
+// What bounds it: VALU issue, three quarters of the cycles (9 000 instructions
 // per 64 pairs in FP64, the refinement's among them, 55 % of them FP64
 // arithmetic), then the table reads (48 bytes per lane and node in FP64, 16 in
 // FP32, at random rows: the LDS is busy a third of the cycles, half of that
-// with bank conflicts).  2^20 pairs in FP64: 0.34 ms (2.2 ms with V evaluated
+// with bank conflicts).  2^20 pairs in FP64: 0.33 ms (2.2 ms with V evaluated
 // directly and a second pass for the flagged pairs, bound by the FP64 VALU);
-// Phase A of 3.5 million pairs in FP32: 0.55 ms (3.3 ms).
+// Phase A of 3.5 million pairs in FP32: 0.53 ms (3.3 ms).
 // ------------------------------------------------------------------------
 constexpr int TAB_THREADS = 1024;
 
@@ -314,7 +314,7 @@ __device__ __forceinline__ double lane_value(double x, int src)
 // chi of one pair by the whole wave with V from the table: the steps of
 // chi_refine_wave in w = 1/r, where the nodes need no division, D'' comes
 // from the polynomial, and sinh and cosh of a node share one exponential.
-template <bool FAR>
+template <CtRange RG>
 __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& gl, double b,
                                                  double E)
 {
@@ -324,7 +324,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
     const double rtop = b > t.P.r_zero ? b : t.P.r_zero;
     const double wtop = 1.0 / rtop;
     const double w = wtop * exp(lane * (log(rtop / (0.98 * t.P.r_floor)) * (1.0 / (REF_SAMPLES - 1))));
-    const double D = 1.0 - b2 * (w * w) - ct_value<double, FAR>(t, w) * iE;
+    const double D = 1.0 - b2 * (w * w) - ct_value<double, RG>(t, w) * iE;
     const double Dup = __shfl(D, lane > 0 ? lane - 1 : 0, 64);
     const double Ddn = __shfl(D, lane < 63 ? lane + 1 : 63, 64);
     const uint64_t neg = __ballot(D <= 0.0);
@@ -341,7 +341,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
         for (int rd = 0; rd < REF_ROUNDS; ++rd) {
             const double x = ref_x(a, c, lane);
             double dV;
-            ct_V<true, FAR>(t, x, dV);
+            ct_V<true, RG>(t, x, dV);
             const double f = -2.0 * b2 * x - dV * iE;
             const uint64_t pos = __ballot(f >= 0.0);
             const int L = ref_pick(pos ? __ffsll((unsigned long long)pos) - 1 : 64);
@@ -353,7 +353,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
         wm = (fc > fa) ? a - fa * (c - a) / (fc - fa) : 0.5 * (a + c);
         wm = fmin(fmax(wm, a), c);
         d2m = (fc - fa) / (c - a);
-        dm = 1.0 - b2 * (wm * wm) - ct_value<double, FAR>(t, wm) * iE;
+        dm = 1.0 - b2 * (wm * wm) - ct_value<double, RG>(t, wm) * iE;
         if (dm <= 0.0) {   // the dip reaches zero: the largest root lies outside it
             wa = outer;
             wb = wm;
@@ -365,7 +365,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
     double fl = 1.0, fh = -1.0;
     for (int rd = 0; rd < REF_ROUNDS && wb > wa; ++rd) {
         const double x = ref_x(wa, wb, lane);
-        const double f = 1.0 - b2 * (x * x) - ct_value<double, FAR>(t, x) * iE;
+        const double f = 1.0 - b2 * (x * x) - ct_value<double, RG>(t, x) * iE;
         const uint64_t np = __ballot(!(f > 0.0));
         const int L = ref_pick(np ? __ffsll((unsigned long long)np) - 1 : 64);
         wa = lane_value(x, L - 1);
@@ -376,7 +376,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
     double w0 = (wb > wa && fl > fh) ? wa + fl * (wb - wa) / (fl - fh) : wb;
     w0 = fmin(fmax(w0, wa), wb);
     double dV, d2V;
-    const double Vmin = ct_V2<FAR>(t, w0, dV, d2V), beta = b * w0;
+    const double Vmin = ct_V2<RG>(t, w0, dV, d2V), beta = b * w0;
     // sinh map of t around the interior peak, else around t = 0, where
     // F / t^2 ~ Q0 + Q2 t^2
     double c = 0.0, h;
@@ -405,7 +405,7 @@ __device__ __forceinline__ double ct_refine_wave(const TabPot& t, const GLRule& 
         const double e = exp(lo + len * (pnl + gl.t[j])), ei = 1.0 / e;
         const double tt = c + 0.5 * h * (e - ei);
         I += gl.w[j] * len * (0.5 * h * (e + ei)) *
-             ct_node<double, FAR>(t, w0, beta * beta, Vmin, iE, tt, smax, nonpos);
+             ct_node<RG>(t, w0, beta * beta, Vmin, iE, tt, smax, nonpos);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) I += __shfl_xor(I, o, 64);
@@ -469,8 +469,8 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
     // on by a few blocks in each round so a workgroup does not meet the same
     // part of a periodic input again.  The waves take them in turn as they get
     // free (the four of a SIMD are not served evenly) until the list may fill,
-    // then all work through the list: 2^20 FP64 pairs 334 us, 391 us with a
-    // fixed chunk per wave and a barrier each.
+    // then all work through the list: 2^20 FP64 pairs 334 us, against 391 us
+    // with a fixed chunk per wave and a barrier each.
     const int64_t per_round = (int64_t)gridDim.x * WAVES;
     for (;;) {
         for (;;) {
@@ -538,8 +538,8 @@ k_chi_tab(Job job, int64_t n, TabArgs<T> a, dsmc_status* st)
         for (int k = wave; k < pairs; k += WAVES) {
             const double b = list.b[k], E = list.E[k];
             double cr;
-            if (__builtin_expect(E < a.e_far, 0)) cr = ct_refine_wave<true>(t, gl, b, E);
-            else cr = ct_refine_wave<false>(t, gl, b, E);
+            if (__builtin_expect(E < a.e_far, 0)) cr = ct_refine_wave<CT_SLOW>(t, gl, b, E);
+            else cr = ct_refine_wave<CT_LOW>(t, gl, b, E);
             if (lane == 0) {
                 if (cr != cr) {
                     count_root_fail(st);
